@@ -104,6 +104,8 @@ struct LayerW {
   uint16_t *Wb = nullptr;   // [out][in] bf16
   uint16_t *Wtb = nullptr;  // [in][out] bf16
   float *b = nullptr;
+  uint16_t *Ws = nullptr;   // W's three bf16 parts (split.hip; the first layer padded to ldG)
+  uint16_t *Wts = nullptr;  // Wt's
   int n_in = 0, n_out = 0;
 };
 
@@ -123,6 +125,8 @@ struct nnp_model {
   // per species: [D][M * n1] = members' first-layer W^T side by side (dE/dG)
   std::vector<float *> Wdg;
   std::vector<uint16_t *> Wdg_b;
+  std::vector<uint16_t *> Wdg_s;         // parts of Wdg
+  bool split = false;                    // float32 model whose GEMMs run on the bf16 matrix cores (split.hip)
   std::vector<void *> weight_allocs;
   int cap = 256;                         // neighbour capacity per atom
   int ldG = 0;                           // row stride of the AEV buffer G: the AEV length
@@ -139,12 +143,11 @@ struct nnp_model {
   DevBuf wave_atom;                      // AEV models: centre of each wave of the per-centre kernels
   size_t max_lds = 64 * 1024;            // LDS bytes one workgroup may use on this device
   std::vector<DevBuf> H, Gd;
-  // fused hidden-layer chain (bfloat16 models whose hidden widths allow it)
+  // fused hidden-layer chain (models whose hidden widths allow it)
   bool chain = false;
-  bool chain_rt2 = false;                // 64-row workgroups fit the LDS
   DevBuf chain_nets;                     // [member][species] ChainNet
   ChainLaunch chain_proto{};             // strides and LDS layout, filled at creation
-  size_t chain_lds = 0;
+  size_t chain_lds = 0;                  // LDS bytes of 16 rows
   // host staging (pinned) for per-call descriptors: a ring of slots, each
   // reused once the copy that last read it has completed
   StageSlot stage[kStageSlots];
@@ -198,6 +201,20 @@ static int upload(nnp_model *m, const void *host, size_t bytes, void **dev) {
   HIP_TRY(hipMalloc(dev, bytes));
   m->weight_allocs.push_back(*dev);
   HIP_TRY(hipMemcpy(*dev, host, bytes, hipMemcpyHostToDevice));
+  return NNP_OK;
+}
+
+// The three bf16 parts of a device matrix [rows][K] (columns padded to Kp)
+// into *out, allocated here (for `copies` such matrices) where it is null.
+static int split_parts(nnp_model *m, const float *src, int rows, int K, int Kp, int copies, uint16_t **out) {
+  if (!*out) {
+    void *p = nullptr;
+    HIP_TRY(hipMalloc(&p, (size_t)copies * rows * Kp * 6));
+    m->weight_allocs.push_back(p);
+    *out = (uint16_t *)p;
+  }
+  launch_split_weights(src, rows, K, K, Kp, *out, nullptr);
+  HIP_TRY(hipGetLastError());
   return NNP_OK;
 }
 
@@ -349,6 +366,22 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
   }
   m->layers.resize((size_t)m->M * S * L);
   const float *wp = d->weights;
+  // float32 on the bfloat16 matrix cores: hidden widths that are whole
+  // 32-column chunks, weights with a finite first part (below a rounding of
+  // the largest float)
+  if (m->precision == NNP_FP32 && L >= 2) {
+    size_t nw = 0;
+    bool ok = true;
+    for (int s = 0; s < S; ++s)
+      for (int l = 0; l < L; ++l) {
+        nw += (size_t)m->widths[s][l + 1] * (m->widths[s][l] + 1);
+        ok = ok && (l + 1 == L || m->widths[s][l + 1] % 32 == 0);
+      }
+    nw *= m->M;
+    bool finite = true;
+    for (size_t k = 0; k < nw; ++k) finite &= std::fabs(wp[k]) <= 3.3895314e38f;
+    m->split = ok && finite;
+  }
   std::vector<float> tmp;
   std::vector<uint16_t> tb;
   for (int mb = 0; mb < m->M; ++mb)
@@ -379,6 +412,15 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
           round_bf16_host(tmp.data(), tb.data(), nw);
           if ((rc = upload(m, tb.data(), nw * 2, (void **)&lw.Wtb))) return rc;
         }
+        if (m->split && l + 1 < L) {
+          // one allocation per species and layer, the members' parts in turn
+          const int Kp = l == 0 ? m->ldG : lw.n_in;
+          const LayerW *first = mb > 0 ? &m->layer(0, s, l) : nullptr;
+          if (first) lw.Ws = first->Ws + (size_t)mb * lw.n_out * Kp * 3;
+          if (first && l > 0) lw.Wts = first->Wts + (size_t)mb * nw * 3;
+          if ((rc = split_parts(m, lw.W, lw.n_out, lw.n_in, Kp, m->M, &lw.Ws))) return rc;
+          if (l > 0 && (rc = split_parts(m, lw.Wt, lw.n_in, lw.n_out, lw.n_out, m->M, &lw.Wts))) return rc;
+        }
         wp += nw;
         if ((rc = upload(m, wp, (size_t)lw.n_out * 4, (void **)&lw.b))) return rc;
         wp += lw.n_out;
@@ -386,6 +428,7 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
   if (L >= 2) {
     m->Wdg.assign(S, nullptr);
     m->Wdg_b.assign(S, nullptr);
+    m->Wdg_s.assign(S, nullptr);
     const float *base = d->weights;
     // offsets of (member, species) first layers in the flat weight array
     std::vector<size_t> off((size_t)m->M * S);
@@ -410,13 +453,17 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
         round_bf16_host(cat.data(), cb.data(), cat.size());
         if ((rc = upload(m, cb.data(), cb.size() * 2, (void **)&m->Wdg_b[s]))) return rc;
       }
+      if (m->split && (rc = split_parts(m, m->Wdg[s], D, MK, MK, 1, &m->Wdg_s[s]))) return rc;
     }
   }
-  // fused chain: bfloat16, 2..4 hidden layers after the first, widths that are
-  // multiples of 32 and at most 256, activation tiles within 64 KB of LDS
-  if (m->precision == NNP_BF16 && L >= 3 && L - 2 <= kChainMax) {
+  // fused chain: 2..4 hidden layers after the first, widths that are
+  // multiples of 32 and at most 256, the activation tiles of 32 rows within a
+  // workgroup's LDS
+  const bool f32 = m->precision == NNP_FP32;
+  if ((m->split || !f32) && L >= 3 && L - 2 <= kChainMax) {
     bool ok = true;
-    size_t lds = 0;
+    const int planes = f32 ? 3 : 1;
+    size_t elems = 0;
     ChainLaunch &cp = m->chain_proto;
     for (int l = 0; l + 1 < L; ++l) {
       for (int s = 0; s < S; ++s) {
@@ -424,12 +471,13 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
         ok = ok && w % 32 == 0 && w <= 256;
       }
       if (l <= kChainMax) {
-        cp.lds_off[l] = (int)lds;
+        cp.lds_off[l] = (int)elems;
         cp.lds_ld[l] = m->ldH[l] + 8;
-        lds += (size_t)kChainRows * (m->ldH[l] + 8) * 2;
+        elems += (size_t)16 * (m->ldH[l] + 8) * planes;
       }
     }
-    ok = ok && lds <= 64 * 1024;
+    const size_t lds = elems * 2;
+    ok = ok && (f32 ? 2 * lds + 64 <= m->max_lds : 2 * lds <= 64 * 1024);
     if (ok) {
       std::vector<ChainNet> nets((size_t)m->M * S);
       for (int mb = 0; mb < m->M; ++mb)
@@ -438,8 +486,14 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
           memset(&n, 0, sizeof n);
           for (int l = 1; l <= L - 2; ++l) {
             LayerW &lw = m->layer(mb, s, l);
-            n.W[l - 1] = lw.Wb;
-            n.Wt[l - 1] = lw.Wtb;
+            uint16_t *frags = nullptr;  // the layer, then its transpose
+            const size_t nf = (size_t)lw.n_in * lw.n_out * planes;
+            HIP_TRY(hipMalloc((void **)&frags, 2 * nf * 2));
+            m->weight_allocs.push_back(frags);
+            launch_weight_frags(lw.W, lw.Wb, lw.n_out, lw.n_in, frags, nullptr);
+            launch_weight_frags(lw.Wt, lw.Wtb, lw.n_in, lw.n_out, frags + nf, nullptr);
+            n.W[l - 1] = frags;
+            n.Wt[l - 1] = frags + nf;
             n.b[l - 1] = lw.b;
           }
           LayerW &lo = m->layer(mb, s, L - 1);
@@ -452,7 +506,6 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
       HIP_TRY(hipMemcpy(m->chain_nets.p, nets.data(), nets.size() * sizeof(ChainNet), hipMemcpyHostToDevice));
       m->chain = true;
       m->chain_lds = lds;
-      m->chain_rt2 = 2 * lds <= m->max_lds;
     }
   }
   for (StageSlot &ss : m->stage) {
@@ -559,7 +612,7 @@ static int for_each_ws(nnp_model *m, int64_t N, int S, int64_t C, int n_chunks, 
   ENS(m->dG, rows * m->D * 4);
   if (m->kind == kDescDp) ENS(m->dp_rec, N * (int64_t)m->dp.ldm * 16);
   ENS(m->e_atom, N * 4);
-  if (m->chain) ENS(m->e_mem, rows * m->M * 4);
+  if (m->chain && m->precision == NNP_BF16) ENS(m->e_mem, rows * m->M * 4);
   ENS(m->W_atom, N * 36);
   ENS(m->partial, (int64_t)n_chunks * 80 + 80);
   ENS(m->desc, DescLayout(S, n_chunks, (int)max_bwd_groups(N, S)).total);
@@ -1317,7 +1370,8 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
       gl.n_seg = 1;
     };
     // with the fused chain only the first layer runs as a separate GEMM
-    const bool use_chain = m->chain && bf16;
+    const bool use_chain = m->chain;
+    const bool split = m->split;
     for (int l = 0; l + 1 < (use_chain ? 2 : L); ++l) {
       GemmLaunch gl{};
       common(gl);
@@ -1327,22 +1381,21 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
       gl.C = m->H[l].p;
       gl.ldc = M * m->ldH[l];
       gl.c_member_stride = m->ldH[l];
-      if (l == 0) {
-        gl.row_mask = gmask;
-        gl.bucket_cnt = m->bucket_cnt.as<int>();
-      }
+      gl.bucket_cnt = m->bucket_cnt.as<int>();
+      if (l == 0) gl.row_mask = gmask;
       for (int mb = 0; mb < M; ++mb)
         for (int s = 0; s < S; ++s) {
           LayerW &lw = m->layer(mb, s, l);
           GemmGroup &g = gl.g[mb * S + s];
-          g.B = bf16 ? (const void *)lw.Wb : (const void *)lw.W;
+          g.B = bf16 ? (const void *)lw.Wb : split ? (const void *)lw.Ws : (const void *)lw.W;
           g.bias = lw.b;
           g.n_out = lw.n_out;
           g.K = lw.n_in;
-          if (l == 0 && bf16) g.K = g.ldb = m->ldG;  // zero-padded columns on both sides
+          if (l == 0 && (bf16 || split)) g.K = g.ldb = m->ldG;  // zero-padded columns on both sides
         }
       site_begin(kSiteGemmFwd + l);
-      launch_gemm(kEpiFwd, bf16, gl, row_tiles, m->ldH[l], m->tune_val[kSiteGemmFwd + l], st);
+      if (split) launch_gemm_split(kEpiFwd, gl, rows, m->ldH[l], m->tune_val[kSiteGemmFwd + l], st);
+      else launch_gemm(kEpiFwd, bf16, gl, row_tiles, m->ldH[l], m->tune_val[kSiteGemmFwd + l], st);
       site_end(kSiteGemmFwd + l);
     }
     if (use_chain) {
@@ -1359,14 +1412,16 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
       cl.n_members = M;
       cl.alpha = m->alpha;
       cl.inv_m = 1.0f / (float)M;
-      cl.e_mem = m->e_mem.as<float>();
+      // member energies: float32 models keep them in the second hidden
+      // layer's buffer, which only the layer-by-layer form fills
+      cl.e_mem = bf16 ? m->e_mem.as<float>() : m->H[1].as<float>();
+      cl.bucket_cnt = m->bucket_cnt.as<int>();
       cl.perm = m->perm.as<int>();
       cl.e_atom = e_atom;
       site_begin(kSiteChain);
-      // tuned shape: 4 or 8 waves, plus 10 for 64-row workgroups
       const int tv = m->tune_val[kSiteChain];
-      launch_chain(cl, L - 2, want_grad, rows, m->chain_lds, tv % 10 == 4 ? 4 : 8,
-                   tv >= 10 && m->chain_rt2 ? 2 : 1, st);
+      launch_chain(cl, split, L - 2, want_grad, rows, m->chain_lds, tv == 4 ? 16 : tv == 8 ? 32 : tv == 18 ? 64 : 0,
+                   m->max_lds, st);
       site_end(kSiteChain);
     } else {
       EnergyLaunch el{};
@@ -1412,12 +1467,14 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
           for (int s = 0; s < S; ++s) {
             LayerW &lw = m->layer(mb, s, l);
             GemmGroup &g = gl.g[mb * S + s];
-            g.B = bf16 ? (const void *)lw.Wtb : (const void *)lw.Wt;
+            g.B = bf16 ? (const void *)lw.Wtb : split ? (const void *)lw.Wts : (const void *)lw.Wt;
             g.n_out = lw.n_in;
             g.K = lw.n_out;
           }
+        gl.bucket_cnt = m->bucket_cnt.as<int>();
         site_begin(kSiteGemmBwd + l);
-        launch_gemm(kEpiBwd, bf16, gl, row_tiles, m->ldH[l - 1], m->tune_val[kSiteGemmBwd + l], st);
+        if (split) launch_gemm_split(kEpiBwd, gl, rows, m->ldH[l - 1], m->tune_val[kSiteGemmBwd + l], st);
+        else launch_gemm(kEpiBwd, bf16, gl, row_tiles, m->ldH[l - 1], m->tune_val[kSiteGemmBwd + l], st);
         site_end(kSiteGemmBwd + l);
       }
       if (L >= 2) {
@@ -1435,12 +1492,13 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
         gl.bucket_cnt = m->bucket_cnt.as<int>();
         for (int s = 0; s < S; ++s) {
           GemmGroup &g = gl.g[s];
-          g.B = bf16 ? (const void *)m->Wdg_b[s] : (const void *)m->Wdg[s];
+          g.B = bf16 ? (const void *)m->Wdg_b[s] : split ? (const void *)m->Wdg_s[s] : (const void *)m->Wdg[s];
           g.n_out = D;
           g.K = m->widths[s][1];
         }
         site_begin(kSiteGemmOut);
-        launch_gemm(kEpiOut, bf16, gl, row_tiles, D, m->tune_val[kSiteGemmOut], st);
+        if (split) launch_gemm_split(kEpiOut, gl, rows, D, m->tune_val[kSiteGemmOut], st);
+        else launch_gemm(kEpiOut, bf16, gl, row_tiles, D, m->tune_val[kSiteGemmOut], st);
         site_end(kSiteGemmOut);
       }
     }
@@ -1597,12 +1655,12 @@ extern "C" int nnp_autotune(nnp_model *m, int n_systems, const int64_t *offs, co
   // candidates: round r sets every GEMM site to kTn[r], the AEV forward to
   // kWpb[r] waves per workgroup, the AEV backward to kBwd[r] (1: a wave per
   // centre with device atomics; 5, 4, 8: a grouped form with that many
-  // waves) and the fused chain to kChainW[r] waves per workgroup
+  // waves) and the fused chain's shape to kChainW[r]
   constexpr int kRounds = 4, kReps = 5;
   const int kTn[kRounds] = {64, 128, 256, 128}, kWpb[kRounds] = {1, 2, 4, 2};
   const int kBwd[kRounds] = {1, 5, 4, 8};
-  // chain: 8 or 4 waves on 32 rows, 8 waves on 64 rows (+10) when the LDS allows
-  const int kChainW[kRounds] = {8, 4, m->chain_rt2 ? 18 : 8, 8};
+  // chain: 32, 16 or (bfloat16) 64 rows per workgroup
+  const int kChainW[kRounds] = {8, 4, m->precision == NNP_BF16 ? 18 : 8, 8};
   // Every candidate runs once untimed, then the rounds take turns kReps
   // times (so that clock and cache warm-up do not favour a late round), and
   // each candidate keeps its fastest time.

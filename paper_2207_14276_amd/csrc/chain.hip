@@ -3,41 +3,33 @@
 //
 // After the first dense layer (a large GEMM over the AEV), the remaining
 // layers of a network are narrow (<= 256 wide): run as separate GEMMs their
-// activations make several round trips through HBM.  Here one workgroup
-// takes 32 rows of one species bucket for one ensemble member and runs the
-// rest of the network on chip (or 64 rows, RT = 2, when the LDS allows: each
-// weight fragment loaded from L2 then feeds twice as many MFMAs, and weight
-// traffic from L2 is what bounds this kernel):
+// activations make several round trips through HBM.  Here one workgroup of
+// eight waves takes 16 HR rows of one species bucket for one ensemble member
+// and runs the rest of the network on chip:
 //   forward   h_l = CELU(h_{l-1} W_l^T + b_l) for the hidden layers l >= 1,
 //             E = h_last . w_out + b_out, d_last = w_out * CELU'(h_last) / M;
 //   backward  d_{l-1} = (d_l W_l) * CELU'(h_{l-1}) down to d_0,
-// keeping every h_l / d_l tile in LDS (bfloat16, rows padded by 8 elements)
-// and writing only d_0 (the input gradient the AEV-gradient GEMM needs) and
-// the member's energy per row.  The products use v_mfma_f32_16x16x32_bf16:
-// with W waves per workgroup (4 or 8, a tuned launch shape) each wave owns
-// every W-th 16-column block of a layer's output; it reads the A fragments
-// of a K step from LDS once for all its blocks and loads the next step's B
-// fragments (weights, L2-resident) during the current MFMAs.  Activations
-// are rounded to bfloat16 exactly where the unfused path stores them.
+// keeping every h_l / d_l tile in LDS and writing only d_0 (the input gradient
+// the AEV-gradient GEMM needs) and the member's energy per row.  A tile is
+// held in P planes: P = 1, bfloat16 models, the values rounded to bfloat16
+// exactly where the unfused path stores them; P = 3, float32 models, the three
+// bfloat16 parts of the values (split.hip), split once when they are written
+// (held as float32 and split by every wave that reads them, the splitting took
+// as many cycles as the MFMAs).
+//
+// What bounds it is the wait for the weights: a layer is only 3 to 8 K steps
+// long, and L2 answers in about as long as a layer takes.  So the weights lie
+// in fragment order (a wave's load is one contiguous KB, no address work),
+// the first steps' fragments of a layer are already on their way while the
+// layer before it finishes (the barriers between layers wait for LDS only),
+// and the K loop is unrolled for each length, so that every wait counts
+// exactly the loads behind it.
 #include "internal.h"
+#include "split.h"
+#include "wave.h"
 
 namespace nnp {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float floatx4_t __attribute__((ext_vector_type(4)));
-
-// float -> bfloat16, round to nearest even (one hardware conversion)
-__device__ inline uint16_t to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ inline float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-// four floats -> four bfloat16 (round to nearest even) in 8 bytes, first value lowest
-typedef __bf16 bf16x2_c __attribute__((ext_vector_type(2)));
-typedef float floatx2_c __attribute__((ext_vector_type(2)));
-__device__ inline uint2 pack4_bf16(float a, float b, float c, float d) {
-  uint2 r;
-  r.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2_c){a, b}, bf16x2_c));
-  r.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2_c){c, d}, bf16x2_c));
-  return r;
-}
 // CELU with the hardware exp2 (about 1 ulp; the result is rounded to
 // bfloat16 next), k_exp = log2(e) / alpha; CELU' from h = CELU(z) with
 // inv_alpha = 1 / alpha.
@@ -46,84 +38,198 @@ __device__ inline float celu_f(float z, float alpha, float k_exp) {
 }
 __device__ inline float dcelu_h(float h, float inv_alpha) { return h > 0.f ? 1.f : 1.f + h * inv_alpha; }
 
-// Sum over aligned groups of 8 lanes (DPP), result in every lane of the group.
-__device__ inline float sum8_dpp(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false));
-  return v;
+// ------------------------------------------------------------------ weights
+// Element k of a row's 32-column chunk c, part p, of a [N][K] matrix (N a
+// multiple of 16, K of 32) in fragment order: 16-row block, chunk, part, then
+// the MFMA operand's lanes (row % 16, columns 8 (lane / 16) + 0..7).
+template <int P>
+__global__ void __launch_bounds__(256)
+k_weight_frags(const float *__restrict__ src, const uint16_t *__restrict__ src_b, int N, int K,
+               uint16_t *__restrict__ dst) {
+  const int total = N * K;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < total; t += gridDim.x * blockDim.x) {
+    const int r = t / K, k = t - r * K;
+    uint16_t *d = dst + ((size_t)((r / 16) * (K / 32) + k / 32) * P) * 512 + ((k % 32) / 8 * 16 + r % 16) * 8 + k % 8;
+    if (P == 1) {
+      d[0] = src_b[t];
+    } else {
+      const float x = src[t];
+      const __bf16 p1 = (__bf16)x;
+      const float a = x - (float)p1;
+      const __bf16 p2 = (__bf16)a;
+      d[0] = __builtin_bit_cast(uint16_t, p1);
+      d[512] = __builtin_bit_cast(uint16_t, p2);
+      d[1024] = __builtin_bit_cast(uint16_t, (__bf16)(a - (float)p2));
+    }
+  }
 }
 
-// C[32 RT x N] = A[32 RT x K] (LDS, bfloat16, row stride lda) . B^T with
-// B[N][K] (global, bfloat16, row stride ldb); K a multiple of 32 (<= 256), N
-// of 16.  Each product is formed transposed (weights as the MFMA's first
-// operand), so that a lane ends with four consecutive columns of one row:
-// for every 16-column block owned by this wave, epi(cb, acc) gets, in
-// acc[h][j], row 16 h + l % 16 and column 16 cb + 4 (l / 16) + j (j = 0..3)
-// of each of the 2 RT sixteen-row groups h; the epilogues then move four
-// bfloat16 values (8 bytes) per LDS access.
-template <int W, int RT, class Epi>
-__device__ inline void chain_gemm(const uint16_t *A, int lda, int K, const uint16_t *__restrict__ B, int ldb,
-                                  int N, int wave, int lane, Epi &&epi) {
-  constexpr int QM = 16 / W;                      // blocks per wave at N = 256
-  constexpr int HR = 2 * RT;                      // sixteen-row groups
-  const int l16 = lane & 15, kq = lane >> 4;
-  const int nkb = K / 32, ncb = N / 16;
-  // this wave's blocks: wave + W q, q < nq (N <= 256: at most 16 / W).
-  // K-step outer, blocks inner: the A fragments of a K step are read from
-  // LDS once for all of the wave's blocks, and the next step's B fragments
-  // are loaded while the current step's MFMAs run.
-  const int nq = ncb > wave ? (ncb - wave + W - 1) / W : 0;
-  if (nq == 0) return;
-  floatx4_t acc[QM][HR];
+void launch_weight_frags(const float *src, const uint16_t *src_b, int N, int K, uint16_t *dst, hipStream_t st) {
+  const unsigned blocks = (unsigned)((N * K + 255) / 256);
+  if (src_b) k_weight_frags<1><<<blocks, 256, 0, st>>>(nullptr, src_b, N, K, dst);
+  else k_weight_frags<3><<<blocks, 256, 0, st>>>(src, nullptr, N, K, dst);
+}
+
+// -------------------------------------------------------------------- tiles
+struct ChainTile {
+  uint16_t *p;  // first plane
+  int ld;       // row stride, elements (padded by 8: the 16 rows of a fragment read fall on different banks)
+  int plane;    // elements between planes
+};
+
+// Four consecutive elements of a row: 8 bytes in each plane.  P = 3: a value
+// without a finite first part keeps its leading bits there (an infinity
+// nothing else), so that its parts still add up to it, and is reported.
+template <int P>
+__device__ inline void put4(const ChainTile &t, int row, int col, float (&x)[4], bool &huge) {
+  uint16_t *d = t.p + row * t.ld + col;
+  if (P == 3) {
+    const bool b = fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))) > kPartMax;
+    if (__builtin_expect(__ballot(b) != 0, 0)) {
+      huge = huge || b;
 #pragma unroll
-  for (int q = 0; q < QM; ++q)
-#pragma unroll
-    for (int h = 0; h < HR; ++h) acc[q][h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  const uint16_t *bp = B + (size_t)(wave * 16 + l16) * ldb + 8 * kq;
-  const size_t bstep = (size_t)16 * W * ldb;      // W blocks of 16 rows
-  // B fragments of K steps kb (bc), kb + 1 (bn) and kb + 2 (bnn): the loads
-  // (L2 hits) are issued two steps ahead of their MFMAs
-  uint4 bc[QM], bn[QM], bnn[QM];
-#pragma unroll
-  for (int q = 0; q < QM; ++q)
-    if (q < nq) {
-      bc[q] = *(const uint4 *)(bp + q * bstep);
-      if (nkb > 1) bn[q] = *(const uint4 *)(bp + q * bstep + 32);
-    }
-  for (int kb = 0; kb < nkb; ++kb) {
-    if (kb + 2 < nkb) {
-#pragma unroll
-      for (int q = 0; q < QM; ++q)
-        if (q < nq) bnn[q] = *(const uint4 *)(bp + q * bstep + (kb + 2) * 32);
-    }
-    bf16x8_t a[HR];
-#pragma unroll
-    for (int h = 0; h < HR; ++h)
-      a[h] = __builtin_bit_cast(bf16x8_t, *(const uint4 *)(A + (16 * h + l16) * lda + kb * 32 + 8 * kq));
-#pragma unroll
-    for (int q = 0; q < QM; ++q) {
-      if (q < nq) {
-        const bf16x8_t b = __builtin_bit_cast(bf16x8_t, bc[q]);
-#pragma unroll
-        for (int h = 0; h < HR; ++h) acc[q][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[h], acc[q][h], 0, 0, 0);
+      for (int k = 0; k < 4; ++k) {
+        const float v = x[k];
+        const bool big = fabsf(v) > kPartMax, inf = fabsf(v) > 3.4028235e38f;
+        const uint32_t u1 = big ? __float_as_uint(v) >> 16 : round2(v, 0.f) & 0xffffu;
+        const float r = inf ? 0.f : v - __uint_as_float(u1 << 16);
+        const uint32_t u2 = round2(r, 0.f) & 0xffffu;
+        d[k] = (uint16_t)u1;
+        d[k + t.plane] = (uint16_t)u2;
+        d[k + 2 * t.plane] = (uint16_t)round2(r - __uint_as_float(u2 << 16), 0.f);
       }
-    }
-#pragma unroll
-    for (int q = 0; q < QM; ++q) {
-      bc[q] = bn[q];
-      bn[q] = bnn[q];
+      return;
     }
   }
 #pragma unroll
-  for (int q = 0; q < QM; ++q)
-    if (q < nq) epi(wave + W * q, acc[q]);
+  for (int p = 0; p < P; ++p) {
+    uint2 w;
+    w.x = round2(x[0], x[1]);
+    w.y = round2(x[2], x[3]);
+    *(uint2 *)(d + p * t.plane) = w;
+    if (p + 1 < P) {
+      x[0] -= __uint_as_float(w.x << 16);
+      x[1] -= __uint_as_float(w.x & 0xffff0000u);
+      x[2] -= __uint_as_float(w.y << 16);
+      x[3] -= __uint_as_float(w.y & 0xffff0000u);
+    }
+  }
+}
+template <int P>
+__device__ inline void get4(const ChainTile &t, int row, int col, float (&x)[4]) {
+  const uint16_t *d = t.p + row * t.ld + col;
+  uint2 w[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) w[p] = *(const uint2 *)(d + p * t.plane);
+  x[0] = __uint_as_float(w[P - 1].x << 16);
+  x[1] = __uint_as_float(w[P - 1].x & 0xffff0000u);
+  x[2] = __uint_as_float(w[P - 1].y << 16);
+  x[3] = __uint_as_float(w[P - 1].y & 0xffff0000u);
+#pragma unroll
+  for (int p = P - 2; p >= 0; --p) {
+    x[0] += __uint_as_float(w[p].x << 16);
+    x[1] += __uint_as_float(w[p].x & 0xffff0000u);
+    x[2] += __uint_as_float(w[p].y << 16);
+    x[3] += __uint_as_float(w[p].y & 0xffff0000u);
+  }
 }
 
-template <int NL, bool GRAD, int W, int RT>
-__global__ void __launch_bounds__(W * kWave) k_chain(ChainLaunch cl) {
-  constexpr int R = kChainRows * RT;   // rows of this workgroup
-  constexpr int HR = 2 * RT;
+// ----------------------------------------------------------------- products
+// C[16 HR x N] = A[16 HR x K] (LDS) . W^T.  Each product is formed transposed
+// (weights as the MFMA's first operand), so that a lane ends with four
+// consecutive columns of one row: block cb's accumulators hold, of each
+// sixteen-row group h, row 16 h + l % 16 and columns 16 cb + 4 (l / 16) + j,
+// j = 0..3.  Wave w owns the 16-column blocks w and w + 8 (N <= 256).
+constexpr int kChainWaves = 8, kChainBlocks = 2;
+constexpr int kChainFirst = 2;  // K steps of the next layer loaded ahead
+// K steps loaded ahead within a layer: what the registers hold
+template <int P, int HR> constexpr int kChainAhead = P == 3 ? (HR == 1 ? 5 : 3) : (HR == 4 ? 2 : 4);
+
+// The loads above stay above (the scheduler would move them down to their
+// uses, and the waits with them).
+__device__ inline void pin_loads() { __builtin_amdgcn_sched_barrier(0); }
+
+template <int P, int HR> struct ChainAcc {
+  floatx4 v[kChainBlocks][HR];
+  floatx4 low[kChainBlocks][P == 3 ? HR : 1];  // P = 3: the small products
+};
+template <int P> struct ChainFirst {
+  uint4 b[kChainFirst][kChainBlocks][P];
+};
+
+// One K step: a block's fragments against the row groups'.
+template <int P, int NQ, int HR>
+__device__ inline void chain_step(const uint16_t *ap, const ChainTile &A, int kb, const uint4 (&w)[NQ][P],
+                                  ChainAcc<P, HR> &acc) {
+  bf16x8 a[HR][P];
+#pragma unroll
+  for (int h = 0; h < HR; ++h)
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      a[h][p] = __builtin_bit_cast(bf16x8, *(const uint4 *)(ap + p * A.plane + 16 * h * A.ld + kb * 32));
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const bf16x8 w1 = __builtin_bit_cast(bf16x8, w[q][0]);
+    if constexpr (P == 1) {
+#pragma unroll
+      for (int h = 0; h < HR; ++h) acc.v[q][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, a[h][0], acc.v[q][h], 0, 0, 0);
+    } else {
+      const bf16x8 w2 = __builtin_bit_cast(bf16x8, w[q][1]), w3 = __builtin_bit_cast(bf16x8, w[q][2]);
+#pragma unroll
+      for (int h = 0; h < HR; ++h) acc.low[q][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, a[h][2], acc.low[q][h], 0, 0, 0);
+#pragma unroll
+      for (int h = 0; h < HR; ++h) acc.low[q][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3, a[h][0], acc.low[q][h], 0, 0, 0);
+#pragma unroll
+      for (int h = 0; h < HR; ++h) acc.low[q][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2, a[h][1], acc.low[q][h], 0, 0, 0);
+#pragma unroll
+      for (int h = 0; h < HR; ++h) acc.low[q][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, a[h][1], acc.low[q][h], 0, 0, 0);
+#pragma unroll
+      for (int h = 0; h < HR; ++h) acc.low[q][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2, a[h][0], acc.low[q][h], 0, 0, 0);
+#pragma unroll
+      for (int h = 0; h < HR; ++h) acc.v[q][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, a[h][0], acc.v[q][h], 0, 0, 0);
+    }
+  }
+}
+
+// All K steps of a layer for NQ blocks of the wave; wp: the wave's first
+// fragments, `first` the ones already loaded.
+template <int P, int NKB, int NQ, int HR>
+__device__ inline void chain_mm(const uint16_t *ap, const ChainTile &A, Global<uint16_t> wp,
+                                const ChainFirst<P> &first, ChainAcc<P, HR> &acc) {
+  constexpr int AH = kChainAhead<P, HR>;
+  uint4 w[NKB][NQ][P];
+  auto load = [&](int k) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int p = 0; p < P; ++p) w[k][q][p] = load16(wp + (q * kChainWaves * NKB + k) * (P * 512) + p * 512);
+  };
+#pragma unroll
+  for (int k = 0; k < NKB; ++k) {
+    if (k < kChainFirst) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int p = 0; p < P; ++p) w[k][q][p] = first.b[k][q][p];
+    } else if (k < AH) {
+      load(k);
+    }
+  }
+  pin_loads();
+#pragma unroll
+  for (int k = 0; k < NKB; ++k) {
+    if (k + AH < NKB) {
+      load(k + AH);
+      pin_loads();
+    }
+    chain_step<P, NQ, HR>(ap, A, k, w[k], acc);
+  }
+}
+
+template <int P, int HR>
+__global__ void __launch_bounds__(kChainWaves * kWave, P == 3 ? 2 : 4)
+k_chain(ChainLaunch cl, int n_hidden, int grad) {
+  constexpr int R = 16 * HR, T = kChainWaves * kWave;
   const float inv_alpha = 1.f / cl.alpha, k_exp = 1.4426950408889634f * inv_alpha;
   extern __shared__ uint4 chain_lds[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
@@ -135,132 +241,238 @@ __global__ void __launch_bounds__(W * kWave) k_chain(ChainLaunch cl) {
   if (lb >= cl.n_blocks) return;
   const int n_rt = cl.n_blocks / cl.n_members;
   const int mb = lb / n_rt;
-  const int r0 = (lb % n_rt) * R;
-  int s = -1;
+  const int r0 = (lb - mb * n_rt) * R;
+  int s = -1, real_end = 0;
   for (int q = 0; q < cl.n_groups; ++q)
-    if (r0 >= cl.bucket_off[q] && r0 < cl.bucket_off[q + 1]) s = q;
-  if (s < 0) return;
+    if (r0 >= cl.bucket_off[q] && r0 < cl.bucket_off[q + 1]) {
+      s = q;
+      real_end = cl.bucket_off[q] + cl.bucket_cnt[q];
+    }
+  if (s < 0 || r0 >= real_end) return;  // padding rows only: their gradients are not read
   const ChainNet &net = cl.nets[mb * cl.n_groups + s];
-  uint16_t *act[NL + 1];
+  auto tile = [&](int l) {  // offsets are of 16 rows
+    return ChainTile{(uint16_t *)chain_lds + cl.lds_off[l] * HR, cl.lds_ld[l], R * cl.lds_ld[l]};
+  };
+  // Layers 1 .. n_hidden forward, then n_hidden .. 1 backward: layer `ph` of
+  // 2 n_hidden (weights, K steps, column blocks).
+  struct Layer {
+    const uint16_t *w;
+    int nkb, ncb;
+  };
+  auto layer = [&](int ph) {
+    const int l = ph <= n_hidden ? ph : 2 * n_hidden + 1 - ph;
+    if (ph <= n_hidden) return Layer{net.W[l - 1], net.width[l - 1] / 32, net.width[l] / 16};
+    return Layer{net.Wt[l - 1], net.width[l] / 32, net.width[l - 1] / 16};
+  };
+  // the wave's block q of a layer; a block past the end repeats the last one
+  auto frags = [&](const Layer &y, int q) {
+    return as_global(y.w) + (size_t)min(wave + q * kChainWaves, y.ncb - 1) * y.nkb * (P * 512) + lane * 8;
+  };
+  ChainFirst<P> first;
+  auto load_first = [&](const Layer &y) {
 #pragma unroll
-  for (int l = 0; l <= NL; ++l) act[l] = (uint16_t *)((char *)chain_lds + (size_t)cl.lds_off[l] * RT);
+    for (int k = 0; k < kChainFirst; ++k)
+#pragma unroll
+      for (int q = 0; q < kChainBlocks; ++q)
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+          first.b[k][q][p] = load16(frags(y, q) + min(k, y.nkb - 1) * (P * 512) + p * 512);
+    pin_loads();
+  };
+  // every wave's LDS writes are done; loads of weights in flight stay in flight
+  auto lds_barrier = [&]() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // P = 3: whether a tile (h_l, then d_l) holds a value without a finite first part
+  __shared__ int huge_tile[2][kChainMax + 1];
+  if (P == 3) {
+    if (tid < 2 * (kChainMax + 1)) (&huge_tile[0][0])[tid] = 0;
+    lds_barrier();
+  }
+  auto report = [&](int d, int l, bool huge) {
+    if (P == 3 && __builtin_expect(__ballot(huge) != 0, 0)) huge_tile[d][l] = 1;
+  };
 
+  Layer cur = layer(1);
+  load_first(cur);
   // h_0 tile (this member's slice of the first layer's output) into LDS
   {
-    const int w0 = net.width[0], cpr = w0 / 8;
-    const uint16_t *src = cl.H0 + (size_t)r0 * cl.ldh + (size_t)mb * cl.h_member_stride;
-    for (int idx = tid; idx < R * cpr; idx += blockDim.x) {
-      const int row = idx / cpr, ch = idx % cpr;
-      *(uint4 *)(act[0] + row * cl.lds_ld[0] + ch * 8) = *(const uint4 *)(src + (size_t)row * cl.ldh + ch * 8);
-    }
-  }
-  __syncthreads();
-
-#pragma unroll
-  for (int l = 1; l <= NL; ++l) {
-    const int K = net.width[l - 1], N = net.width[l];
-    const float *bias = net.b[l - 1];
-    uint16_t *out = act[l];
-    const int ldo = cl.lds_ld[l];
-    if (l < NL) {
-      chain_gemm<W, RT>(act[l - 1], cl.lds_ld[l - 1], K, net.W[l - 1], K, N, wave, lane,
-                 [&](int cb, const floatx4_t *acc) {
-                   const int col = cb * 16 + 4 * kq;
-                   const float4 bc = *(const float4 *)(bias + col);
-#pragma unroll
-                   for (int h = 0; h < HR; ++h)
-                     *(uint2 *)(out + (16 * h + l16) * ldo + col) =
-                         pack4_bf16(celu_f(acc[h][0] + bc.x, cl.alpha, k_exp), celu_f(acc[h][1] + bc.y, cl.alpha, k_exp),
-                                    celu_f(acc[h][2] + bc.z, cl.alpha, k_exp), celu_f(acc[h][3] + bc.w, cl.alpha, k_exp));
-                 });
+    const ChainTile t0 = tile(0);
+    const int w0 = net.width[0];
+    bool huge = false;
+    if (P == 1) {
+      const uint16_t *src = cl.H0 + (size_t)r0 * cl.ldh + (size_t)mb * cl.h_member_stride;
+      const int ch = 8 * (tid & 31);
+      if (ch < w0)
+        for (int row = tid >> 5; row < R; row += T / 32)
+          *(uint4 *)(t0.p + row * t0.ld + ch) = *(const uint4 *)(src + (size_t)row * cl.ldh + ch);
     } else {
-      // last hidden layer: h_last (bfloat16) into its tile
-      chain_gemm<W, RT>(act[l - 1], cl.lds_ld[l - 1], K, net.W[l - 1], K, N, wave, lane,
-                 [&](int cb, const floatx4_t *acc) {
-                   const int col = cb * 16 + 4 * kq;
-                   const float4 bc = *(const float4 *)(bias + col);
+      const float *src = (const float *)cl.H0 + (size_t)r0 * cl.ldh + (size_t)mb * cl.h_member_stride;
+      const int ch = 4 * (tid & 63);
+      if (ch < w0) {
 #pragma unroll
-                   for (int h = 0; h < HR; ++h)
-                     *(uint2 *)(out + (16 * h + l16) * ldo + col) =
-                         pack4_bf16(celu_f(acc[h][0] + bc.x, cl.alpha, k_exp), celu_f(acc[h][1] + bc.y, cl.alpha, k_exp),
-                                    celu_f(acc[h][2] + bc.z, cl.alpha, k_exp), celu_f(acc[h][3] + bc.w, cl.alpha, k_exp));
-                 });
-    }
-    __syncthreads();
-  }
-
-  // the member's energy of each row, E = h_last . w_out + b_out, and (for
-  // forces) d_last = w_out CELU'(h_last) / M in place of h_last.  Eight
-  // threads per row, each over the 8-column chunks seg, seg + 8, ..., then
-  // summed over the eight: a fixed order, whatever the workgroup's shape.
-  {
-    const int N = net.width[NL], nch = N / 8, ldo = cl.lds_ld[NL];
-    uint16_t *hl = act[NL];
-    // R * 8 is a multiple of the workgroup size: every group of eight lanes
-    // takes the loop's iterations together
-    for (int t8 = tid; t8 < R * 8; t8 += W * kWave) {
-      const int row = t8 >> 3, seg = t8 & 7;
-      float e = 0.f;
-      for (int ch = seg; ch < nch; ch += 8) {
-        uint4 u = *(const uint4 *)(hl + row * ldo + ch * 8);
-        const float4 w0 = *(const float4 *)(net.w_out + ch * 8);
-        const float4 w1 = *(const float4 *)(net.w_out + ch * 8 + 4);
-        const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-        uint16_t hv[8];
-        *(uint4 *)hv = u;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const float h = from_bf16(hv[k]);
-          e += h * wv[k];
-          hv[k] = to_bf16(wv[k] * dcelu_h(h, inv_alpha) * cl.inv_m);
-        }
-        if (GRAD) *(uint4 *)(hl + row * ldo + ch * 8) = *(const uint4 *)hv;
-      }
-      e = sum8_dpp(e);
-      if (seg == 0) {
-        if (cl.n_members == 1) {
-          // a single network: the row's energy is the atomic energy
-          const int atom = cl.perm[r0 + row];
-          if (atom >= 0) cl.e_atom[atom] = e + net.b_out;
-        } else {
-          cl.e_mem[(size_t)(r0 + row) * cl.n_members + mb] = e + net.b_out;
+        for (int row = tid >> 6; row < R; row += T / 64) {
+          // (padding rows hold whatever an earlier call left there)
+          const float4 v = r0 + row < real_end ? *(const float4 *)(src + (size_t)row * cl.ldh + ch)
+                                               : make_float4(0.f, 0.f, 0.f, 0.f);
+          float x[4] = {v.x, v.y, v.z, v.w};
+          put4<P>(t0, row, ch, x, huge);
         }
       }
     }
-    __syncthreads();
+    report(0, 0, huge);
   }
-  if (!GRAD) return;
+  lds_barrier();
 
-  // backward: d_{l-1} = (d_l W_l) * CELU'(h_{l-1}), in place over h_{l-1}
+  float *d0 = (float *)cl.D0 + (size_t)r0 * cl.ldd + (size_t)mb * cl.d_member_stride;  // P = 3
+  const int n_ph = grad ? 2 * n_hidden : n_hidden;
+  for (int ph = 1; ph <= n_ph; ++ph) {
+    const bool fwd = ph <= n_hidden;
+    const int l_in = fwd ? ph - 1 : 2 * n_hidden + 1 - ph;  // input tile
+    const int l_out = fwd ? ph : l_in - 1;                  // output tile
+    const ChainTile A = tile(l_in), out = tile(l_out);
+    const uint16_t *ap = A.p + l16 * A.ld + 8 * kq;
+    const int nq = cur.ncb > wave + kChainWaves ? 2 : cur.ncb > wave ? 1 : 0;
+    float4 bias[kChainBlocks];
+    if (fwd) {
 #pragma unroll
-  for (int l = NL; l >= 1; --l) {
-    const int K = net.width[l], N = net.width[l - 1];
-    uint16_t *hd = act[l - 1];
-    const int ldo = cl.lds_ld[l - 1];
-    chain_gemm<W, RT>(act[l], cl.lds_ld[l], K, net.Wt[l - 1], K, N, wave, lane,
-               [&](int cb, const floatx4_t *acc) {
-                 const int col = cb * 16 + 4 * kq;
+      for (int q = 0; q < kChainBlocks; ++q)
+        bias[q] = load4f(as_global(net.b[l_out - 1]) + 16 * min(wave + q * kChainWaves, cur.ncb - 1) + 4 * kq);
+    }
+    ChainAcc<P, HR> acc;
 #pragma unroll
-                 for (int h = 0; h < HR; ++h) {
-                   uint2 *p = (uint2 *)(hd + (16 * h + l16) * ldo + col);
-                   const uint2 hv = *p;
-                   *p = pack4_bf16(acc[h][0] * dcelu_h(__uint_as_float(hv.x << 16), inv_alpha),
-                                   acc[h][1] * dcelu_h(__uint_as_float(hv.x & 0xffff0000u), inv_alpha),
-                                   acc[h][2] * dcelu_h(__uint_as_float(hv.y << 16), inv_alpha),
-                                   acc[h][3] * dcelu_h(__uint_as_float(hv.y & 0xffff0000u), inv_alpha));
-                 }
-               });
-    __syncthreads();
+    for (int q = 0; q < kChainBlocks; ++q) {
+#pragma unroll
+      for (int h = 0; h < HR; ++h) {
+        acc.v[q][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (P == 3) acc.low[q][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+    const bool plain = P == 1 || __builtin_amdgcn_readfirstlane(huge_tile[fwd ? 0 : 1][l_in]) == 0;
+    if (plain) {
+      const Global<uint16_t> wp = frags(cur, 0);
+#define NNP_CHAIN_K(NKB)                                                                       \
+  case NKB:                                                                                    \
+    if (nq == 2) chain_mm<P, NKB, 2, HR>(ap, A, wp, first, acc);                               \
+    else if (nq == 1) chain_mm<P, NKB, 1, HR>(ap, A, wp, first, acc);                          \
+    break;
+      switch (cur.nkb) {
+        NNP_CHAIN_K(1)
+        NNP_CHAIN_K(2)
+        NNP_CHAIN_K(3)
+        NNP_CHAIN_K(4)
+        NNP_CHAIN_K(5)
+        NNP_CHAIN_K(6)
+        NNP_CHAIN_K(7)
+        default: NNP_CHAIN_K(8)
+      }
+#undef NNP_CHAIN_K
+    } else if constexpr (P == 3) {
+#pragma unroll 1
+      for (int t = 0; t < 8 * cur.nkb; ++t) {  // element t % 8 of K step t / 8
+#pragma unroll
+        for (int q = 0; q < kChainBlocks; ++q) {
+          const float w = joined(frags(cur, q) + (t >> 3) * (P * 512) + (t & 7), 512);
+#pragma unroll
+          for (int h = 0; h < HR; ++h)
+            acc.v[q][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                w, joined(ap + 16 * h * A.ld + (t >> 3) * 32 + (t & 7), A.plane), acc.v[q][h], 0, 0, 0);
+        }
+      }
+    }
+    // the next layer's first weights, before this one's epilogue and barrier
+    cur = layer(ph < n_ph ? ph + 1 : ph);
+    load_first(cur);
+
+    bool huge = false;
+#pragma unroll
+    for (int q = 0; q < kChainBlocks; ++q) {
+      if (q < nq) {
+        const int col = 16 * (wave + q * kChainWaves) + 4 * kq;
+#pragma unroll
+        for (int h = 0; h < HR; ++h) {
+          floatx4 v = acc.v[q][h];
+          if (P == 3) v += acc.low[q][h];
+          const int row = 16 * h + l16;
+          float x[4];
+          if (fwd) {
+            const float z[4] = {v[0] + bias[q].x, v[1] + bias[q].y, v[2] + bias[q].z, v[3] + bias[q].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              x[j] = P == 1 ? celu_f(z[j], cl.alpha, k_exp) : celu32(z[j], cl.alpha, inv_alpha);
+          } else {
+            get4<P>(out, row, col, x);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = v[j] * dcelu_h(x[j], inv_alpha);
+          }
+          if (P == 3 && ph == 2 * n_hidden)  // d_0 straight to memory
+            *(float4 *)(d0 + (size_t)row * cl.ldd + col) = make_float4(x[0], x[1], x[2], x[3]);
+          else
+            put4<P>(out, row, col, x, huge);
+        }
+      }
+    }
+    report(fwd ? 0 : 1, l_out, huge);
+    if (P == 3 && ph == 2 * n_hidden) return;
+    lds_barrier();
+
+    // the member's energy of each row, E = h_last . w_out + b_out, and (for
+    // forces) d_last = w_out CELU'(h_last) / M in place of h_last.  Eight
+    // threads per row, each over the 8-column chunks seg, seg + 8, ..., then
+    // summed over the eight: a fixed order, whatever the workgroup's shape.
+    if (ph == n_hidden) {
+      const int nch = net.width[n_hidden] / 8;
+      const ChainTile hl = out;
+      bool hg = false;
+      // R * 8 is a multiple of 64: every group of eight lanes takes the loop's
+      // iterations together
+      for (int t8 = tid; t8 < R * 8; t8 += T) {
+        const int row = t8 >> 3, seg = t8 & 7;
+        float e = 0.f;
+        for (int ch = seg; ch < nch; ch += 8) {
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+            const int col = ch * 8 + 4 * half;
+            float h[4];
+            get4<P>(hl, row, col, h);
+            const float4 w4 = load4f(as_global(net.w_out) + col);
+            const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              e += h[k] * w[k];
+              h[k] = w[k] * dcelu_h(h[k], inv_alpha) * cl.inv_m;
+            }
+            if (grad) put4<P>(hl, row, col, h, hg);
+          }
+        }
+        e = sum8(e);
+        if (seg == 0) {
+          if (cl.n_members == 1) {
+            // a single network: the row's energy is the atomic energy
+            const int atom = cl.perm[r0 + row];
+            if (atom >= 0) cl.e_atom[atom] = e + net.b_out;
+          } else {
+            cl.e_mem[(size_t)(r0 + row) * cl.n_members + mb] = e + net.b_out;
+          }
+        }
+      }
+      report(1, n_hidden, hg);
+      lds_barrier();
+    }
   }
+  if (!grad) return;
 
-  // d_0 tile to global (16-byte stores)
-  {
-    const int w0 = net.width[0], cpr = w0 / 8;
+  // d_0 tile to memory (bfloat16, 16-byte stores)
+  if (P == 1) {
+    const ChainTile t0 = tile(0);
+    const int w0 = net.width[0];
     uint16_t *dst = cl.D0 + (size_t)r0 * cl.ldd + (size_t)mb * cl.d_member_stride;
-    for (int idx = tid; idx < R * cpr; idx += blockDim.x) {
-      const int row = idx / cpr, ch = idx % cpr;
-      *(uint4 *)(dst + (size_t)row * cl.ldd + ch * 8) = *(const uint4 *)(act[0] + row * cl.lds_ld[0] + ch * 8);
-    }
+    const int ch = 8 * (tid & 31);
+    if (ch < w0)
+      for (int row = tid >> 5; row < R; row += T / 32)
+        *(uint4 *)(dst + (size_t)row * cl.ldd + ch) = *(const uint4 *)(t0.p + row * t0.ld + ch);
   }
 }
 
@@ -278,37 +490,36 @@ __global__ void k_chain_mean(const float *__restrict__ e_mem, int M, const int *
   e_atom[atom] = e * inv_m;
 }
 
-template <int W, int RT>
-static void chain_t(const ChainLaunch &cl, int n_hidden, bool grad, unsigned blocks, size_t lds_bytes,
-                    hipStream_t st) {
-  blocks = xcd_grid(blocks, cl.xcd_chunk);
-  if (n_hidden == 1) {
-    if (grad) k_chain<1, true, W, RT><<<blocks, W * kWave, lds_bytes, st>>>(cl);
-    else k_chain<1, false, W, RT><<<blocks, W * kWave, lds_bytes, st>>>(cl);
-  } else if (n_hidden == 2) {
-    if (grad) k_chain<2, true, W, RT><<<blocks, W * kWave, lds_bytes, st>>>(cl);
-    else k_chain<2, false, W, RT><<<blocks, W * kWave, lds_bytes, st>>>(cl);
-  } else {
-    if (grad) k_chain<3, true, W, RT><<<blocks, W * kWave, lds_bytes, st>>>(cl);
-    else k_chain<3, false, W, RT><<<blocks, W * kWave, lds_bytes, st>>>(cl);
-  }
+void launch_chain_mean(const ChainLaunch &cl, int rows, hipStream_t st) {
+  k_chain_mean<<<(rows + 255) / 256, 256, 0, st>>>(cl.e_mem, cl.n_members, cl.perm, cl.bucket_off, cl.n_groups,
+                                                    rows, cl.inv_m, cl.e_atom);
 }
 
-// lds_bytes: the activation tiles of 32 rows; rt = 2 takes 64 rows per
-// workgroup (twice the LDS), rt = 1 32.  rows is a multiple of 128.
-void launch_chain(ChainLaunch cl, int n_hidden, bool grad, int rows, size_t lds_bytes, int waves, int rt,
-                  hipStream_t st) {
-  const int R = kChainRows * (rt == 2 ? 2 : 1);
-  const unsigned blocks = (unsigned)(rows / R * cl.n_members);
-  if (blocks == 0) return;
-  cl.n_blocks = (int)blocks;
-  cl.xcd_chunk = 512 / R;   // 512 rows of one network per chunk
-  if (rt == 2) {
-    if (waves == 4) chain_t<4, 2>(cl, n_hidden, grad, blocks, 2 * lds_bytes, st);
-    else chain_t<8, 2>(cl, n_hidden, grad, blocks, 2 * lds_bytes, st);
+template <int P, int HR>
+static void chain_t(ChainLaunch cl, int n_hidden, bool grad, int rows, size_t lds16, hipStream_t st) {
+  cl.n_blocks = rows / (16 * HR) * cl.n_members;
+  cl.xcd_chunk = 512 / (16 * HR);   // 512 rows of one network per chunk
+  k_chain<P, HR><<<xcd_grid((unsigned)cl.n_blocks, cl.xcd_chunk), kChainWaves * kWave, lds16 * HR, st>>>(cl, n_hidden,
+                                                                                                      grad ? 1 : 0);
+}
+
+// lds16: LDS bytes of the activation tiles of 16 rows.  rows_pref: rows per
+// workgroup (16, 32 or 64), 0: by the grid.  More rows amortize the weights'
+// trip from L2; fewer fill the compute units sooner.  rows is a multiple of
+// 128.
+void launch_chain(const ChainLaunch &cl, bool f32, int n_hidden, bool grad, int rows, size_t lds16, int rows_pref,
+                  size_t max_lds, hipStream_t st) {
+  if (rows <= 0) return;
+  const long long all = (long long)rows * cl.n_members;
+  int r = rows_pref ? rows_pref : all >= 64 * 512 && !f32 ? 64 : all >= 32 * 256 ? 32 : 16;
+  while (r > 16 && lds16 * (r / 16) + 64 > max_lds) r /= 2;
+  if (f32) {
+    if (r >= 32) chain_t<3, 2>(cl, n_hidden, grad, rows, lds16, st);
+    else chain_t<3, 1>(cl, n_hidden, grad, rows, lds16, st);
   } else {
-    if (waves == 4) chain_t<4, 1>(cl, n_hidden, grad, blocks, lds_bytes, st);
-    else chain_t<8, 1>(cl, n_hidden, grad, blocks, lds_bytes, st);
+    if (r >= 64) chain_t<1, 4>(cl, n_hidden, grad, rows, lds16, st);
+    else if (r >= 32) chain_t<1, 2>(cl, n_hidden, grad, rows, lds16, st);
+    else chain_t<1, 1>(cl, n_hidden, grad, rows, lds16, st);
   }
   if (cl.n_members > 1)
     k_chain_mean<<<(rows + 255) / 256, 256, 0, st>>>(cl.e_mem, cl.n_members, cl.perm, cl.bucket_off, cl.n_groups,

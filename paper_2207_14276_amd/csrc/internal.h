@@ -206,13 +206,14 @@ struct GemmLaunch {
 
 enum { kEpiFwd = 0, kEpiBwd = 1, kEpiOut = 2 };
 
-// Fused hidden-layer chain (bfloat16 models): layers 1 .. L-2 and the output
-// layer of one (member, species) network, forward and input gradient.
-constexpr int kChainRows = 32;   // rows per workgroup
+// Fused hidden-layer chain: layers 1 .. L-2 and the output layer of one
+// (member, species) network, forward and input gradient.  float32 models:
+// weights as their three bfloat16 parts, float32 H0 and D0 behind the same
+// pointers.
 constexpr int kChainMax = 3;     // hidden layers after the first, at most
 struct ChainNet {
-  const uint16_t *W[kChainMax];   // layer l: bfloat16 [width[l]][width[l-1]]
-  const uint16_t *Wt[kChainMax];  // its transpose [width[l-1]][width[l]]
+  const uint16_t *W[kChainMax];   // layer l [width[l]][width[l-1]], in fragment order (launch_weight_frags)
+  const uint16_t *Wt[kChainMax];  // its transpose
   const float *b[kChainMax];      // [width[l]]
   const float *w_out;             // output layer weights [width[NL]]
   float b_out;                    // output layer bias
@@ -223,7 +224,8 @@ struct ChainLaunch {
   uint16_t *D0; int ldd; int d_member_stride;        // d_0 = dE/dz_0 out
   const ChainNet *nets;                               // device [member][species]
   const int *bucket_off; int n_groups; int n_members;
-  int lds_off[kChainMax + 1];                         // byte offset of the h_l tile
+  const int *bucket_cnt;                              // [n_groups] real rows per bucket
+  int lds_off[kChainMax + 1];                         // offset of the h_l tile for 16 rows (elements, all planes)
   int lds_ld[kChainMax + 1];                          // its row stride (elements)
   float alpha, inv_m;
   float *e_mem;                                       // [rows][members] energies
@@ -323,10 +325,21 @@ void launch_aev_bwd(const float4 *pos, const int *sys_of, const SysDesc *sys, co
 // tn_pref: column-tile width 64, 128 or 256 (anything else: the width heuristic).
 void launch_gemm(int epi, bool bf16, GemmLaunch gl, int row_tiles, int max_n_out, int tn_pref, hipStream_t st);
 void launch_energy(const EnergyLaunch &el, bool bf16, int rows, hipStream_t st);
-// waves per workgroup 4 or 8; rt = 2: 64 rows per workgroup (2 lds_bytes of
-// LDS), else 32
-void launch_chain(ChainLaunch cl, int n_hidden, bool grad, int rows, size_t lds_bytes, int waves, int rt,
-                  hipStream_t st);
+// A layer's weights [N][K] (float32, or bfloat16 when src_b is given) in the
+// chain's fragment order: 3 parts of N K elements, or N K.
+void launch_weight_frags(const float *src, const uint16_t *src_b, int N, int K, uint16_t *dst, hipStream_t st);
+// f32: float32 model; lds16: LDS bytes of 16 rows; rows_pref: rows per
+// workgroup 16, 32 or 64 (0: by the grid).
+void launch_chain(const ChainLaunch &cl, bool f32, int n_hidden, bool grad, int rows, size_t lds16, int rows_pref,
+                  size_t max_lds, hipStream_t st);
+// float32 models on the bfloat16 matrix cores (split.hip).  Weights: src
+// [rows][K] float32 (row stride ld) to parts [rows][Kp / 32][3][32], Kp a
+// multiple of 32 >= K, zeros past K.
+void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, uint16_t *dst, hipStream_t st);
+// As launch_gemm with float32 activations and parts as B (row_mask nullable,
+// bucket_cnt required); every K a multiple of 32; where the members share A,
+// n_out too, and member m's parts follow member m - 1's in memory.
+void launch_gemm_split(int epi, GemmLaunch gl, int rows, int max_n_out, int tn_pref, hipStream_t st);
 // src: host memory the device reads directly (coherent pinned); bytes are
 // rounded up to 16 on both sides
 void launch_copy_from_host(const void *src, void *dst, size_t bytes, hipStream_t st);

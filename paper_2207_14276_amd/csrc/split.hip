@@ -1,0 +1,334 @@
+// Dense layers of the float32 model on the bfloat16 matrix cores.
+//
+// A float32 operand x is taken as three bfloat16 parts, x = p1 + p2 + p3 (each
+// part the rounding of what the earlier ones leave; 3 x 8 significant bits, so
+// the remainder is below 2^-26 |x|), and a product x w as the six part
+// products down to 2^-18: p1 w1, p1 w2, p2 w1, p2 w2, p1 w3, p3 w1.  Each of
+// them is exact in the matrix core's float32 accumulation; p1 w1 sums in one
+// accumulator and the five small ones in a second, added at the end.  The six
+// v_mfma_f32_16x16x32_bf16 take 6/16 of the time of the float32 MFMAs they
+// replace, and the main sum is rounded once per 32 products instead of once
+// per 2.  The weights' parts are laid out once, when the model is created:
+// per row, chunks of 32 columns, each chunk the 32 first, second and third
+// parts side by side (192 contiguous bytes).  Activations stay float32 in
+// memory and LDS; a wave splits them as it reads its fragments, in the shadow
+// of its MFMAs.
+//
+// A fragment with a value that has no finite first part (infinite, or within
+// a rounding of the largest float) takes its products on the float32 matrix
+// instruction instead, with the weights put together again from their parts
+// (exact), so that overflows come out as they do there.  Models whose weights
+// are not finite, or whose widths leave a partial 32-column chunk, stay on
+// the float32 kernels of mlp.hip.
+#include "internal.h"
+#include "split.h"
+#include "wave.h"
+
+#include <algorithm>
+
+namespace nnp {
+
+// ------------------------------------------------------------------ weights
+// Parts of src [rows][K] (row stride ld) into dst [rows][Kp / 32][3][32];
+// columns past K are zeros.
+__global__ void __launch_bounds__(256)
+k_split_weights(const float *__restrict__ src, int rows, int K, int ld, int Kp, uint16_t *__restrict__ dst) {
+  const size_t total = (size_t)rows * Kp;
+  for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
+    const int r = (int)(t / Kp), k = (int)(t - (size_t)r * Kp);
+    const float x = k < K ? src[(size_t)r * ld + k] : 0.f;
+    const __bf16 p1 = (__bf16)x;
+    const float a = x - (float)p1;
+    const __bf16 p2 = (__bf16)a;
+    const __bf16 p3 = (__bf16)(a - (float)p2);
+    uint16_t *d = dst + ((size_t)r * (Kp / 32) + k / 32) * kPartChunk + k % 32;
+    d[0] = __builtin_bit_cast(uint16_t, p1);
+    d[32] = __builtin_bit_cast(uint16_t, p2);
+    d[64] = __builtin_bit_cast(uint16_t, p3);
+  }
+}
+
+void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, uint16_t *dst, hipStream_t st) {
+  const size_t total = (size_t)rows * Kp;
+  if (total == 0) return;
+  const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 4096);
+  k_split_weights<<<blocks, 256, 0, st>>>(src, rows, K, ld, Kp, dst);
+}
+
+// ------------------------------------------------------------- grouped GEMM
+// The grouped GEMM of mlp.hip (same groups, epilogues and row records) for
+// the split operands: C[rows, n_out] = sum over K segments of A . B^T, A
+// float32, B the weights' parts.  A workgroup of WR x WC waves, each 16 HR
+// rows x 16 CB columns, takes a tile of TM rows and TN columns; both operands
+// reach LDS by direct global loads in chunks of 32 columns, STAGES chunks in
+// a ring.  LDS slots are 16 bytes: A row r's eight slots at 8 r + (slot ^
+// aswz(r)), a part's row r's four at 4 r + (slot ^ bswz(r)); the XORs keep the
+// fragment reads free of bank conflicts.  Products are formed transposed
+// (weights as the first operand), so that a lane ends with four consecutive
+// columns of one row.
+//
+// 128 x 64 tiles (4 x 1 waves of 32 x 64: every activation is split by one
+// wave only), two workgroups per compute unit.  16 x 64 tiles (1 x 4 waves of
+// 16 x 16) serve calls whose 128-row tiles would leave compute units idle: a
+// wave's chain of dependent MFMAs is an eighth as long, and the row tiles
+// without a real row are skipped.  Every output element sums its products in
+// the same order in both.
+__device__ inline int aswz(int r) { return (r >> 1) & 7; }
+__device__ inline int bswz(int r) { return ((r >> 1) ^ (r >> 3)) & 3; }
+
+constexpr int vm_count(int n) { return 0xF70 | (n & 15) | ((n >> 4) << 14); }
+// Waits until at most `ahead` chunks' loads of this wave are outstanding.
+template <int LOADS, int MAXA>
+__device__ inline void wait_ahead(int ahead) {
+  if (MAXA >= 3 && ahead >= 3) __builtin_amdgcn_s_waitcnt(vm_count(3 * LOADS));
+  else if (MAXA >= 2 && ahead >= 2) __builtin_amdgcn_s_waitcnt(vm_count(2 * LOADS));
+  else if (MAXA >= 1 && ahead >= 1) __builtin_amdgcn_s_waitcnt(vm_count(LOADS));
+  else __builtin_amdgcn_s_waitcnt(vm_count(0));
+}
+
+template <int EPI, int HR, int CB, int WR, int WC, int STAGES>
+__global__ void __launch_bounds__(WR * WC * kWave, 2)
+k_gemm_split(GemmLaunch gl) {
+  constexpr int TM = 16 * HR * WR, TN = 16 * CB * WC, T = WR * WC * kWave, TK = 32;
+  constexpr int A_SLOTS = TM * 8, B_SLOTS = TN * 12;
+  // A tiles smaller than one load of the workgroup: its first waves load them
+  constexpr int A_LD = (A_SLOTS + T - 1) / T, B_LD = B_SLOTS / T;
+  constexpr int A_WAVES = A_SLOTS < T ? A_SLOTS / kWave : WR * WC;
+  static_assert(B_SLOTS % T == 0 && (A_SLOTS % T == 0 || A_SLOTS < T), "whole load instructions");
+  extern __shared__ uint4 split_lds[];
+  const float inv_alpha = 1.f / gl.alpha;
+
+  const int lb = xcd_chunked(blockIdx.x, gl.xcd_chunk);
+  if (lb >= gl.n_blocks) return;
+  // columns: all members' side by side (member-major, as their weights lie)
+  // where the members share A (gl.span), else one member per block
+  const int n_ct = gl.col_tiles;
+  const int ct = lb % n_ct;
+  const int mb = gl.span ? 0 : (lb / n_ct) % gl.n_members;
+  const int rt = gl.span ? lb / n_ct : lb / (n_ct * gl.n_members);
+  const int r0 = rt * TM;
+  int s = -1, real_end = 0;
+  for (int q = 0; q < gl.n_groups; ++q)
+    if (r0 >= gl.bucket_off[q] && r0 < gl.bucket_off[q + 1]) {
+      s = q;
+      real_end = gl.bucket_off[q] + gl.bucket_cnt[q];
+    }
+  if (s < 0 || r0 >= real_end) return;  // no row of an atom in this tile
+  const GemmGroup grp = gl.g[mb * gl.n_groups + s];
+  const int n_cols = gl.span ? grp.n_out * gl.n_members : grp.n_out;
+  const int c0 = ct * TN;
+  if (c0 >= n_cols) return;
+  const int K = grp.K, nseg = gl.n_seg, nk = K / TK;
+
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int wr = wave / WC, wc = wave % WC;
+
+  // The 16-column halves of the AEV that some row of the tile has (see
+  // GemmLaunch::row_mask): a chunk without one is not loaded in the first
+  // layer, a column block without one is not stored in the dE/dG product.
+  constexpr bool kMaskK = EPI == kEpiFwd, kMaskN = EPI == kEpiOut;
+  unsigned long long live_h = ~0ull;
+  const bool masked = gl.row_mask != nullptr && (kMaskN || (kMaskK && nseg == 1 && nk <= 32));
+  if (masked) {
+    unsigned h_lo = 0, h_hi = 0;
+    for (int r = lane; r < min(TM, real_end - r0); r += kWave) {
+      const unsigned long long h = gl.row_mask[r0 + r];
+      h_lo |= (unsigned)h;
+      h_hi |= (unsigned)(h >> 32);
+    }
+    live_h = ((unsigned long long)wave_or(h_hi) << 32) | wave_or(h_lo);
+  }
+  bool wave_live = c0 + wc * 16 * CB < n_cols;
+  if (kMaskN && masked) {
+    const unsigned long long tile_h = (live_h >> (c0 / 16)) & ((1ull << (TN / 16)) - 1);
+    if (tile_h == 0) return;  // uniform over the workgroup, nothing issued yet
+    wave_live = wave_live && ((live_h >> ((c0 + wc * 16 * CB) / 16)) & ((1ull << CB) - 1)) != 0;
+  }
+
+  // uniform tile bases and this thread's byte offsets from them
+  const char *A = (const char *)((const float *)gl.A + (size_t)r0 * gl.lda + (size_t)mb * gl.a_member_stride);
+  const unsigned ldb = (unsigned)(nk * nseg) * (kPartChunk * 2);  // bytes of a row of B
+  const char *B = (const char *)grp.B + (size_t)c0 * ldb;
+  unsigned aoff[A_LD], boff[B_LD];
+#pragma unroll
+  for (int q = 0; q < A_LD; ++q) {
+    const int sl = q * T + tid, row = sl >> 3, ch = (sl & 7) ^ aswz(row);
+    aoff[q] = (unsigned)(row * gl.lda + ch * 4) * 4u;
+  }
+#pragma unroll
+  for (int q = 0; q < B_LD; ++q) {
+    const int sl = q * T + tid, part = sl / (TN * 4), row = (sl - part * (TN * 4)) >> 2, ch = (sl & 3) ^ bswz(row);
+    // past the columns: a valid row, its results are not stored
+    boff[q] = (unsigned)min(row, n_cols - 1 - c0) * ldb + (part * 32 + ch * 8) * 2;
+  }
+  const bool loads_a = wave < A_WAVES;  // (wave-uniform)
+  auto issue = [&](int c, int stage) {
+    const int seg = c / nk;
+    const char *ac = A + ((size_t)seg * gl.a_seg_stride + (size_t)(c - seg * nk) * TK) * 4;
+    const char *bc = B + (size_t)c * (kPartChunk * 2);
+    uint4 *dst = split_lds + stage * (A_SLOTS + B_SLOTS) + wave * kWave;
+    if (loads_a) {
+#pragma unroll
+      for (int q = 0; q < A_LD; ++q)
+        __builtin_amdgcn_global_load_lds((const void *)(ac + aoff[q]),
+                                         (__attribute__((address_space(3))) void *)(dst + q * T), 16, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < B_LD; ++q)
+      __builtin_amdgcn_global_load_lds((const void *)(bc + boff[q]),
+                                       (__attribute__((address_space(3))) void *)(dst + A_SLOTS + q * T), 16, 0, 0);
+  };
+
+  floatx4 acc[HR][CB], low[HR][CB];  // p1 w1, and the five small products
+#pragma unroll
+  for (int h = 0; h < HR; ++h)
+#pragma unroll
+    for (int j = 0; j < CB; ++j) acc[h][j] = low[h][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  int total = nk * nseg;
+  unsigned long long todo = 0;  // chunks left to issue (masked first layer)
+  if (kMaskK && masked) {
+    const unsigned long long x = live_h | (live_h >> 1);  // bit 2 c: chunk c has a live half
+    for (int c = 0; c < nk; ++c) todo |= ((x >> (2 * c)) & 1ull) << c;
+    if (todo == 0) todo = 1;
+    total = __builtin_popcountll(todo);
+  }
+  auto next = [&](int k) {
+    if (!(kMaskK && masked)) return k;
+    const int c = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    return c;
+  };
+  for (int q = 0; q < STAGES - 1; ++q)
+    if (q < total) issue(next(q), q);
+
+  for (int c = 0; c < total; ++c) {
+    if (A_WAVES == WR * WC || loads_a) wait_ahead<A_LD + B_LD, STAGES - 2>(min(total - 1 - c, STAGES - 2));
+    else wait_ahead<B_LD, STAGES - 2>(min(total - 1 - c, STAGES - 2));
+    // every wave has its part of chunk c and is done with chunk c - 1, whose
+    // stage the next issue fills
+    __builtin_amdgcn_s_barrier();
+    if (c + STAGES - 1 < total) issue(next(c + STAGES - 1), (c + STAGES - 1) % STAGES);
+    const uint4 *As = split_lds + (c % STAGES) * (A_SLOTS + B_SLOTS);
+    const uint4 *Bs = As + A_SLOTS;
+    if (!wave_live) continue;
+    Parts a[HR];
+    float big = 0.f;
+#pragma unroll
+    for (int h = 0; h < HR; ++h) {
+      const int r = (wr * HR + h) * 16 + l16;
+      // (typed vector reads: an untyped copy would make the compiler wait for
+      // every load to LDS in flight)
+      const floatx4 u = *(const floatx4 *)&As[8 * r + ((2 * kq) ^ aswz(r))];
+      const floatx4 v = *(const floatx4 *)&As[8 * r + ((2 * kq + 1) ^ aswz(r))];
+      const float x[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
+      // (padding rows hold whatever an earlier call left there)
+      big = fmaxf(big, r0 + r < real_end ? max8(x) : 0.f);
+      a[h] = split8(x);
+    }
+    // block j's fragment of part p: slot(j)[4 TN p] (the XOR of a row depends
+    // on its block's parity alone)
+    const uint4 *be = Bs + 4 * ((wc * CB) * 16 + l16);
+    const int xe = kq ^ bswz((wc * CB) * 16 + l16), xo = kq ^ bswz((wc * CB + 1) * 16 + l16);
+    auto slot = [&](int j) { return be + 64 * j + (j & 1 ? xo : xe); };
+    if (__ballot(big > kPartMax) == 0) {
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        const bf16x8 b1 = __builtin_bit_cast(bf16x8, slot(j)[0]);
+        const bf16x8 b2 = __builtin_bit_cast(bf16x8, slot(j)[4 * TN]);
+        const bf16x8 b3 = __builtin_bit_cast(bf16x8, slot(j)[8 * TN]);
+#pragma unroll
+        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a[h].p3, low[h][j], 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b3, a[h].p1, low[h][j], 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b2, a[h].p2, low[h][j], 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a[h].p2, low[h][j], 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b2, a[h].p1, low[h][j], 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < HR; ++h) acc[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a[h].p1, acc[h][j], 0, 0, 0);
+      }
+    } else {
+#pragma unroll 1
+      for (int k = 0; k < 8; ++k) {
+#pragma unroll
+        for (int j = 0; j < CB; ++j) {
+          const float b = joined((const uint16_t *)slot(j) + k, 32 * TN);
+#pragma unroll
+          for (int h = 0; h < HR; ++h) {
+            const int r = (wr * HR + h) * 16 + l16;
+            const float x = ((const float *)&As[8 * r + ((2 * kq + (k >> 2)) ^ aswz(r))])[k & 3];
+            acc[h][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b, x, acc[h][j], 0, 0, 0);
+          }
+        }
+      }
+    }
+  }
+
+  // lane: row l % 16 of each sixteen, columns 4 (l / 16) + 0..3 of each
+  // sixteen, which lie within one member (widths are multiples of 32 wherever
+  // columns span members)
+  if (!wave_live) return;
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    const int v16 = c0 + (wc * CB + j) * 16;  // wave-uniform
+    // (a descriptor length may end inside a sixteen; it is a multiple of 4)
+    if (v16 + 4 * kq >= n_cols || (kMaskN && !((live_h >> (v16 / 16)) & 1ull))) continue;
+    const int om = gl.span ? v16 / grp.n_out : mb;
+    const int col = v16 - (gl.span ? om * grp.n_out : 0) + 4 * kq;
+    float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (EPI == kEpiFwd) bias = *(const float4 *)(gl.g[om * gl.n_groups + s].bias + col);
+#pragma unroll
+    for (int h = 0; h < HR; ++h) {
+      const int row = r0 + (wr * HR + h) * 16 + l16;
+      const floatx4 v = acc[h][j] + low[h][j];
+      float4 o;
+      if (EPI == kEpiFwd) {
+        o = make_float4(celu32(v[0] + bias.x, gl.alpha, inv_alpha), celu32(v[1] + bias.y, gl.alpha, inv_alpha),
+                        celu32(v[2] + bias.z, gl.alpha, inv_alpha), celu32(v[3] + bias.w, gl.alpha, inv_alpha));
+      } else if (EPI == kEpiBwd) {
+        const float4 x = *(const float4 *)((const float *)gl.H + (size_t)row * gl.ldh + (size_t)om * gl.h_member_stride + col);
+        o = make_float4(v[0] * dcelu32(x.x, inv_alpha) * gl.scale, v[1] * dcelu32(x.y, inv_alpha) * gl.scale,
+                        v[2] * dcelu32(x.z, inv_alpha) * gl.scale, v[3] * dcelu32(x.w, inv_alpha) * gl.scale);
+      } else {
+        o = make_float4(v[0] * gl.scale, v[1] * gl.scale, v[2] * gl.scale, v[3] * gl.scale);
+      }
+      *(float4 *)((float *)gl.C + (size_t)row * gl.ldc + (size_t)om * gl.c_member_stride + col) = o;
+    }
+  }
+}
+
+template <int EPI, int HR, int CB, int WR, int WC, int STAGES>
+static void gemm_split_t(GemmLaunch gl, int rows, int cols, hipStream_t st) {
+  constexpr int TM = 16 * HR * WR, TN = 16 * CB * WC;
+  gl.col_tiles = (cols + TN - 1) / TN;
+  gl.xcd_chunk = (gl.span ? 1 : gl.n_members) * gl.col_tiles;
+  gl.n_blocks = rows / TM * gl.xcd_chunk;
+  const size_t lds = (size_t)STAGES * (TM * 8 + TN * 12) * 16;
+  k_gemm_split<EPI, HR, CB, WR, WC, STAGES>
+      <<<xcd_grid((unsigned)gl.n_blocks, gl.xcd_chunk), WR * WC * kWave, lds, st>>>(gl);
+}
+
+// tn_pref 64: 16-row tiles, 128 or 256: 128-row tiles, else by the grid.
+void launch_gemm_split(int epi, GemmLaunch gl, int rows, int max_n_out, int tn_pref, hipStream_t st) {
+  if (rows <= 0) return;
+  // members side by side where they share A and every 32-column block lies
+  // in one member
+  gl.span = epi == kEpiFwd && gl.a_member_stride == 0 && gl.n_members > 1;
+  int cols = max_n_out;
+  if (gl.span) cols *= gl.n_members;
+  const long long big = (long long)(rows / 128) * ((cols + 127) / 128) * (gl.span ? 1 : gl.n_members);
+  const bool small = tn_pref == 64 || (tn_pref != 128 && tn_pref != 256 && big < 256);
+#define NNP_SPLIT(E)                                                  \
+  if (small) gemm_split_t<E, 1, 1, 1, 4, 4>(gl, rows, cols, st);      \
+  else gemm_split_t<E, 2, 8, 4, 1, 2>(gl, rows, cols, st)
+  if (epi == kEpiFwd) { NNP_SPLIT(kEpiFwd); }
+  else if (epi == kEpiBwd) { NNP_SPLIT(kEpiBwd); }
+  else { NNP_SPLIT(kEpiOut); }
+#undef NNP_SPLIT
+}
+
+}  // namespace nnp

@@ -10,6 +10,23 @@ __device__ inline unsigned lanes_below(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
 }
 
+// A pointer that the kernel read from memory, as one to global memory: the
+// compiler knows no more than that it is some address, and would load through
+// it with flat instructions, which count as LDS accesses too, so that every
+// wait for one waits for all loads in flight.
+template <class T> using Global = const __attribute__((address_space(1))) T *;
+template <class T> __device__ inline Global<T> as_global(const T *p) { return (Global<T>)p; }
+typedef unsigned uintx4_v __attribute__((ext_vector_type(4)));
+typedef float floatx4_v __attribute__((ext_vector_type(4)));
+template <class T> __device__ inline uint4 load16(Global<T> p) {
+  const uintx4_v v = *(Global<uintx4_v>)p;
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+__device__ inline float4 load4f(Global<float> p) {
+  const floatx4_v v = *(Global<floatx4_v>)p;
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
 // Hardware reciprocal and square root (about 1 ulp), in place of the
 // correctly rounded division and square-root sequences.
 __device__ inline float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
