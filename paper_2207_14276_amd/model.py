@@ -346,15 +346,18 @@ class NNPFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, coords, species, boxes, offsets, model: NNPModel):
         res = model.energy_forces(coords, species, boxes, offsets, forces=True)
-        offs = np.asarray(offsets, dtype=np.int64)
-        counts = torch.as_tensor(np.diff(offs), device=coords.device)
-        ctx.save_for_backward(res.forces, counts)
+        ctx.save_for_backward(res.forces)
+        ctx.counts = np.diff(np.asarray(offsets, dtype=np.int64))
         ctx.coords_dtype = coords.dtype
         return res.energy
 
     @staticmethod
     @torch.autograd.function.once_differentiable
     def backward(ctx, grad_e):
-        forces, counts = ctx.saved_tensors
-        g = torch.repeat_interleave(grad_e.to(torch.float32), counts)
-        return (-g[:, None] * forces).to(ctx.coords_dtype), None, None, None, None
+        (forces,) = ctx.saved_tensors
+        g = -grad_e.to(torch.float32)
+        if len(ctx.counts) > 1:
+            # the output size is known here: no wait for the device
+            g = torch.repeat_interleave(g, torch.as_tensor(ctx.counts, device=g.device),
+                                        output_size=int(forces.shape[0]))
+        return (g[:, None] * forces).to(ctx.coords_dtype), None, None, None, None
