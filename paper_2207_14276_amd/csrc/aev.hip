@@ -1,7 +1,8 @@
 // Atomic environment vectors and their gradient (section "ANI models":
 // cosine cutoff, radial and angular symmetry functions).
 //
-// One wavefront per centre atom; for calls of several systems the waves take
+// One wavefront per centre atom (or a workgroup of four, where one per centre
+// leaves the chip idle); for calls of several systems the waves take
 // the centres of the largest systems first (wave_atom), so that no costly
 // centre starts last.  The centre's neighbour entries (its list row, or for
 // small systems without a list the atoms of its system) are re-derived from
@@ -201,6 +202,31 @@ __device__ __attribute__((always_inline)) inline bool load_entry(int e, int n, c
   return v;
 }
 
+// One entry (vector d, R in w) into slot q of the radial list and slot qa of
+// the angular list.
+template <bool BWD>
+__device__ __attribute__((always_inline)) inline void put_entry(int q, int qa, bool inR, bool inA, int j,
+                                                                const float4 &d, float kr, float ka, WaveLds &w) {
+  if (inR) {
+    float sn, cs;
+    __sincosf(kr * d.w, &sn, &cs);
+    // the pair geometry and the gradients need only the direction and R
+    const float ir = fast_rcp(d.w);
+    w.rD[q] = make_float4(d.x * ir, d.y * ir, d.z * ir, d.w);
+    if (BWD) {
+      w.rF2[q] = make_float2(0.5f * cs + 0.5f, -0.5f * kr * sn);
+      w.rJ[q] = j;
+    } else {
+      w.rFc[q] = 0.5f * cs + 0.5f;
+    }
+  }
+  if (inA) {
+    if (BWD) w.aIdx[qa] = q;
+    else w.aIdx16[qa] = (unsigned short)q;
+    if (!BWD) w.aFc[qa] = 0.5f * __cosf(ka * d.w) + 0.5f;
+  }
+}
+
 // Builds the species-sorted radial list (R < rc_r) and angular list
 // (R < rc_a, a subset) of centre i in LDS from its neighbour row, or (self
 // >= 0) from all atoms of its system, keeping those a list would hold (R^2
@@ -292,24 +318,98 @@ __device__ inline void fill_lists(int lane, int n, const int2 *__restrict__ ent,
       pR[s] += __popcll(mR);
       pA[s] += __popcll(mA);
     }
-    if (inR) {
-      float sn, cs;
-      __sincosf(kr * d.w, &sn, &cs);
-      // the pair geometry and the gradients need only the direction and R
-      const float ir = fast_rcp(d.w);
-      w.rD[q] = make_float4(d.x * ir, d.y * ir, d.z * ir, d.w);
-      if (BWD) {
-        w.rF2[q] = make_float2(0.5f * cs + 0.5f, -0.5f * kr * sn);
-        w.rJ[q] = j;
-      } else {
-        w.rFc[q] = 0.5f * cs + 0.5f;
+    put_entry<BWD>(q, qa, inR, inA, j, d, kr, ka, w);
+  }
+}
+
+// A workgroup of W waves at one centre (W = 1: a wave on its own): orders the
+// LDS writes of all of them before their later reads.
+template <int W> __device__ inline void centre_sync() {
+  if constexpr (W == 1) {
+    wave_lds_sync();
+  } else {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  }
+}
+
+// fill_lists by the W waves of a workgroup: wave v takes the row's 64-entry
+// chunks v, v + W, ...; the chunks' species counts meet in LDS (cnt, 16 ints a
+// chunk), and every entry lands where the one-wave form puts it.
+constexpr int kMaxChunks = 1024 / kWave + 1;  // rows hold at most 1,024 entries, systems without a list one more
+template <bool BWD, int W>
+__device__ inline void fill_lists_group(int wave, int lane, int n, const int2 *__restrict__ ent, int self, int j0,
+                                        int n_sys, const float4 *__restrict__ pos, const float4 &pi,
+                                        const float L[3], const AevConst &c, WaveLds &w, int *cnt) {
+  const int S = c.S;
+  const float rc2 = c.rc_r * c.rc_r;
+  auto load = [&](int b, int &sj, int &j, float4 &d, bool &inR, bool &inA) {
+    load_entry(b + lane, n, ent, self, j0, n_sys, pos, pi, L, sj, j, d);
+    inR = sj >= 0 && d.w < c.rc_r && (self < 0 || d.x * d.x + d.y * d.y + d.z * d.z < rc2);
+    inA = inR && d.w < c.rc_a;
+  };
+  // the wave's first chunk stays in registers for both passes
+  int sj0 = -1, jj0 = 0;
+  float4 d0 = make_float4(0.f, 0.f, 0.f, 1e30f);
+  bool inR0 = false, inA0 = false;
+  const int b0 = wave * kWave;
+  if (b0 < n) load(b0, sj0, jj0, d0, inR0, inA0);
+  for (int b = b0; b < n; b += W * kWave) {
+    int sj = sj0, j = jj0;
+    float4 d = d0;
+    bool inR = inR0, inA = inA0;
+    if (b != b0) load(b, sj, j, d, inR, inA);
+    int v = 0;  // lane s: radial entries of species s, lane 8 + s: angular ones
+#pragma unroll
+    for (int s = 0; s < kMaxSpecies; ++s) {
+      const int r = __popcll(__ballot(inR && sj == s)), a = __popcll(__ballot(inA && sj == s));
+      v = lane == s ? r : lane == 8 + s ? a : v;
+    }
+    if (lane < 16) cnt[(b / kWave) * 16 + lane] = v;
+  }
+  centre_sync<W>();
+  // lane s / 8 + s: the species' total, then its first slot in the list
+  const int chunks = (n + kWave - 1) / kWave;
+  int tot = 0;
+  if (lane < 16)
+    for (int k = 0; k < chunks; ++k) tot += cnt[k * 16 + lane];
+  int first = tot;
+#pragma unroll
+  for (int d = 1; d < 8; d <<= 1) {
+    const int y = __shfl_up(first, d, 8);
+    if ((lane & 7) >= d) first += y;
+  }
+  first -= tot;
+  if (wave == 0 && lane < 16) {
+    int *t = (lane < 8 ? w.ls->cR : w.ls->cA) + (lane & 7);
+    t[0] = (lane & 7) < S ? tot : 0;
+    t[8] = first;  // oR / oA follow cR / cA
+  }
+  const float kr = kPi / c.rc_r, ka = kPi / c.rc_a;
+  (void)ka;
+  int done = 0;  // chunks before b, summed into `first` so far
+  for (int b = b0; b < n; b += W * kWave) {
+    if (lane < 16)
+      for (; done < b / kWave; ++done) first += cnt[done * 16 + lane];
+    done = b / kWave;
+    int sj = sj0, j = jj0;
+    float4 d = d0;
+    bool inR = inR0, inA = inA0;
+    if (b != b0) load(b, sj, j, d, inR, inA);
+    int q = 0, qa = 0;
+#pragma unroll
+    for (int s = 0; s < kMaxSpecies; ++s) {
+      const unsigned long long mR = __ballot(inR && sj == s);
+      if (!mR) continue;
+      const unsigned long long mA = __ballot(inA && sj == s);
+      const int fR = __builtin_amdgcn_readlane(first, s), fA = __builtin_amdgcn_readlane(first, 8 + s);
+      if (sj == s) {
+        q = fR + (int)lanes_below(mR);
+        qa = fA + (int)lanes_below(mA);
       }
     }
-    if (inA) {
-      if (BWD) w.aIdx[qa] = q;
-      else w.aIdx16[qa] = (unsigned short)q;
-      if (!BWD) w.aFc[qa] = 0.5f * __cosf(ka * d.w) + 0.5f;
-    }
+    put_entry<BWD>(q, qa, inR, inA, j, d, kr, ka, w);
   }
 }
 
@@ -370,7 +470,13 @@ __device__ inline unsigned long long spread_pairs(unsigned long long x) {
 static_assert(kNShfRad == 16 && kAngBlock == 32, "row mask halves");
 static_assert(kMaxSpecies + kMaxSpecies * (kMaxSpecies + 1) <= 64, "row mask width");
 
-template <int WPB, bool BF16>
+// Several waves per centre (GROUP): for calls with fewer centres than the chip
+// has SIMDs, where a centre's chain of passes is the call's latency, and for
+// neighbour capacities whose lists leave too few waves on a compute unit.  The
+// waves share the centre's lists; the radial species and the species-pair
+// blocks are dealt out over them, each block whole to one wave, so that every
+// sum is formed as by one wave.
+template <int WPB, bool BF16, bool GROUP>
 __global__ void __launch_bounds__(WPB * kWave)
 k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
           const SysDesc *__restrict__ sys, const int2 *__restrict__ nbr,
@@ -382,11 +488,20 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
   // the wave index is uniform across the wave: keep it (and the centre's
   // index, descriptors and row pointers) in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
-  const int wv = blockIdx.x * WPB + wave;
+  constexpr int W = GROUP ? WPB : 1;  // waves per centre
+  const int wv = GROUP ? (int)blockIdx.x : blockIdx.x * WPB + wave;
   const int i = wave_atom && wv < N ? __builtin_amdgcn_readfirstlane(wave_atom[wv]) : wv;
   // an atom without a network row (outside a caller's mask) is skipped
   const bool live = i < N && row_of_atom[i] >= 0;
-  WaveLds w = carve<false>((char *)lds4 + wave * wave_lds_bytes<false>(cap), cap);
+  WaveLds w = carve<false>((char *)lds4 + (GROUP ? 0 : wave * wave_lds_bytes<false>(cap)), cap);
+  int *cnt = nullptr;
+  if (GROUP) {
+    // the waves' pair scratch follows the lists (the chunk counts use it first)
+    char *scratch = (char *)lds4 + wave_lds_bytes<false>(cap);
+    cnt = (int *)scratch;
+    w.tGeo = (float2 *)(scratch + wave * kPairPass * 24);
+    w.tF2 = (float4 *)(scratch + wave * kPairPass * 24 + kPairPass * 8);
+  }
   float4 pi = make_float4(0.f, 0.f, 0.f, 0.f);
   float L[3] = {0.f, 0.f, 0.f};
   int n = 0, j0 = 0, n_sys = 0, self = -1;
@@ -405,7 +520,8 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
       self = i - d.atom_off;
     }
   }
-  fill_lists<false>(lane, n, row, self, j0, n_sys, pos, pi, L, c, w);
+  if constexpr (GROUP) fill_lists_group<false, W>(wave, lane, n, row, self, j0, n_sys, pos, pi, L, c, w, cnt);
+  else fill_lists<false>(lane, n, row, self, j0, n_sys, pos, pi, L, c, w);
   __syncthreads();
   if (!live) return;
   const Lists &ls = *w.ls;
@@ -413,7 +529,7 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
   // records) goes to status[1]: the current value is read here and compared
   // at the end, so that the wave does not wait for it
   int nb_cnt = 0, nb_max = 0;
-  if (status) {
+  if (status && (!GROUP || wave == 0)) {
     for (int s = 0; s < c.S; ++s) nb_cnt += ls.cR[s];
     nb_max = __hip_atomic_load(status + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -426,7 +542,7 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
     const int m = lane >> 2, slot = lane & 3;
     const float shf = pick(c.shf_r, m);
     const float keta = -c.eta_r * 1.4426950408889634f;
-    for (int s = 0; s < c.S; ++s) {
+    for (int s = GROUP ? wave : 0; s < c.S; s += W) {
       float acc = 0.f;
       const int o = ls.oR[s];
       const int cnt = ls.cR[s];
@@ -461,14 +577,14 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
     // an entry, species pairs with a pair
     if (row_mask) {
       const unsigned long long radial = __ballot(lane < c.S && ls.cR[min(lane, kMaxSpecies - 1)] > 0);
-      if (lane == 0) row_mask[r_i] = radial | spread_pairs(nonempty) << c.S;
+      if (lane == 0 && (!GROUP || wave == 0)) row_mask[r_i] = radial | spread_pairs(nonempty) << c.S;
     }
     // blocks without a pair of their two species are zero: written in one
     // pass of 16-byte stores over the angular part of the row
     {
       constexpr int kChunksPerBlock = kAngBlock * (BF16 ? 2 : 4) / 16;
       uint4 *ang = (uint4 *)((char *)Grow + (size_t)c.rad_len * (BF16 ? 2 : 4));
-      for (int k = lane; k < n_blk * kChunksPerBlock; k += kWave)
+      for (int k = GROUP ? (int)threadIdx.x : lane; k < n_blk * kChunksPerBlock; k += W * kWave)
         if (!((nonempty >> (k / kChunksPerBlock)) & 1ull)) ang[k] = make_uint4(0u, 0u, 0u, 0u);
     }
     // Passes of 64 pair slots.  A block with more than 64 pairs left fills
@@ -477,6 +593,17 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
     // of 8 slots, so that every group of 8 slots belongs to one block.
     float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f, acc3 = 0.f;
     unsigned long long pending = nonempty;
+    if constexpr (GROUP) {
+      // the blocks whose middle lies in this wave's share of all pair slots
+      int end = (bT + 7) & ~7;
+#pragma unroll
+      for (int d = 1; d < 32; d <<= 1) {  // n_blk <= 28
+        const int y = __shfl_up(end, d, 32);
+        if ((lane & 31) >= d) end += y;
+      }
+      const int total = __builtin_amdgcn_readlane(end, n_blk - 1), mid = end - ((bT + 7) >> 1);
+      pending = __ballot(bT > 0 && min((int)((float)mid * (float)W * fast_rcp((float)max(total, 1))), W - 1) == wave);
+    }
     int u = 0;  // pairs of the first pending block done by earlier passes
     while (pending) {
       const int q = __builtin_ctzll(pending);
@@ -660,13 +787,14 @@ struct SinkHash {
   }
 };
 
-// Backward of centre i by one wave (wave-uniform i; no workgroup barrier, so
-// waves of one workgroup may work on different centres): dE/dd of every
+// Backward of centre i by one wave (W = 1; wave-uniform i, no workgroup
+// barrier, so waves of one workgroup may work on different centres) or by the
+// W waves of a workgroup (see k_aev_fwd), which share the lists: dE/dd of every
 // radial entry from the radial and angular terms, the centre's virial row
 // W_atom[i] = -sum d (x) dE/dd, and its force contributions through sink:
 // -dE/dd onto each neighbour, the sum of dE/dd onto the centre.
-template <class Sink>
-__device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ pos, const int *__restrict__ sys_of,
+template <int W, class Sink>
+__device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__restrict__ pos, const int *__restrict__ sys_of,
                                   const SysDesc *__restrict__ sys, const int2 *__restrict__ nbr,
                                   const int *__restrict__ nbr_cnt, int cap, const int *__restrict__ row_of_atom,
                                   const float *__restrict__ dG, int ldg, const AevConst &c,
@@ -675,7 +803,7 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
   // virial share is zero
   const int r_i = row_of_atom[i];
   if (r_i < 0) {
-    if (lane < 9) W_atom[(size_t)9 * i + lane] = 0.f;
+    if (lane < 9 && wave == 0) W_atom[(size_t)9 * i + lane] = 0.f;
     return;
   }
   const SysDesc &d = sys[sys_of[i]];
@@ -687,8 +815,11 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
   const float L[3] = {d.L[0], d.L[1], d.L[2]};
   const int j0 = d.atom_off;
   const int2 *row = nbr ? nbr + nbr_row(d, i, cap) : nbr;
-  fill_lists<true>(lane, n, row, self, j0, n_sys, pos, pi, L, c, w);
-  wave_lds_sync();
+  // (the chunk counts of a group lie where the dE/dd accumulators follow)
+  if constexpr (W > 1) fill_lists_group<true, W>(wave, lane, n, row, self, j0, n_sys, pos, pi, L, c, w, (int *)w.rG);
+  else fill_lists<true>(lane, n, row, self, j0, n_sys, pos, pi, L, c, w);
+  centre_sync<W>();
+  const int first_e = wave * kWave + lane;  // this lane's first entry of a list
   const Lists &ls = *w.ls;
   const float *g = dG + (size_t)r_i * ldg;
   int nR = 0;
@@ -700,7 +831,7 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
   // accumulators.
   {
     const float keta = -c.eta_r * 1.4426950408889634f;
-    for (int e = lane; e < nR; e += kWave) {
+    for (int e = first_e; e < nR; e += W * kWave) {
       int sp = 0;
 #pragma unroll
       for (int s = 1; s < kMaxSpecies; ++s) sp += e >= ls.oR[s] ? 1 : 0;
@@ -725,7 +856,7 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
       gg[0] = (double)(dEdR * d.x); gg[1] = (double)(dEdR * d.y); gg[2] = (double)(dEdR * d.z);
     }
   }
-  wave_lds_sync();
+  centre_sync<W>();
 
   // angular cutoff of every angular entry, into its radial cutoff slot (the
   // radial stage above was the last reader of those)
@@ -733,14 +864,14 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
     const float ka = kPi / c.rc_a;
     int nA = 0;
     for (int s = 0; s < c.S; ++s) nA += ls.cA[s];
-    for (int e = lane; e < nA; e += kWave) {
+    for (int e = first_e; e < nA; e += W * kWave) {
       const int q = w.aIdx[e];
       float sn, cs;
       __sincosf(ka * w.rD[q].w, &sn, &cs);
       w.rF2[q] = make_float2(0.5f * cs + 0.5f, -0.5f * ka * sn);
     }
   }
-  wave_lds_sync();
+  centre_sync<W>();
 
   // angular: lane per neighbour pair over the pair stream of all blocks
   // (the blocks' pairs one after another, in feature order)
@@ -767,7 +898,8 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
     // the block searches visit non-empty blocks only
     const unsigned long long nonempty = __ballot(bT > 0);
     int qb = nonempty ? __builtin_ctzll(nonempty) : 0;
-    for (int base = 0; base < P; base += kPairPass) {
+    for (int round = 0; round < P; round += W * kPairPass) {
+      const int base = round + wave * kPairPass;  // (W > 1: possibly past the end, in the last round)
       for (unsigned long long m = nonempty & (~0ull << (qb + 1)); m; m &= m - 1) {
         const int r = __builtin_ctzll(m);
         if (__builtin_amdgcn_readlane(bStart, r) > base) break;
@@ -775,6 +907,8 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
       }
       const bool valid = base + lane < P;
       const int t = min(base + lane, P - 1);
+      // (the pass's values; the adds below take the waves' passes in turn)
+      float gjx = 0.f, gjy = 0.f, gjz = 0.f, gkx = 0.f, gky = 0.f, gkz = 0.f;
       // this lane's block: the last non-empty one starting at or before its
       // pair; the pass's blocks are few, their starts wave-uniform
       int p = qb;
@@ -865,20 +999,28 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
         const float beta = dcos - (sinv > 1e-12f ? dsin * cosv * fast_rcp(sinv) : 0.f);
         const float bj = beta * fast_rcp(dj.w), bk = beta * fast_rcp(dk.w);
         const float uj = dRj - bj * cosv, uk = dRk - bk * cosv;
-        // float64 LDS atomics: the wave's own region, so the adds to an
-        // entry happen in one fixed order (program order, then lane order
-        // within an instruction) and the sums are the same on every call
-        double *gj = w.rG + 3 * qj;
-        double *gk = w.rG + 3 * qk;
-        atomicAdd(gj + 0, (double)(bj * dk.x + uj * dj.x));
-        atomicAdd(gj + 1, (double)(bj * dk.y + uj * dj.y));
-        atomicAdd(gj + 2, (double)(bj * dk.z + uj * dj.z));
-        atomicAdd(gk + 0, (double)(bk * dj.x + uk * dk.x));
-        atomicAdd(gk + 1, (double)(bk * dj.y + uk * dk.y));
-        atomicAdd(gk + 2, (double)(bk * dj.z + uk * dk.z));
+        gjx = bj * dk.x + uj * dj.x; gjy = bj * dk.y + uj * dj.y; gjz = bj * dk.z + uj * dj.z;
+        gkx = bk * dj.x + uk * dk.x; gky = bk * dj.y + uk * dk.y; gkz = bk * dj.z + uk * dk.z;
+      }
+      // float64 LDS atomics into the centre's own region, a pass after the
+      // other: the adds to an entry happen in one fixed order (pass, then
+      // program order, then lane order within an instruction) and the sums are
+      // the same on every call
+      for (int turn = 0; turn < W; ++turn) {
+        if ((W == 1 || turn == wave) && valid) {
+          double *gj = w.rG + 3 * qj;
+          double *gk = w.rG + 3 * qk;
+          atomicAdd(gj + 0, (double)gjx);
+          atomicAdd(gj + 1, (double)gjy);
+          atomicAdd(gj + 2, (double)gjz);
+          atomicAdd(gk + 0, (double)gkx);
+          atomicAdd(gk + 1, (double)gky);
+          atomicAdd(gk + 2, (double)gkz);
+        }
+        if (W > 1) centre_sync<W>();
       }
     }
-    wave_lds_sync();
+    centre_sync<W>();
   }
 
   // scatter: -dE/dd onto each neighbour, the sum onto the centre (fixed
@@ -888,11 +1030,20 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
     float vir[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) vir[q] = 0.f;
+    // a group: its first wave forms the centre's sums (in the one-wave order),
+    // the others send the neighbours' shares
+    if (W > 1 && wave > 0) {
+      for (int e = first_e - kWave; e < nR; e += (W - 1) * kWave) {
+        const float gx = (float)w.rG[3 * e], gy = (float)w.rG[3 * e + 1], gz = (float)w.rG[3 * e + 2];
+        sink.add(w.rJ[e], -to_fix(gx), -to_fix(gy), -to_fix(gz));
+      }
+      return;
+    }
     for (int e = lane; e < nR; e += kWave) {
       const float4 ur = w.rD[e];  // unit vector and R
       const float4 dv = make_float4(ur.x * ur.w, ur.y * ur.w, ur.z * ur.w, ur.w);
       const float gx = (float)w.rG[3 * e], gy = (float)w.rG[3 * e + 1], gz = (float)w.rG[3 * e + 2];
-      sink.add(w.rJ[e], -to_fix(gx), -to_fix(gy), -to_fix(gz));
+      if (W == 1) sink.add(w.rJ[e], -to_fix(gx), -to_fix(gy), -to_fix(gz));
       fi0 += gx; fi1 += gy; fi2 += gz;
       vir[0] -= dv.x * gx; vir[1] -= dv.x * gy; vir[2] -= dv.x * gz;
       vir[3] -= dv.y * gx; vir[4] -= dv.y * gy; vir[5] -= dv.y * gz;
@@ -912,12 +1063,12 @@ __device__ inline void bwd_centre(int i, int lane, const float4 *__restrict__ po
     }
   }
   // the next centre of this wave rewrites the lists
-  wave_lds_sync();
+  if (W == 1) wave_lds_sync();
 }
 
-// Per-centre form (caller pair lists, small cell grids): one wave per centre,
-// forces by device atomics.
-template <int WPB>
+// Per-centre form: one wave per centre, or the WPB waves of a workgroup
+// (GROUP), forces by device atomics.
+template <int WPB, bool GROUP>
 __global__ void __launch_bounds__(WPB * kWave)
 k_aev_bwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
           const SysDesc *__restrict__ sys, const int2 *__restrict__ nbr,
@@ -928,13 +1079,13 @@ k_aev_bwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
   // the wave index is uniform across the wave: keep it (and the centre's
   // index, descriptors and row pointers) in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
-  const int wv = blockIdx.x * WPB + wave;
+  const int wv = GROUP ? (int)blockIdx.x : blockIdx.x * WPB + wave;
   if (wv >= N.get()) return;
   // the centre of this wave (the costliest systems' centres first)
   const int i = wave_atom ? __builtin_amdgcn_readfirstlane(wave_atom[wv]) : wv;
-  WaveLds w = carve<true>((char *)lds4 + wave * wave_lds_bytes<true>(cap), cap);
+  WaveLds w = carve<true>((char *)lds4 + (GROUP ? 0 : wave * wave_lds_bytes<true>(cap)), cap);
   const SysDesc &d = sys[sys_of[i]];
-  bwd_centre(i, lane, pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg, c, W_atom, w,
+  bwd_centre<GROUP ? WPB : 1>(i, GROUP ? wave : 0, lane, pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg, c, W_atom, w,
              SinkGlobal{Ffix, fix_shift(d)});
 }
 
@@ -971,7 +1122,7 @@ k_aev_bwd_sys(const int2 *__restrict__ groups, const float4 *__restrict__ pos, c
   WaveLds w = carve<true>((char *)lds4 + wave * wave_lds_bytes<true>(cap), cap);
   const SinkSys sink{tab, off};
   for (int p = next_centre(&counter, lane); p < gr.y; p = next_centre(&counter, lane))
-    bwd_centre(gr.x + p, lane, pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg, c, W_atom, w, sink);
+    bwd_centre<1>(gr.x + p, 0, lane, pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg, c, W_atom, w, sink);
   __syncthreads();
   for (int t = threadIdx.x; t < n3; t += WPB * kWave) {
     const unsigned long long v = tab[t];
@@ -1010,7 +1161,7 @@ k_aev_bwd_cells(const int *__restrict__ cell_start, const int *__restrict__ cell
   const int shift = fix_shift(sys[sys_of[cell_atoms[b]]]);
   const SinkHash sink{hkey, hval, Ffix, shift};
   for (int p = next_centre(&counter, lane); b + p < e; p = next_centre(&counter, lane))
-    bwd_centre(cell_atoms[b + p], lane, pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg, c, W_atom, w,
+    bwd_centre<1>(cell_atoms[b + p], 0, lane, pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg, c, W_atom, w,
                sink);
   __syncthreads();
   for (int t = threadIdx.x; t < kBwdHash; t += WPB * kWave) {
@@ -1029,42 +1180,64 @@ k_aev_bwd_cells(const int *__restrict__ cell_start, const int *__restrict__ cell
 // and single-wave workgroups pack the compute units most freely (it was the
 // fastest shape on most measured batches).
 template <bool BWD>
-static int waves_for_cap(int cap, int pref) {
+static int waves_for_cap(int cap, int pref) {  // centres per workgroup, a wave each
   const size_t per = wave_lds_bytes<BWD>(cap);
   if ((pref == 1 || pref == 2 || pref == 4) && per * pref <= 64 * 1024) return pref;
   return 1;
+}
+
+// Several waves per centre where the centres alone leave the chip idle:
+//   - few centres: at most 1,024 (one wave per SIMD), or 4,096 in systems
+//     without a list, whose dense environments make a centre's passes many.
+//     Measured, forward / backward: 101 atoms 55 / 52 -> 21 / 26 us; 64 dense
+//     solutes (4,000 atoms) 74 / 77 -> 46 / 61 us, 100 of them 82 / 94 -> 68 /
+//     96; a water box of 1,200 atoms 15 / 18 -> 13 / 19, of 2,001 14 / 22 ->
+//     17 / 28 us (a centre has two passes, and waits for the group);
+//   - lists so long that the LDS holds fewer than eleven one-wave centres per
+//     compute unit: a mix of solutes and boxes of 60 to 2,400 atoms at a
+//     capacity of 640 (18 / 36 KB a wave) 344 / 579 -> 206 / 370 us; water at
+//     256 (8 / 15 KB) 39 / 73 -> 62 / 90 us.
+constexpr int kGroupWaves = 4;
+static bool group_centres(int n_centres, bool list, size_t lds_per_wave, size_t max_lds) {
+  return n_centres <= (list ? 1024 : 4096) || lds_per_wave * 11 > max_lds;
 }
 
 template <bool BF16>
 static void aev_fwd_t(const float4 *pos, const int *sys_of, const SysDesc *sys, const int2 *nbr,
                       const int *nbr_cnt, int cap, const int *row_of_atom, void *G, int ldg,
                       unsigned long long *row_mask, const int *wave_atom, int *status, Live N, const AevConst &c,
-                      int wpb_pref, hipStream_t st) {
+                      int wpb_pref, size_t max_lds, hipStream_t st) {
+  if (group_centres(N.v, nbr != nullptr, wave_lds_bytes<false>(cap), max_lds)) {
+    const size_t lds = wave_lds_bytes<false>(cap) + kGroupWaves * kPairPass * 24;
+    k_aev_fwd<kGroupWaves, BF16, true><<<(unsigned)N.v, kGroupWaves * kWave, lds, st>>>(
+        pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg, row_mask, wave_atom, status, N, c);
+    return;
+  }
   int wpb = waves_for_cap<false>(cap, wpb_pref);
   size_t lds = wave_lds_bytes<false>(cap) * wpb;
   unsigned grid = (unsigned)((N.v + wpb - 1) / wpb);
   if (wpb == 4)
-    k_aev_fwd<4, BF16><<<grid, 4 * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
-                                                     row_mask, wave_atom, status, N, c);
+    k_aev_fwd<4, BF16, false><<<grid, 4 * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
+                                                            row_mask, wave_atom, status, N, c);
   else if (wpb == 2)
-    k_aev_fwd<2, BF16><<<grid, 2 * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
-                                                     row_mask, wave_atom, status, N, c);
+    k_aev_fwd<2, BF16, false><<<grid, 2 * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
+                                                            row_mask, wave_atom, status, N, c);
   else
-    k_aev_fwd<1, BF16><<<grid, kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
-                                                 row_mask, wave_atom, status, N, c);
+    k_aev_fwd<1, BF16, false><<<grid, kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
+                                                        row_mask, wave_atom, status, N, c);
 }
 
 void launch_aev_fwd(const float4 *pos, const int *sys_of, const SysDesc *sys, const int2 *nbr,
                     const int *nbr_cnt, int cap, const int *row_of_atom, void *G, bool g_bf16,
                     int ldg, Live N, const AevConst &c, unsigned long long *row_mask, const int *wave_atom,
-                    int *status, int wpb_pref, hipStream_t st) {
+                    int *status, int wpb_pref, size_t max_lds, hipStream_t st) {
   if (N.v <= 0) return;
   if (g_bf16)
     aev_fwd_t<true>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg, row_mask, wave_atom, status, N, c,
-                    wpb_pref, st);
+                    wpb_pref, max_lds, st);
   else
     aev_fwd_t<false>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg, row_mask, wave_atom, status, N, c,
-                     wpb_pref, st);
+                     wpb_pref, max_lds, st);
 }
 
 template <int WPB>
@@ -1086,8 +1259,15 @@ static void aev_bwd_launch(int form, size_t lds, unsigned grid, const AevBwdGrou
       return;
     }
   }
+  if constexpr (WPB == kGroupWaves) {
+    if (form == 3) {
+      k_aev_bwd<WPB, true><<<grid, WPB * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg,
+                                                           N, c, Ffix, W_atom, gp.wave_atom);
+      return;
+    }
+  }
   if constexpr (WPB <= 4)
-    k_aev_bwd<WPB><<<grid, WPB * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg, N, c,
+    k_aev_bwd<WPB, false><<<grid, WPB * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg, N, c,
                                                    Ffix, W_atom, gp.wave_atom);
 }
 
@@ -1105,6 +1285,11 @@ void launch_aev_bwd(const float4 *pos, const int *sys_of, const SysDesc *sys, co
                     int wpb_pref, size_t max_lds, hipStream_t st) {
   if (N.v <= 0) return;
   const size_t per = wave_lds_bytes<true>(cap);
+  if (group_centres(N.v, nbr != nullptr, per, max_lds)) {
+    aev_bwd_launch<kGroupWaves>(3, per, (unsigned)N.v, gp, pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg,
+                                N, c, Ffix, W_atom, st);
+    return;
+  }
   int form = 0;
   size_t table = 0;
   if (wpb_pref >= 4) {

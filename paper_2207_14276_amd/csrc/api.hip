@@ -1130,6 +1130,10 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
   int max_n = 0;
   for (int s = 0; s < n_sys; ++s) max_n = std::max(max_n, sd[s].n);
   const bool direct = all_small && !nl && m->kind == kDescAev && mode != kNbr && max_n - 1 <= cap;
+  // entries the AEV kernels' lists in LDS must hold: without a list, the
+  // largest system's other atoms (the capacity may be far above them, and the
+  // LDS decides how many waves a compute unit runs)
+  const int lds_cap = direct ? std::min(cap, std::max(4, (max_n - 1 + 3) / 4 * 4)) : cap;
   // centre groups of the AEV backward's per-system form: consecutive centres
   // of one system, the systems in order of decreasing size (the costliest
   // groups start first)
@@ -1341,9 +1345,9 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
         launch_dp_fwd(pos, coords, pool_state, m->sys_of.as<int>(), dsys, pool_nbr, pool_cnt, cap,
                       m->row_of_atom.as<int>(), Gp, g_bf16, ldg, N, m->dp, rec, wpb, st);
       else
-        launch_aev_fwd(pos, m->sys_of.as<int>(), dsys, direct ? nullptr : pool_nbr, pool_cnt, cap,
+        launch_aev_fwd(pos, m->sys_of.as<int>(), dsys, direct ? nullptr : pool_nbr, pool_cnt, lds_cap,
                        m->row_of_atom.as<int>(), Gp, g_bf16, ldg, lN, m->aev, tm, wave_atom,
-                       direct ? status : nullptr, wpb, st);
+                       direct ? status : nullptr, wpb, m->max_lds, st);
     };
     if (mode == kAev) {
       descriptor(m->dG.p, false, D, nullptr, nullptr, 0);
@@ -1525,7 +1529,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
           gp.n_cells = (int)C_l;
           if (graph) gp.live_cells = &live->n_cells;
         }
-        launch_aev_bwd(pos, m->sys_of.as<int>(), dsys, direct ? nullptr : pool_nbr, pool_cnt, cap,
+        launch_aev_bwd(pos, m->sys_of.as<int>(), dsys, direct ? nullptr : pool_nbr, pool_cnt, lds_cap,
                        m->row_of_atom.as<int>(), m->dG.as<float>(), D, lN, m->aev, Ffix,
                        m->W_atom.as<float>(), gp, m->tune_val[kSiteAevBwd], m->max_lds, st);
       }
