@@ -791,7 +791,7 @@ struct SinkHash {
 // barrier, so waves of one workgroup may work on different centres) or by the
 // W waves of a workgroup (see k_aev_fwd), which share the lists: dE/dd of every
 // radial entry from the radial and angular terms, the centre's virial row
-// W_atom[i] = -sum d (x) dE/dd, and its force contributions through sink:
+// W_atom[i] = -sum d (x) dE/dd (where asked for), and its force contributions through sink:
 // -dE/dd onto each neighbour, the sum of dE/dd onto the centre.
 template <int W, class Sink>
 __device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__restrict__ pos, const int *__restrict__ sys_of,
@@ -803,7 +803,7 @@ __device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__res
   // virial share is zero
   const int r_i = row_of_atom[i];
   if (r_i < 0) {
-    if (lane < 9 && wave == 0) W_atom[(size_t)9 * i + lane] = 0.f;
+    if (W_atom && lane < 9 && wave == 0) W_atom[(size_t)9 * i + lane] = 0.f;
     return;
   }
   const SysDesc &d = sys[sys_of[i]];
@@ -1045,6 +1045,7 @@ __device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__res
       const float gx = (float)w.rG[3 * e], gy = (float)w.rG[3 * e + 1], gz = (float)w.rG[3 * e + 2];
       if (W == 1) sink.add(w.rJ[e], -to_fix(gx), -to_fix(gy), -to_fix(gz));
       fi0 += gx; fi1 += gy; fi2 += gz;
+      if (!W_atom) continue;
       vir[0] -= dv.x * gx; vir[1] -= dv.x * gy; vir[2] -= dv.x * gz;
       vir[3] -= dv.y * gx; vir[4] -= dv.y * gy; vir[5] -= dv.y * gz;
       vir[6] -= dv.z * gx; vir[7] -= dv.z * gy; vir[8] -= dv.z * gz;
@@ -1052,10 +1053,12 @@ __device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__res
     fi0 = wave_sum(fi0);
     fi1 = wave_sum(fi1);
     fi2 = wave_sum(fi2);
+    if (W_atom) {
 #pragma unroll
-    for (int q = 0; q < 9; ++q) vir[q] = wave_sum(vir[q]);
+      for (int q = 0; q < 9; ++q) vir[q] = wave_sum(vir[q]);
+    }
     if (lane == 0) sink.add(i, to_fix(fi0), to_fix(fi1), to_fix(fi2));
-    if (lane < 9) {
+    if (W_atom && lane < 9) {
       float v = vir[0];
 #pragma unroll
       for (int q = 1; q < 9; ++q) v = lane == q ? vir[q] : v;

@@ -1338,6 +1338,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     const bool bf16 = m->precision == NNP_BF16;
     const bool dp = m->kind == kDescDp;
     const bool want_grad = o.forces != nullptr;
+    float *W_atom = o.virial ? m->W_atom.as<float>() : nullptr;  // per-centre virials, where asked for
     // descriptor forward into rows of G (the AEV export: float32 rows of the
     // dE/dG buffer, gathered back to atom order)
     auto descriptor = [&](void *Gp, bool g_bf16, int ldg, float4 *rec, unsigned long long *tm, int wpb) {
@@ -1514,7 +1515,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
         const bool cells = !pairs && !all_small;
         launch_dp_bwd(dsys, n_sys, all_small, cells ? m->cell_start.as<int>() : nullptr,
                       m->cell_atoms.as<int>(), (int)C, m->row_of_atom.as<int>(), m->dG.as<float>(), D, N, m->dp,
-                      m->dp_rec.as<float4>(), o.forces, m->W_atom.as<float>(), m->tune_val[kSiteAevBwd], st);
+                      m->dp_rec.as<float4>(), o.forces, W_atom, m->tune_val[kSiteAevBwd], st);
       } else {
         AevBwdGroups gp;
         gp.wave_atom = wave_atom;
@@ -1531,14 +1532,14 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
         }
         launch_aev_bwd(pos, m->sys_of.as<int>(), dsys, direct ? nullptr : pool_nbr, pool_cnt, lds_cap,
                        m->row_of_atom.as<int>(), m->dG.as<float>(), D, lN, m->aev, Ffix,
-                       m->W_atom.as<float>(), gp, m->tune_val[kSiteAevBwd], m->max_lds, st);
+                       W_atom, gp, m->tune_val[kSiteAevBwd], m->max_lds, st);
       }
       site_end(kSiteAevBwd);
     }
     mark();
-    launch_reduce(e_atom, want_grad ? m->W_atom.as<float>() : nullptr, dsys, lS,
+    launch_reduce(e_atom, W_atom, dsys, lS,
                   d_chunk_sys, d_chunk_begin, lChunks, d_sys_chunk_off,
-                  !graph && one_chunk_each && n_chunks == n_sys,
+                  !graph && one_chunk_each && n_chunks == n_sys, !graph && max_n <= 256,
                   m->partial.as<double>(), o.energy, o.virial, Ffix, o.forces, st);
     mark();
     if (ev) m->last_stages = stage - 1;

@@ -317,7 +317,7 @@ k_dp_fwd(const float4 *__restrict__ pos, const float *__restrict__ coords,
 }
 
 // Backward of centre i (one wavefront, row r of dE/dG): the explicit terms
-// of its slots, the frame terms, and its virial share.  add(j, x, y, z) takes
+// of its slots, the frame terms, and (W_atom) its virial share.  add(j, x, y, z) takes
 // a contribution to the force on atom j; every lane may call it.
 template <class Add>
 __device__ inline void dp_centre_bwd(int i, int lane, int r, const float *__restrict__ dG, int ldg,
@@ -357,11 +357,13 @@ __device__ inline void dp_centre_bwd(int i, int lane, int r, const float *__rest
       fi[a] += gd[a];
     }
     add(j, -gd[0], -gd[1], -gd[2]);
+    if (!W_atom) continue;
     for (int a = 0; a < 3; ++a)
       for (int b = 0; b < 3; ++b) vir[3 * a + b] -= dvv[a] * gd[b];
   }
   for (int q = 0; q < 9; ++q) A[q] = wave_sum(A[q]);
-  for (int q = 0; q < 9; ++q) vir[q] = wave_sum(vir[q]);
+  if (W_atom)
+    for (int q = 0; q < 9; ++q) vir[q] = wave_sum(vir[q]);
   for (int a = 0; a < 3; ++a) fi[a] = wave_sum(fi[a]);
 
   // frame terms: e_x = d_a/|d_a|, e_y = u/|u| with u = (I - e_x e_x^T) d_b,
@@ -403,7 +405,7 @@ __device__ inline void dp_centre_bwd(int i, int lane, int r, const float *__rest
     if (lane == 1 && f.nu > 0.f) add(jb, -gb[0], -gb[1], -gb[2]);
   }
   if (lane == 2) add(i, fi[0], fi[1], fi[2]);
-  if (lane < 9) {
+  if (W_atom && lane < 9) {
     float v = vir[0];
     for (int q = 1; q < 9; ++q) v = lane == q ? vir[q] : v;
     W_atom[(size_t)9 * i + lane] = v;
@@ -420,7 +422,7 @@ k_dp_bwd(const int *__restrict__ row_of_atom, const float *__restrict__ dG, int 
   if (i >= N) return;
   const int r = row_of_atom[i];
   if (r < 0) {  // outside a caller's mask: no energy, no virial share
-    if (lane < 9) W_atom[(size_t)9 * i + lane] = 0.f;
+    if (W_atom && lane < 9) W_atom[(size_t)9 * i + lane] = 0.f;
     return;
   }
   dp_centre_bwd(i, lane, r, dG, ldg, c, rec, W_atom, [&](int j, float x, float y, float z) {
@@ -449,7 +451,7 @@ k_dp_bwd_sys(const SysDesc *__restrict__ sys, const int *__restrict__ row_of_ato
     const int i = a0 + il;
     const int r = row_of_atom[i];
     if (r < 0) {
-      if (lane < 9) W_atom[(size_t)9 * i + lane] = 0.f;
+      if (W_atom && lane < 9) W_atom[(size_t)9 * i + lane] = 0.f;
       continue;
     }
     dp_centre_bwd(i, lane, r, dG, ldg, c, rec, W_atom, [&](int j, float x, float y, float z) {
@@ -524,7 +526,7 @@ k_dp_bwd_cells(const int *__restrict__ cell_start, const int *__restrict__ cell_
     const int i = cell_atoms[p];
     const int r = row_of_atom[i];
     if (r < 0) {
-      if (lane < 9) W_atom[(size_t)9 * i + lane] = 0.f;
+      if (W_atom && lane < 9) W_atom[(size_t)9 * i + lane] = 0.f;
       continue;
     }
     dp_centre_bwd(i, lane, r, dG, ldg, c, rec, W_atom, [&](int j, float x, float y, float z) {

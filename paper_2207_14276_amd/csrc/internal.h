@@ -317,6 +317,7 @@ struct AevBwdGroups {
   const int *wave_atom = nullptr;  // one wave per centre: the centre of wave w (nullable: w)
 };
 // Forces go into Ffix [N][3] (64-bit fixed point, cleared by the caller).
+// W_atom nullable: no virial.
 // nbr null: no neighbour list (as for launch_aev_fwd).
 void launch_aev_bwd(const float4 *pos, const int *sys_of, const SysDesc *sys, const int2 *nbr,
                     const int *nbr_cnt, int cap, const int *row_of_atom, const float *dG,
@@ -347,9 +348,10 @@ void launch_fill(float *p, size_t n, float v, hipStream_t st);
 void launch_fill_i32(int *p, size_t n, int v, hipStream_t st);
 // Ffix (nullable): fixed-point forces, converted into F [N][3] float32 here.
 // direct: chunk s is system s for every system (one pass, no partials).
+// small: no system has more than 256 atoms.
 void launch_reduce(const float *e_atom, const float *W_atom, const SysDesc *sys, Live n_sys,
                    const int *chunk_sys, const int *chunk_begin, Live n_chunks,
-                   const int *sys_chunk_off, bool direct, double *partial, double *energy, double *virial,
+                   const int *sys_chunk_off, bool direct, bool small, double *partial, double *energy, double *virial,
                    const unsigned long long *Ffix, float *F, hipStream_t st);
 void launch_gather_rows(const float *src, int ld, const int *row_of_atom, int N, int D,
                         float *dst, hipStream_t st);
