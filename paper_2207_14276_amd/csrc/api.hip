@@ -654,7 +654,7 @@ static int64_t bucket_up(int64_t v) {
 // with: the launch sizes, the call's form and every address a kernel takes.
 struct GraphKey {
   int64_t n_launch, s_launch, c_launch, g_launch;
-  int all_small, cap;
+  int form, cap;  // form: all systems small, prepared by a workgroup each
   const void *ptr[12];
   unsigned long long ws_gen;
   bool operator==(const GraphKey &o) const { return memcmp(this, &o, sizeof o) == 0; }
@@ -935,7 +935,7 @@ struct PairIn {
 // recently used graph makes room when the cache is full.
 template <class Record>
 static int replay(nnp_model *m, GraphRun *gr, hipStream_t st, int64_t n_l, int64_t s_l, int64_t c_l,
-                  int64_t g_l, bool all_small, int cap, std::initializer_list<const void *> ptrs,
+                  int64_t g_l, int form, int cap, std::initializer_list<const void *> ptrs,
                   Record &&record) {
   GraphCache *gc = gr->cache;
   if (!gc || !gr->capture_stream) return fail(NNP_EINVAL, "graph replay needs a cache and a capture stream");
@@ -945,7 +945,7 @@ static int replay(nnp_model *m, GraphRun *gr, hipStream_t st, int64_t n_l, int64
   k.s_launch = s_l;
   k.c_launch = c_l;
   k.g_launch = g_l;
-  k.all_small = all_small ? 1 : 0;
+  k.form = form;
   k.cap = cap;
   int q = 0;
   for (const void *p : ptrs)
@@ -1159,6 +1159,14 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
   // the launch sizes are the call's.
   const bool graph = gr && gr->use_graph && m->kind == kDescAev && mode == kFull && nl && !pairs &&
                      !m->timing && !m->tuning && !o.no_alloc && N > 0;
+  // small calls: ingest, cells and buckets by one workgroup (per system).
+  // cells_bwd: the backward may group its centres by cells, also of systems
+  // that keep their lists (see launch_aev_bwd and launch_dp_bwd)
+  const bool prep_batch = all_small && !nl && N <= kPrepAtoms && n_sys <= kPrepSystems;  // (all_small: no pairs, N > 0)
+  bool prep_systems = !pairs && !all_small && N > 0 && max_n <= kPrepAtoms && n_sys <= kPrepSystems;
+  for (int s = 0; s < n_sys && prep_systems; ++s) prep_systems = sd[s].cell_cap <= kPrepCells;
+  const bool prep_one = prep_systems && n_sys == 1;  // its buckets too
+  const bool cells_bwd = mode == kFull && o.forces && (m->kind == kDescDp || m->tune_val[kSiteAevBwd] >= 4);
   int N_l = N, S_l = n_sys, chunks_l = n_chunks, groups_l = (int)groups.size();
   int64_t C_l = C;
   if (graph) {
@@ -1282,15 +1290,28 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     int2 *pool_nbr = nl ? nl->nbr.as<int2>() : m->nbr.as<int2>();
     int *pool_cnt = nl ? nl->cnt.as<int>() : m->nbr_cnt.as<int>();
     AtomState *pool_state = nl ? nl->state.as<AtomState>() : m->state.as<AtomState>();
-    if (nl) launch_skin_check(coords, dsys, lS, pool_state, 0.5f * nl->skin, nl->stats.as<int>(), st);
+    if (nl && !prep_systems)
+      launch_skin_check(coords, dsys, lS, pool_state, 0.5f * nl->skin, nl->stats.as<int>(), st);
     // AEV models accumulate forces in fixed point (converted by the reduction),
     // DeepPot-style models in float32 straight in the output
     const bool fix_forces = mode == kFull && o.forces && m->kind == kDescAev;
     unsigned long long *Ffix = fix_forces ? m->Ffix.as<unsigned long long>() : nullptr;
     // the launch order of the AEV kernels' centres, for calls of several systems
     int *wave_atom = m->kind == kDescAev && n_sys > 1 && !pairs ? m->wave_atom.as<int>() : nullptr;
-    launch_ingest(coords, species, pin.mask, dsys, lS, lN, m->S, pos, m->sys_of.as<int>(), pool_state,
-                  status, mode == kFull && !fix_forces ? o.forces : nullptr, Ffix, wave_atom, st);
+    float *zero_forces = mode == kFull && !fix_forces ? o.forces : nullptr;
+    if (prep_batch)
+      launch_prepare_batch(coords, species, dsys, n_sys, N, m->S, pos, m->sys_of.as<int>(), pool_state, status,
+                           zero_forces, Ffix, wave_atom, m->bucket_off.as<int>(), m->bucket_cnt.as<int>(),
+                           m->perm.as<int>(), m->row_of_atom.as<int>(), st);
+    else if (prep_systems)
+      launch_prepare_systems(coords, species, dsys, lS, m->S, nl ? 0.5f * nl->skin : -1.f, rc_list, cells_bwd,
+                             prep_one, pos, m->sys_of.as<int>(), pool_state, status,
+                             nl ? nl->stats.as<int>() : nullptr, zero_forces, Ffix, wave_atom,
+                             m->cell_start.as<int>(), m->cell_atoms.as<int>(), m->bucket_off.as<int>(),
+                             m->bucket_cnt.as<int>(), m->perm.as<int>(), m->row_of_atom.as<int>(), st);
+    else
+      launch_ingest(coords, species, pin.mask, dsys, lS, lN, m->S, pos, m->sys_of.as<int>(), pool_state,
+                    status, zero_forces, Ffix, wave_atom, st);
     mark();
     if (pairs) {
       // the caller's list replaces the cell search (stage "cells" stays empty)
@@ -1302,13 +1323,15 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
       if (!direct)
         launch_nbr_small(pos, m->sys_of.as<int>(), dsys, lN, rc_list, cap, pool_nbr, pool_cnt, status, st);
     } else {
-      launch_grid(dsys, lS, pos, m->cell_count.as<int>(), rc_list, st);
-      launch_cell_count(pos, m->sys_of.as<int>(), dsys, lN, m->cell_count.as<int>(), m->atom_cell.as<int>(),
-                        m->atom_slot.as<int>(), st);
-      launch_scan(m->cell_count.as<int>(), m->cell_start.as<int>(), lC, st);
-      launch_cell_scatter(m->atom_cell.as<int>(), m->atom_slot.as<int>(), m->cell_start.as<int>(), lN,
-                          m->cell_atoms.as<int>(), st);
-      launch_cell_sort(m->cell_start.as<int>(), lC, m->cell_atoms.as<int>(), st);
+      if (!prep_systems) {
+        launch_grid(dsys, lS, pos, m->cell_count.as<int>(), rc_list, st);
+        launch_cell_count(pos, m->sys_of.as<int>(), dsys, lN, m->cell_count.as<int>(), m->atom_cell.as<int>(),
+                          m->atom_slot.as<int>(), st);
+        launch_scan(m->cell_count.as<int>(), m->cell_start.as<int>(), lC, st);
+        launch_cell_scatter(m->atom_cell.as<int>(), m->atom_slot.as<int>(), m->cell_start.as<int>(), lN,
+                            m->cell_atoms.as<int>(), st);
+        launch_cell_sort(m->cell_start.as<int>(), lC, m->cell_atoms.as<int>(), st);
+      }
       mark();
       launch_nbr_build(pos, m->sys_of.as<int>(), dsys, lS, (int)C_l, m->cell_start.as<int>(),
                        m->cell_atoms.as<int>(), lN, rc_list, cap, pool_nbr, pool_cnt, status, st);
@@ -1322,8 +1345,9 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     mark();
     const int nblk = (N_l + 1023) / 1024;
     const int rows = (N_l + kTileM - 1) / kTileM * kTileM + m->S * kTileM;
-    launch_species_bucket(pos, wave_atom, lN, m->S, m->block_counts.as<int>(), nblk, m->bucket_off.as<int>(),
-                          m->bucket_cnt.as<int>(), m->perm.as<int>(), m->row_of_atom.as<int>(), rows, st);
+    if (!prep_batch && !prep_one)
+      launch_species_bucket(pos, wave_atom, lN, m->S, m->block_counts.as<int>(), nblk, m->bucket_off.as<int>(),
+                            m->bucket_cnt.as<int>(), m->perm.as<int>(), m->row_of_atom.as<int>(), rows, st);
     // AEV models: the forward records per row the column halves it may have
     // non-zero, and the first layer and the dE/dG product skip what no row
     // of a tile has
@@ -1555,7 +1579,8 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     if (nl) record_builds();
     return NNP_OK;
   }
-  const int rc_replay = replay(m, gr, st, N_l, S_l, C_l, groups_l, all_small, cap,
+  const int form = (all_small ? 1 : 0) | (prep_systems ? 2 : 0) | (prep_one ? 4 : 0);
+  const int rc_replay = replay(m, gr, st, N_l, S_l, C_l, groups_l, form, cap,
                 {coords, species, o.energy, o.forces, o.virial, o.atom_energy, nl, (const void *)gr->pre,
                  (const void *)gr->post, gr->ctx, m->desc.p, nullptr},
                 [&](hipStream_t cs) -> int {

@@ -257,6 +257,22 @@ void launch_ingest(const float *coords, const int *species, const unsigned char 
                    const SysDesc *sys, Live n_sys, Live N, int S, float4 *pos, int *sys_of,
                    AtomState *state, int *status, float *zero_forces, unsigned long long *zero_fix,
                    int *wave_atom, hipStream_t st);
+// Small calls: one workgroup does several of the steps below (nbr.hip).
+constexpr int kPrepAtoms = 4096;    // atoms of the call, or of a system
+constexpr int kPrepCells = 4096;    // reserved cells of a system
+constexpr int kPrepSystems = 1024;  // systems of a batch
+void launch_prepare_batch(const float *coords, const int *species, const SysDesc *sys, int n_sys, int N, int S,
+                          float4 *pos, int *sys_of, AtomState *state, int *status, float *zero_forces,
+                          unsigned long long *zero_fix, int *wave_atom, int *bucket_off, int *bucket_cnt, int *perm,
+                          int *row_of_atom, hipStream_t st);
+// half_skin < 0: no pool (no skin check).  all_cells: cells of every system,
+// not only of those whose list is built.  buckets: one system, its species
+// buckets too.
+void launch_prepare_systems(const float *coords, const int *species, SysDesc *sys, Live n_sys, int S, float half_skin,
+                            float rc_list, bool all_cells, bool buckets, float4 *pos, int *sys_of, AtomState *state,
+                            int *status, int *stats, float *zero_forces, unsigned long long *zero_fix,
+                            int *wave_atom, int *cell_start, int *cell_atoms, int *bucket_off, int *bucket_cnt,
+                            int *perm, int *row_of_atom, hipStream_t st);
 constexpr int kSmallSystem = 512;   // largest non-periodic system of the small-system search
 void launch_nbr_small(const float4 *pos, const int *sys_of, const SysDesc *sys, Live N, float rc_list,
                       int cap, int2 *nbr, int *nbr_cnt, int *status, hipStream_t st);

@@ -12,6 +12,57 @@ namespace nnp {
 // so neighbour vectors stay consistent with the stored lattice images.
 constexpr int kIngestLdsSystems = 1024;  // more systems: staging costs more than it saves
 
+// The record of atom i of system d (the state of its list is updated).
+__device__ inline float4 ingest_atom(int i, const SysDesc &d, int rebuild, const float *__restrict__ coords,
+                                     const int *__restrict__ species, const unsigned char *__restrict__ mask, int S,
+                                     AtomState *__restrict__ state, int *__restrict__ status) {
+  const float cx = coords[3 * i], cy = coords[3 * i + 1], cz = coords[3 * i + 2];
+  float x = cx, y = cy, z = cz;
+  AtomState &a = state[d.state_off + (i - d.atom_off)];
+  if (d.periodic) {
+    float wx, wy, wz;
+    if (rebuild) {
+      wx = floorf(cx / d.L[0]); wy = floorf(cy / d.L[1]); wz = floorf(cz / d.L[2]);
+    } else {
+      const float4 w = a.wrap;
+      wx = w.x; wy = w.y; wz = w.z;
+    }
+    x = cx - wx * d.L[0];
+    y = cy - wy * d.L[1];
+    z = cz - wz * d.L[2];
+    if (rebuild) {
+      // rounding can land exactly on L: fold into the cell grid's range
+      if (x >= d.L[0]) { x -= d.L[0]; wx += 1.f; }
+      if (y >= d.L[1]) { y -= d.L[1]; wy += 1.f; }
+      if (z >= d.L[2]) { z -= d.L[2]; wz += 1.f; }
+      a.wrap = make_float4(wx, wy, wz, 0.f);
+    }
+  }
+  if (rebuild) a.ref = make_float4(cx, cy, cz, 0.f);
+  int s = species[i];
+  if (s < 0 || s >= S) {
+    atomicOr(status, kStatBadSpecies);
+    s = 0;
+  }
+  // an atom outside the caller's mask has no network (species slot -1)
+  if (mask && !mask[i]) s = -1;
+  return make_float4(x, y, z, __int_as_float(s));
+}
+
+// The force output of atom i starts from zero (the backward accumulates into it).
+__device__ inline void clear_forces(int i, float *__restrict__ zero_forces, unsigned long long *__restrict__ zero_fix) {
+  if (zero_forces) {
+    zero_forces[3 * (size_t)i] = 0.f;
+    zero_forces[3 * (size_t)i + 1] = 0.f;
+    zero_forces[3 * (size_t)i + 2] = 0.f;
+  }
+  if (zero_fix) {
+    zero_fix[3 * (size_t)i] = 0ull;
+    zero_fix[3 * (size_t)i + 1] = 0ull;
+    zero_fix[3 * (size_t)i + 2] = 0ull;
+  }
+}
+
 __global__ void k_ingest(const float *__restrict__ coords, const int *__restrict__ species,
                          const unsigned char *__restrict__ mask,
                          const SysDesc *__restrict__ sys, Live n_sys_, Live N_, int S,
@@ -30,17 +81,7 @@ __global__ void k_ingest(const float *__restrict__ coords, const int *__restrict
   }
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
-  // the force output starts from zero (the backward accumulates into it)
-  if (zero_forces) {
-    zero_forces[3 * (size_t)i] = 0.f;
-    zero_forces[3 * (size_t)i + 1] = 0.f;
-    zero_forces[3 * (size_t)i + 2] = 0.f;
-  }
-  if (zero_fix) {
-    zero_fix[3 * (size_t)i] = 0ull;
-    zero_fix[3 * (size_t)i + 1] = 0ull;
-    zero_fix[3 * (size_t)i + 2] = 0ull;
-  }
+  clear_forces(i, zero_forces, zero_fix);
   auto first_atom = [&](int k) { return staged ? s_off[k] : sys[k].atom_off; };
   // system of atom i: last s with atom_off <= i (binary search)
   int lo = 0, hi = n_sys - 1;
@@ -52,37 +93,7 @@ __global__ void k_ingest(const float *__restrict__ coords, const int *__restrict
   while (lo + 1 < n_sys && first_atom(lo + 1) <= i) ++lo;
   const SysDesc &d = sys[lo];
   if (wave_atom) wave_atom[d.order_off + (i - d.atom_off)] = i;
-  const float cx = coords[3 * i], cy = coords[3 * i + 1], cz = coords[3 * i + 2];
-  float x = cx, y = cy, z = cz;
-  AtomState &a = state[d.state_off + (i - d.atom_off)];
-  if (d.periodic) {
-    float wx, wy, wz;
-    if (d.rebuild) {
-      wx = floorf(cx / d.L[0]); wy = floorf(cy / d.L[1]); wz = floorf(cz / d.L[2]);
-    } else {
-      const float4 w = a.wrap;
-      wx = w.x; wy = w.y; wz = w.z;
-    }
-    x = cx - wx * d.L[0];
-    y = cy - wy * d.L[1];
-    z = cz - wz * d.L[2];
-    if (d.rebuild) {
-      // rounding can land exactly on L: fold into the cell grid's range
-      if (x >= d.L[0]) { x -= d.L[0]; wx += 1.f; }
-      if (y >= d.L[1]) { y -= d.L[1]; wy += 1.f; }
-      if (z >= d.L[2]) { z -= d.L[2]; wz += 1.f; }
-      a.wrap = make_float4(wx, wy, wz, 0.f);
-    }
-  }
-  if (d.rebuild) a.ref = make_float4(cx, cy, cz, 0.f);
-  int s = species[i];
-  if (s < 0 || s >= S) {
-    atomicOr(status, kStatBadSpecies);
-    s = 0;
-  }
-  // an atom outside the caller's mask has no network (species slot -1)
-  if (mask && !mask[i]) s = -1;
-  pos[i] = make_float4(x, y, z, __int_as_float(s));
+  pos[i] = ingest_atom(i, d, d.rebuild, coords, species, mask, S, state, status);
   sys_of[i] = lo;
 }
 
@@ -130,6 +141,31 @@ void launch_skin_check(const float *coords, SysDesc *sys, Live n_sys, const Atom
 }
 
 // -------------------------------------------------------------- cell grids
+// The grid of a non-periodic system from its bounding box.
+__device__ inline void fit_grid(SysDesc &d, float (&mn)[3], float (&mx)[3], float rc_list) {
+  const float rc = rc_list * (1.0f + 1e-5f);
+  int nc[3];
+  float ext[3];
+  for (int k = 0; k < 3; ++k) {
+    if (d.n == 0) { mn[k] = 0.f; mx[k] = 0.f; }
+    ext[k] = fmaxf(mx[k] - mn[k], 0.f);
+    nc[k] = max(1, (int)floorf(ext[k] / rc));
+    nc[k] = min(nc[k], 1024);
+  }
+  // keep the product within the reserved cells: widen the largest axis' cells
+  while ((long long)nc[0] * nc[1] * nc[2] > d.cell_cap) {
+    int k = (nc[0] >= nc[1] && nc[0] >= nc[2]) ? 0 : (nc[1] >= nc[2] ? 1 : 2);
+    nc[k] = max(1, nc[k] - 1);
+  }
+  for (int k = 0; k < 3; ++k) {
+    d.origin[k] = mn[k];
+    d.nc[k] = nc[k];
+    d.edge[k] = nc[k] > 1 ? ext[k] / nc[k] : fmaxf(ext[k], rc);
+    // guard the edge so floor((x - origin) / edge) of the max lands in-grid
+    d.edge[k] = fmaxf(d.edge[k], rc);
+  }
+}
+
 // One wave per system.  Periodic: the host already set nc/edge.  Non-periodic:
 // cells of edge >= rc_list over the bounding box, at most cell_cap cells.
 // Also clears the system's cell counters.
@@ -153,27 +189,7 @@ __global__ void k_grid(SysDesc *__restrict__ sys, Live n_sys, const float4 *__re
         mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], off));
       }
     if (lane == 0) {
-      const float rc = rc_list * (1.0f + 1e-5f);
-      int nc[3];
-      float ext[3];
-      for (int k = 0; k < 3; ++k) {
-        if (d.n == 0) { mn[k] = 0.f; mx[k] = 0.f; }
-        ext[k] = fmaxf(mx[k] - mn[k], 0.f);
-        nc[k] = max(1, (int)floorf(ext[k] / rc));
-        nc[k] = min(nc[k], 1024);
-      }
-      // keep the product within the reserved cells: widen the largest axis' cells
-      while ((long long)nc[0] * nc[1] * nc[2] > d.cell_cap) {
-        int k = (nc[0] >= nc[1] && nc[0] >= nc[2]) ? 0 : (nc[1] >= nc[2] ? 1 : 2);
-        nc[k] = max(1, nc[k] - 1);
-      }
-      for (int k = 0; k < 3; ++k) {
-        d.origin[k] = mn[k];
-        d.nc[k] = nc[k];
-        d.edge[k] = nc[k] > 1 ? ext[k] / nc[k] : fmaxf(ext[k], rc);
-        // guard the edge so floor((x - origin) / edge) of the max lands in-grid
-        d.edge[k] = fmaxf(d.edge[k], rc);
-      }
+      fit_grid(d, mn, mx, rc_list);
       sys[s] = d;
     }
   }
@@ -765,10 +781,335 @@ k_species_place(const float4 *__restrict__ pos, const int *__restrict__ wave_ato
   }
 }
 
+// ---------------------------------------------------------- small preparations
+// The steps above are each a launch of a few microseconds whose work is less;
+// for small calls one workgroup of 1,024 threads does several of them in a
+// row, with at most kPrepAtoms atoms in its registers and LDS.  Its latency
+// bounds it (5 us for a few atoms, 12 us for 2,001 with their cells, 30 us for
+// 6,000), against 4.5 us for each launch that it replaces (nine for a system
+// whose list is built), so the line lies at 4,096 atoms: a call on 2,001 went
+// from 122 to 111 us, 24 kept lists of 13,500 atoms in all from 722 to 654,
+// 24 atoms from 85 to 78, and one on 6,006 took 282 this way against 278.
+constexpr int kPrepThreads = 1024, kPrepEach = kPrepAtoms / kPrepThreads;
+static_assert(kPrepAtoms == kWave * kWave && kPrepThreads / kWave >= kMaxSpecies, "counts per 64 places: a wave's scan");
+
+// Species buckets (as k_species_place) of N <= kPrepAtoms atoms by one
+// workgroup: atom_at(p) and slot_at(p) give the atom in place p of the launch
+// order and its species slot.
+template <class AtomAt, class SlotAt>
+__device__ inline void bucket_one(int N, int S, int *__restrict__ bucket_off, int *__restrict__ bucket_cnt,
+                                  int *__restrict__ perm, int *__restrict__ row_of_atom, AtomAt &&atom_at,
+                                  SlotAt &&slot_at) {
+  __shared__ int cnt[kPrepEach][kPrepThreads / kWave][8];  // per 64 places: species counts, then first rows
+  __shared__ int tot[8], off[8 + 1];
+  const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
+  int slot[kPrepEach], rank[kPrepEach];
+#pragma unroll
+  for (int k = 0; k < kPrepEach; ++k) {
+    const int p = k * kPrepThreads + t;
+    slot[k] = p < N ? slot_at(p) : -1;
+    rank[k] = 0;
+    int v = 0;
+#pragma unroll
+    for (int q = 0; q < kMaxSpecies; ++q) {
+      const unsigned long long m = __ballot(slot[k] == q);
+      if (slot[k] == q)
+        rank[k] = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+      v = lane == q ? __popcll(m) : v;
+    }
+    if (lane < 8) cnt[k][w][lane] = v;
+  }
+  __syncthreads();
+  // a wave per species: the places' counts become first rows in the bucket
+  if (w < kMaxSpecies) {
+    int &c = cnt[lane / (kPrepThreads / kWave)][lane % (kPrepThreads / kWave)][w];
+    const int v = c;
+    int x = v;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    c = x - v;
+    if (lane == kWave - 1) tot[w] = x;
+  }
+  __syncthreads();
+  if (t == 0) {
+    int o = 0;
+#pragma unroll
+    for (int q = 0; q < kMaxSpecies; ++q) {
+      if (q > S) break;
+      off[q] = o;
+      o += (tot[q] + kTileM - 1) / kTileM * kTileM;
+    }
+    off[S] = o;
+  }
+  __syncthreads();
+  if (t <= S) bucket_off[t] = off[t];
+  if (t < S) bucket_cnt[t] = tot[t];
+  for (int q = 0; q < S; ++q)
+    for (int r = off[q] + tot[q] + t; r < off[q + 1]; r += kPrepThreads) perm[r] = -1;
+#pragma unroll
+  for (int k = 0; k < kPrepEach; ++k) {
+    const int p = k * kPrepThreads + t;
+    if (p >= N) break;
+    const int i = atom_at(p);
+    if (slot[k] >= 0) {
+      const int row = off[slot[k]] + cnt[k][w][slot[k]] + rank[k];
+      perm[row] = i;
+      row_of_atom[i] = row;
+    } else {
+      row_of_atom[i] = -1;   // no network row: the AEV kernels skip the atom
+    }
+  }
+}
+
+__global__ void __launch_bounds__(kPrepThreads)
+k_species_one(const float4 *__restrict__ pos, const int *__restrict__ wave_atom, Live N_, int S,
+              int *__restrict__ bucket_off, int *__restrict__ bucket_cnt, int *__restrict__ perm,
+              int *__restrict__ row_of_atom) {
+  auto atom_at = [&](int p) { return wave_atom ? wave_atom[p] : p; };
+  bucket_one(N_.get(), S, bucket_off, bucket_cnt, perm, row_of_atom, atom_at,
+             [&](int p) { return __float_as_int(pos[atom_at(p)].w); });
+}
+
+// Ingest and species buckets of a call of small systems without a box, by one
+// workgroup.
+__global__ void __launch_bounds__(kPrepThreads)
+k_prepare_batch(const float *__restrict__ coords, const int *__restrict__ species, const SysDesc *__restrict__ sys,
+                int n_sys, int N, int S, float4 *__restrict__ pos, int *__restrict__ sys_of,
+                AtomState *__restrict__ state, int *__restrict__ status, float *__restrict__ zero_forces,
+                unsigned long long *__restrict__ zero_fix, int *__restrict__ wave_atom, int *__restrict__ bucket_off,
+                int *__restrict__ bucket_cnt, int *__restrict__ perm, int *__restrict__ row_of_atom) {
+  __shared__ int first[kPrepSystems];
+  __shared__ int at[kPrepAtoms];  // place -> atom | species slot << 16
+  const int t = threadIdx.x;
+  for (int k = t; k < n_sys; k += kPrepThreads) first[k] = sys[k].atom_off;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPrepEach; ++k) {
+    const int i = k * kPrepThreads + t;
+    if (i >= N) break;
+    clear_forces(i, zero_forces, zero_fix);
+    // system of atom i: the last one that starts at or before it
+    int lo = 0, hi = n_sys - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (first[mid] <= i) lo = mid; else hi = mid - 1;
+    }
+    const SysDesc &d = sys[lo];
+    const float4 p = ingest_atom(i, d, d.rebuild, coords, species, nullptr, S, state, status);
+    pos[i] = p;
+    sys_of[i] = lo;
+    const int place = (wave_atom ? d.order_off : d.atom_off) + (i - d.atom_off);
+    if (wave_atom) wave_atom[place] = i;
+    at[place] = i | (__float_as_int(p.w) << 16);
+  }
+  __syncthreads();
+  bucket_one(N, S, bucket_off, bucket_cnt, perm, row_of_atom, [&](int p) { return at[p] & 0xffff; },
+             [&](int p) { return at[p] >> 16; });
+}
+
+// A workgroup per system: skin check (half_skin >= 0: lists in a pool), ingest,
+// and, for a system whose list is built in this call (or with all_cells), its
+// grid and its cells' atoms in index order; with a single system its species
+// buckets too.  cell_atoms of a system lie at its atoms' own places, so no scan
+// over the systems is needed.
+__global__ void __launch_bounds__(kPrepThreads)
+k_prepare_systems(const float *__restrict__ coords, const int *__restrict__ species, SysDesc *__restrict__ sys,
+                  Live n_sys_, int S, float half_skin, float rc_list, int all_cells, int buckets,
+                  float4 *__restrict__ pos, int *__restrict__ sys_of, AtomState *__restrict__ state,
+                  int *__restrict__ status, int *__restrict__ stats, float *__restrict__ zero_forces,
+                  unsigned long long *__restrict__ zero_fix, int *__restrict__ wave_atom,
+                  int *__restrict__ cell_start, int *__restrict__ cell_atoms, int *__restrict__ bucket_off,
+                  int *__restrict__ bucket_cnt, int *__restrict__ perm, int *__restrict__ row_of_atom) {
+  __shared__ int count[kPrepCells + 1];         // atoms per cell, then first places
+  __shared__ unsigned short member[kPrepAtoms]; // species slots by atom; then local atoms by cell, as they arrive
+  __shared__ SysDesc sd;
+  __shared__ float box[kPrepThreads / kWave][6];
+  __shared__ int wsum[kPrepThreads / kWave];
+  __shared__ int any;
+  const int s = blockIdx.x;
+  if (s >= n_sys_.get()) return;  // the whole workgroup
+  const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
+  if (t == 0) {
+    sd = sys[s];
+    any = 0;
+  }
+  __syncthreads();
+  const int n = sd.n, a0 = sd.atom_off;
+  int rebuild = sd.rebuild;
+  if (half_skin >= 0.f) {
+    // rebuilt once any atom has moved more than half the skin since the last
+    // build (then no pair can have entered the cutoff unseen)
+    if (!rebuild) {
+      bool far = false;
+      for (int k = t; k < n; k += kPrepThreads) {
+        const float4 r = state[sd.state_off + k].ref;
+        const float *c = coords + 3 * (size_t)(a0 + k);
+        const float dx = c[0] - r.x, dy = c[1] - r.y, dz = c[2] - r.z;
+        far = far || dx * dx + dy * dy + dz * dz > half_skin * half_skin;
+      }
+      if (far) any = 1;
+      __syncthreads();
+      rebuild = any;
+    }
+    if (t == 0) {
+      sys[s].rebuild = rebuild;
+      if (rebuild && n > 0) atomicAdd(stats, 1);
+    }
+  }
+  float4 p[kPrepEach];
+#pragma unroll
+  for (int k = 0; k < kPrepEach; ++k) {
+    const int l = k * kPrepThreads + t, i = a0 + l;
+    p[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (l < n) {
+      clear_forces(i, zero_forces, zero_fix);
+      p[k] = ingest_atom(i, sd, rebuild, coords, species, nullptr, S, state, status);
+      pos[i] = p[k];
+      sys_of[i] = s;
+      if (wave_atom) wave_atom[sd.order_off + l] = i;
+    }
+  }
+  if (buckets) {
+#pragma unroll
+    for (int k = 0; k < kPrepEach; ++k) {
+      const int l = k * kPrepThreads + t;
+      if (l < n) member[l] = (unsigned short)__float_as_int(p[k].w);
+    }
+    __syncthreads();
+    bucket_one(n, S, bucket_off, bucket_cnt, perm, row_of_atom, [&](int q) { return q; },
+               [&](int q) { return (int)(short)member[q]; });
+    __syncthreads();
+  }
+  if (!rebuild && !all_cells) return;
+
+  if (!sd.periodic) {
+    float mn[3] = {3.4e38f, 3.4e38f, 3.4e38f}, mx[3] = {-3.4e38f, -3.4e38f, -3.4e38f};
+#pragma unroll
+    for (int k = 0; k < kPrepEach; ++k) {
+      if (k * kPrepThreads + t >= n) break;
+      mn[0] = fminf(mn[0], p[k].x); mx[0] = fmaxf(mx[0], p[k].x);
+      mn[1] = fminf(mn[1], p[k].y); mx[1] = fmaxf(mx[1], p[k].y);
+      mn[2] = fminf(mn[2], p[k].z); mx[2] = fmaxf(mx[2], p[k].z);
+    }
+    for (int o = 32; o >= 1; o >>= 1)
+      for (int k = 0; k < 3; ++k) {
+        mn[k] = fminf(mn[k], __shfl_xor(mn[k], o));
+        mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], o));
+      }
+    if (lane == 0)
+      for (int k = 0; k < 3; ++k) {
+        box[w][k] = mn[k];
+        box[w][3 + k] = mx[k];
+      }
+    __syncthreads();
+    if (t == 0) {
+      for (int v = 0; v < kPrepThreads / kWave; ++v)
+        for (int k = 0; k < 3; ++k) {
+          mn[k] = fminf(mn[k], box[v][k]);
+          mx[k] = fmaxf(mx[k], box[v][3 + k]);
+        }
+      fit_grid(sd, mn, mx, rc_list);
+      for (int k = 0; k < 3; ++k) {
+        sys[s].origin[k] = sd.origin[k];
+        sys[s].nc[k] = sd.nc[k];
+        sys[s].edge[k] = sd.edge[k];
+      }
+    }
+  }
+  const int cells = sd.cell_cap;
+  for (int c = t; c < cells; c += kPrepThreads) count[c] = 0;
+  __syncthreads();
+  int cell[kPrepEach], place[kPrepEach];
+#pragma unroll
+  for (int k = 0; k < kPrepEach; ++k) {
+    cell[k] = 0;
+    place[k] = 0;
+    if (k * kPrepThreads + t >= n) continue;
+    const int cx = cell_coord(p[k].x, sd.origin[0], sd.edge[0], sd.nc[0]);
+    const int cy = cell_coord(p[k].y, sd.origin[1], sd.edge[1], sd.nc[1]);
+    const int cz = cell_coord(p[k].z, sd.origin[2], sd.edge[2], sd.nc[2]);
+    cell[k] = (cx * sd.nc[1] + cy) * sd.nc[2] + cz;
+    place[k] = atomicAdd(&count[cell[k]], 1);
+  }
+  __syncthreads();
+  // exclusive scan of the counts: kPrepCells / 1024 consecutive cells per thread
+  constexpr int kEach = kPrepCells / kPrepThreads;
+  int c4[kEach], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kEach; ++k) {
+    const int c = t * kEach + k;
+    c4[k] = c < cells ? count[c] : 0;
+    sum += c4[k];
+  }
+  int x = sum;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == kWave - 1) wsum[w] = x;
+  __syncthreads();
+  int run = x - sum;
+  for (int v = 0; v < w; ++v) run += wsum[v];
+#pragma unroll
+  for (int k = 0; k < kEach; ++k) {
+    const int c = t * kEach + k;
+    if (c < cells) {
+      count[c] = run;
+      cell_start[sd.cell_off + c] = a0 + run;
+    }
+    run += c4[k];
+  }
+  if (t == 0) {
+    count[cells] = n;
+    cell_start[sd.cell_off + cells] = a0 + n;  // the next system's first place, or the end
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPrepEach; ++k)
+    if (k * kPrepThreads + t < n) member[count[cell[k]] + place[k]] = (unsigned short)(k * kPrepThreads + t);
+  __syncthreads();
+  // each atom's rank among its cell's
+#pragma unroll
+  for (int k = 0; k < kPrepEach; ++k) {
+    const int l = k * kPrepThreads + t;
+    if (l >= n) continue;
+    const int b = count[cell[k]], e = count[cell[k] + 1];
+    int rank = 0;
+    for (int q = b; q < e; ++q) rank += (int)member[q] < l;
+    cell_atoms[a0 + b + rank] = a0 + l;
+  }
+}
+
+void launch_prepare_batch(const float *coords, const int *species, const SysDesc *sys, int n_sys, int N, int S,
+                          float4 *pos, int *sys_of, AtomState *state, int *status, float *zero_forces,
+                          unsigned long long *zero_fix, int *wave_atom, int *bucket_off, int *bucket_cnt, int *perm,
+                          int *row_of_atom, hipStream_t st) {
+  k_prepare_batch<<<1, kPrepThreads, 0, st>>>(coords, species, sys, n_sys, N, S, pos, sys_of, state, status,
+                                              zero_forces, zero_fix, wave_atom, bucket_off, bucket_cnt, perm,
+                                              row_of_atom);
+}
+
+void launch_prepare_systems(const float *coords, const int *species, SysDesc *sys, Live n_sys, int S, float half_skin,
+                            float rc_list, bool all_cells, bool buckets, float4 *pos, int *sys_of, AtomState *state,
+                            int *status, int *stats, float *zero_forces, unsigned long long *zero_fix,
+                            int *wave_atom, int *cell_start, int *cell_atoms, int *bucket_off, int *bucket_cnt,
+                            int *perm, int *row_of_atom, hipStream_t st) {
+  k_prepare_systems<<<n_sys.v, kPrepThreads, 0, st>>>(
+      coords, species, sys, n_sys, S, half_skin, rc_list, all_cells ? 1 : 0, buckets ? 1 : 0, pos, sys_of, state,
+      status, stats, zero_forces, zero_fix, wave_atom, cell_start, cell_atoms, bucket_off, bucket_cnt, perm,
+      row_of_atom);
+}
+
 void launch_species_bucket(const float4 *pos, const int *wave_atom, Live N, int S, int *block_counts,
                            int n_blocks, int *bucket_off, int *bucket_cnt, int *perm, int *row_of_atom,
                            int rows_cap, hipStream_t st) {
   (void)rows_cap;
+  if (N.v > 0 && N.v <= kPrepAtoms) {
+    k_species_one<<<1, kPrepThreads, 0, st>>>(pos, wave_atom, N, S, bucket_off, bucket_cnt, perm, row_of_atom);
+    return;
+  }
   // blocks past the live atoms (launches sized for more) count zeros
   if (N.v > 0) k_species_count<<<n_blocks, kBucketBlock, 0, st>>>(pos, wave_atom, N, S, block_counts);
   if (N.v > 0 && n_blocks <= kPlaceBlocks) {
