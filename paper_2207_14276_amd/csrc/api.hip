@@ -1115,8 +1115,9 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     std::vector<int> order(n_sys);
     for (int s = 0; s < n_sys; ++s) order[s] = s;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sd[a].n > sd[b].n; });
-    int next = 0;
+    int next = 0, place = 0;
     for (int s : order) {
+      sd[place++].by_size = s;
       sd[s].order_off = next;
       next += sd[s].n;
     }

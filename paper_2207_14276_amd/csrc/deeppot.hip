@@ -14,15 +14,14 @@
 // float32 neighbour vector of the packed atom records, as the AEV kernels do.
 //
 // Forward, one wavefront per centre:
-//   1. lane per list entry: per-species counts of the list by ballot (the
-//      buckets' capacities);
+//   1. lane per list entry: per-species counts of the list by LDS counters
+//      (the buckets' capacities);
 //   2. again lane per entry: the float64 R^2 and cutoff test, placement of
 //      the entries inside the cutoff into per-species buckets in LDS (key,
-//      tie, float32 vector, atom index);
-//   3. per species bucket, lane per entry: rank = number of bucket entries
-//      ahead of it (O(n_s^2 / 64) per lane, all lanes reading the same LDS
-//      word at a time); ranks below sel[s] claim a slot; ranks 0 and 1 are
-//      the species' frame candidates;
+//      tie, float32 vector, atom index), in any order;
+//   3. lane per bucket entry: rank = number of entries of its bucket ahead of
+//      it; ranks below sel[s] claim a slot; ranks 0 and 1 are the species'
+//      frame candidates;
 //   4. the two nearest among the candidates give the frame;
 //   5. lane per slot: four features, written as one 16-byte (8-byte in
 //      bfloat16) store, empty slots as zeros, and the slot's record
@@ -51,16 +50,22 @@ __device__ inline float4 slot_record(const float4 &d, int j) { return make_float
 
 // Per-wave LDS header.
 struct DpHead {
-  int cnt[8], off[8];                      // valid entries per species, bucket offsets
-  int fa, fb, pad0, pad1;                  // bucket positions of the frame neighbours (-1: none)
-  ulonglong2 cand[2 * kMaxSpecies + 2];    // each species' two nearest (key, tie)
-  int candv[2 * kMaxSpecies + 2];          // their bucket positions (-1: none)
+  int cnt[8], off[8], in[8];               // list entries per species, bucket offsets, entries inside the cutoff
+  int sel[8], soff[8];
+  double ckey[2 * kMaxSpecies];            // each species' two nearest (key: NaN if none)
+  unsigned long long ctie[2 * kMaxSpecies];
+  int candv[2 * kMaxSpecies];              // their bucket positions (-1: none)
+  int fa, fb;                              // bucket positions of the frame neighbours (-1: none)
 };
+static_assert(kMaxSpecies <= 8, "species tables");
 
+// Buckets start and end at multiples of four, so that keys are read four at a
+// time; unused places hold NaN.
+__host__ __device__ inline int dp_places(int cap) { return (cap + 3 * kMaxSpecies + 3) / 4 * 4; }
 __host__ __device__ inline size_t dp_head_bytes() { return (sizeof(DpHead) + 15) / 16 * 16; }
-// header, then per list entry: key/tie 16, vector 16, atom index 4; slot table
+// header, then per place: key 8, tie 8, vector 16, atom index 4; slot table
 __host__ __device__ inline size_t dp_lds_bytes(int cap, int n_slots) {
-  return dp_head_bytes() + (size_t)cap * (16 + 16 + 4) + ((size_t)n_slots * 4 + 15) / 16 * 16;
+  return dp_head_bytes() + (size_t)dp_places(cap) * (16 + 16 + 4) + ((size_t)n_slots * 4 + 15) / 16 * 16;
 }
 
 // Squared distance of the neighbour order, float64, no fused operations:
@@ -74,54 +79,33 @@ __device__ inline double dp_key(const float ci[3], const float *cj, int mx, int 
   return (dx * dx + dy * dy) + dz * dz;
 }
 
-// (key, tie) lexicographic order; R^2 >= 0, so its bits order like the value
-__device__ inline bool before(const ulonglong2 &a, const ulonglong2 &b) {
-  return a.x < b.x || (a.x == b.x && a.y < b.y);
+// (key, tie) lexicographic order
+__device__ inline bool before(double ka, unsigned long long ta, double kb, unsigned long long tb) {
+  return ka < kb || (ka == kb && ta < tb);
 }
 
-// One list entry of centre i: validity, species, order key and tie.
+// One list entry of centre i: the neighbour's record (w: its species slot, -1
+// for no entry or an atom outside the caller's mask).
 struct Entry {
   int2 en;
-  bool valid;
-  int sj;
-  ulonglong2 kt;
+  float4 pj;
 };
 
 __device__ inline Entry read_entry(int e, int n, const int2 *__restrict__ row, int j0, int n_sys,
-                                   const float4 *__restrict__ pos, const float *__restrict__ coords,
-                                   const AtomState *__restrict__ state, long long state_j0,
-                                   bool wrapped, const int wi[3], const float ci[3],
-                                   const double Ld[3], double rc2) {
+                                   const float4 *__restrict__ pos) {
   Entry r;
   r.en = make_int2(0, 0);
-  r.valid = false;
-  r.sj = -1;
-  r.kt = make_ulonglong2(~0ull, ~0ull);
+  r.pj = make_float4(0.f, 0.f, 0.f, __int_as_float(-1));
   if (e >= n) return r;
   r.en = row[e];
-  if ((unsigned)r.en.x >= (unsigned)n_sys) return r;
-  const int j = j0 + r.en.x;
-  r.sj = __float_as_int(pos[j].w);
-  if (r.sj < 0) return r;
-  int mx, my, mz;
-  unpack_image(r.en.y, mx, my, mz);
-  if (wrapped) {
-    // images refer to the wrapped records; shift them to the caller's frame
-    const float4 wj = state[state_j0 + r.en.x].wrap;
-    mx += wi[0] - (int)wj.x;
-    my += wi[1] - (int)wj.y;
-    mz += wi[2] - (int)wj.z;
-  }
-  const double key = dp_key(ci, coords + 3 * (size_t)j, mx, my, mz, Ld);
-  r.valid = key < rc2;
-  const unsigned img = ((unsigned)(mx + 512) & 1023u) << 20 | ((unsigned)(my + 512) & 1023u) << 10 |
-                       ((unsigned)(mz + 512) & 1023u);
-  r.kt = make_ulonglong2((unsigned long long)__double_as_longlong(key),
-                         (unsigned long long)(unsigned)r.en.x << 32 | img);
+  if ((unsigned)r.en.x < (unsigned)n_sys) r.pj = pos[j0 + r.en.x];
   return r;
 }
 
-// Local axes from the float32 vectors (and lengths) of a and b.
+// Local axes from the float32 vectors (and lengths) of a and b.  The fused
+// operations are written out: which of the products of a sum are fused is not
+// left to the compiler, whose choice changes with the code around it (a last
+// bit here can move a feature to the next bfloat16 value).
 struct Frame {
   float ex[3], ey[3], ez[3];
   float ra, nu;  // |d_a|; |u| (0: e_y, e_z undefined)
@@ -137,16 +121,16 @@ __device__ inline Frame make_frame(bool has_a, const float4 &da, bool has_b, con
   const float ia = 1.f / da.w;
   f.ex[0] = da.x * ia; f.ex[1] = da.y * ia; f.ex[2] = da.z * ia;
   if (!has_b) return f;
-  const float t = db.x * f.ex[0] + db.y * f.ex[1] + db.z * f.ex[2];
-  const float u0 = db.x - t * f.ex[0], u1 = db.y - t * f.ex[1], u2 = db.z - t * f.ex[2];
-  const float uu = u0 * u0 + u1 * u1 + u2 * u2;
-  if (!(uu > 1e-12f * (db.x * db.x + db.y * db.y + db.z * db.z))) return f;
+  const float t = fmaf(db.z, f.ex[2], fmaf(db.y, f.ex[1], db.x * f.ex[0]));
+  const float u0 = fmaf(-f.ex[0], t, db.x), u1 = fmaf(-f.ex[1], t, db.y), u2 = fmaf(-f.ex[2], t, db.z);
+  const float uu = fmaf(u2, u2, fmaf(u0, u0, u1 * u1));
+  if (!(uu > 1e-12f * fmaf(db.z, db.z, fmaf(db.y, db.y, db.x * db.x)))) return f;
   f.nu = sqrtf(uu);
   const float iu = 1.f / f.nu;
   f.ey[0] = u0 * iu; f.ey[1] = u1 * iu; f.ey[2] = u2 * iu;
-  f.ez[0] = f.ex[1] * f.ey[2] - f.ex[2] * f.ey[1];
-  f.ez[1] = f.ex[2] * f.ey[0] - f.ex[0] * f.ey[2];
-  f.ez[2] = f.ex[0] * f.ey[1] - f.ex[1] * f.ey[0];
+  f.ez[0] = fmaf(f.ex[1], f.ey[2], -(f.ex[2] * f.ey[1]));
+  f.ez[1] = fmaf(f.ex[2], f.ey[0], -(f.ex[0] * f.ey[2]));
+  f.ez[2] = fmaf(f.ex[0], f.ey[1], -(f.ex[1] * f.ey[0]));
   return f;
 }
 
@@ -167,6 +151,12 @@ template <> __device__ inline void store_slot<true>(void *row, int k, float4 f) 
 
 }  // namespace
 
+// Instruction issue bounds it (2,480 per centre of about 60 neighbours of seven
+// species in its first form: a third of them in the ranking, compares of 128
+// bits and their scalar logic, species by species; a third in ballots over the
+// species).  Hence counters in LDS, ranks by the float64 key alone, one compare
+// and one add per pair with every lane on its own bucket, and a second pass
+// over (key, tie) only where two keys are equal.
 template <int WPB, bool BF16>
 __global__ void __launch_bounds__(WPB * kWave)
 k_dp_fwd(const float4 *__restrict__ pos, const float *__restrict__ coords,
@@ -181,11 +171,13 @@ k_dp_fwd(const float4 *__restrict__ pos, const float *__restrict__ coords,
   const int r = row_of_atom[i];
   if (r < 0) return;  // outside a caller's mask: no network row
   char *base = (char *)lds4 + (size_t)wave * dp_lds_bytes(cap, c.n_slots);
+  const int places = dp_places(cap);
   DpHead *h = (DpHead *)base;
-  ulonglong2 *bkt = (ulonglong2 *)(base + dp_head_bytes());
-  float4 *bd = (float4 *)(bkt + cap);
-  int *bj = (int *)(bd + cap);
-  int *smap = bj + cap;
+  double *bkey = (double *)(base + dp_head_bytes());
+  unsigned long long *btie = (unsigned long long *)(bkey + places);
+  float4 *bd = (float4 *)(btie + places);
+  int *bj = (int *)(bd + places);
+  int *smap = bj + places;
 
   const SysDesc &d = sys[sys_of[i]];
   const int n = min(nbr_cnt[d.state_off + (i - d.atom_off)], cap);
@@ -203,92 +195,164 @@ k_dp_fwd(const float4 *__restrict__ pos, const float *__restrict__ coords,
   }
 
   // 1. list entries per species: bucket capacities (the cutoff test in step 2
-  //    may drop some; buckets then keep unused space at their ends)
-  int cnt[kMaxSpecies];
+  //    may drop some; buckets then keep unused space at their ends).  The first
+  //    entries stay in registers for step 2.
+  constexpr int kHold = 2;
+  const double nan = __longlong_as_double(-1ll);
+  Entry held[kHold];
 #pragma unroll
-  for (int s = 0; s < kMaxSpecies; ++s) cnt[s] = 0;
-  for (int b = 0; b < n; b += kWave) {
-    const int e = b + lane;
-    int sj = -1;
-    if (e < n) {
-      const int2 en = row[e];
-      if ((unsigned)en.x < (unsigned)n_sys) sj = __float_as_int(pos[j0 + en.x].w);
-    }
-#pragma unroll
-    for (int s = 0; s < kMaxSpecies; ++s) cnt[s] += __popcll(__ballot(sj == s));
+  for (int k = 0; k < kHold; ++k) held[k] = read_entry(k * kWave + lane, n, row, j0, n_sys, pos);
+  if (lane < 8) {
+    h->cnt[lane] = 0;
+    h->in[lane] = 0;
+    h->sel[lane] = lane < c.S ? c.sel[lane] : 0;
+    h->soff[lane] = lane < c.S ? c.soff[lane] : 0;
   }
-  int off[kMaxSpecies];
-  {
-    int o = 0;
-#pragma unroll
-    for (int s = 0; s < kMaxSpecies; ++s) { off[s] = o; o += cnt[s]; }
-  }
-  if (lane == 0) {
-    h->fa = -1;
-    h->fb = -1;
-  }
-  if (lane < 2 * kMaxSpecies + 2) {
-    h->cand[lane] = make_ulonglong2(~0ull, ~0ull);
+  if (lane < 2 * kMaxSpecies) {
+    h->ckey[lane] = nan;
     h->candv[lane] = -1;
   }
   for (int k = lane; k < c.n_slots; k += kWave) smap[k] = -1;
-
-  // 2. species buckets
+  wave_lds_sync();
+  auto count = [&](const Entry &x) {
+    const int sj = __float_as_int(x.pj.w);
+    if (sj >= 0) atomicAdd(&h->cnt[sj], 1);
+  };
+#pragma unroll
+  for (int k = 0; k < kHold; ++k)
+    if (k * kWave < n) count(held[k]);
+  for (int b = kHold * kWave; b < n; b += kWave) count(read_entry(b + lane, n, row, j0, n_sys, pos));
+  wave_lds_sync();
+  int total;  // places in use
   {
-    int run[kMaxSpecies];
-#pragma unroll
-    for (int s = 0; s < kMaxSpecies; ++s) run[s] = 0;
-    for (int b = 0; b < n; b += kWave) {
-      const int e = b + lane;
-      const Entry x = read_entry(e, n, row, j0, n_sys, pos, coords, state, d.state_off, wrapped, wi, ci,
-                                 Ld, c.rc2);
-      int at = 0;
-#pragma unroll
-      for (int s = 0; s < kMaxSpecies; ++s) {
-        const unsigned long long m = __ballot(x.valid && x.sj == s);
-        if (x.valid && x.sj == s) at = off[s] + run[s] + (int)lanes_below(m);
-        run[s] += __popcll(m);
-      }
-      if (x.valid) {
-        bkt[at] = x.kt;
-        bd[at] = entry_vec(pi, pos[j0 + x.en.x], x.en.y, L);
-        bj[at] = j0 + x.en.x;
-      }
+    const int v = lane < 8 ? (h->cnt[lane] + 3) / 4 * 4 : 0;
+    int x = v;
+    for (int o = 1; o < 8; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= o) x += y;
     }
-#pragma unroll
-    for (int s = 0; s < kMaxSpecies; ++s) cnt[s] = run[s];   // the entries inside the cutoff
+    if (lane < 8) h->off[lane] = x - v;
+    total = __builtin_amdgcn_readlane(x, 7);
   }
+  for (int k = lane; k < total; k += kWave) bkey[k] = nan;
   wave_lds_sync();
 
-  // 3. rank inside each species bucket
-  for (int s = 0; s < c.S; ++s) {
-    const int cs = cnt[s], os = off[s], sel = c.sel[s], so = c.soff[s];
-    for (int vb = 0; vb < cs; vb += kWave) {
-      const int q = vb + lane;
-      const bool act = q < cs;
-      const ulonglong2 me = act ? bkt[os + q] : make_ulonglong2(~0ull, ~0ull);
+  // 2. species buckets
+  auto place = [&](const Entry &x) {
+    const int sj = __float_as_int(x.pj.w);
+    if (sj < 0) return;
+    const int j = j0 + x.en.x;
+    int mx, my, mz;
+    unpack_image(x.en.y, mx, my, mz);
+    // (without a box the record holds the caller's coordinates)
+    float cj[3] = {x.pj.x, x.pj.y, x.pj.z};
+    if (wrapped) {
+      // images refer to the wrapped records; shift them to the caller's frame
+      const float4 wj = state[d.state_off + x.en.x].wrap;
+      mx += wi[0] - (int)wj.x;
+      my += wi[1] - (int)wj.y;
+      mz += wi[2] - (int)wj.z;
+      for (int a = 0; a < 3; ++a) cj[a] = coords[3 * (size_t)j + a];
+    }
+    const double key = dp_key(ci, cj, mx, my, mz, Ld);
+    if (!(key < c.rc2)) return;
+    const unsigned img = ((unsigned)(mx + 512) & 1023u) << 20 | ((unsigned)(my + 512) & 1023u) << 10 |
+                         ((unsigned)(mz + 512) & 1023u);
+    const int at = h->off[sj] + atomicAdd(&h->in[sj], 1);
+    bkey[at] = key;
+    btie[at] = (unsigned long long)(unsigned)x.en.x << 32 | img;
+    bd[at] = entry_vec(pi, x.pj, x.en.y, L);
+    bj[at] = j;
+  };
+#pragma unroll
+  for (int k = 0; k < kHold; ++k)
+    if (k * kWave < n) place(held[k]);
+  for (int b = kHold * kWave; b < n; b += kWave) place(read_entry(b + lane, n, row, j0, n_sys, pos));
+  wave_lds_sync();
+
+  // 3. ranks inside the species buckets.  Where all keys of a bucket differ
+  //    (the ranks then add up to m (m - 1) / 2 over its m entries), the order
+  //    is that of the keys; otherwise a second pass looks at the ties too and
+  //    writes every slot and candidate again.
+  auto claim = [&](int q, int s, int rank) {
+    if (rank < h->sel[s]) smap[h->soff[s] + rank] = q;
+    if (rank < 2) {
+      h->ckey[2 * s + rank] = bkey[q];
+      h->ctie[2 * s + rank] = btie[q];
+      h->candv[2 * s + rank] = q;
+    }
+  };
+  auto bucket_of = [&](int q) {
+    int s = 0;
+#pragma unroll
+    for (int t = 1; t < kMaxSpecies; ++t) s += q >= h->off[t] ? 1 : 0;  // (empty buckets share their start)
+    return s;
+  };
+  int ranks = 0;
+  for (int b = 0; b < total; b += kWave) {
+    const int q = b + lane;
+    if (q >= total) continue;
+    const int s = bucket_of(q), os = h->off[s], cs = h->in[s];
+    if (q - os >= cs) continue;
+    const double me = bkey[q];
+    int rank = 0;
+    for (int t = os; t < os + cs; t += 4) {
+      const double k0 = bkey[t], k1 = bkey[t + 1], k2 = bkey[t + 2], k3 = bkey[t + 3];
+      rank += k0 < me;
+      rank += k1 < me;
+      rank += k2 < me;
+      rank += k3 < me;
+    }
+    ranks += cs - 1 - 2 * rank;
+    claim(q, s, rank);
+  }
+  // sum over the entries of m - 1 - 2 rank: zero where all keys differ (each
+  // tie adds to it)
+  for (int o = 32; o >= 1; o >>= 1) ranks += __shfl_xor(ranks, o);
+  if (ranks != 0) {
+    for (int b = 0; b < total; b += kWave) {
+      const int q = b + lane;
+      if (q >= total) continue;
+      const int s = bucket_of(q), os = h->off[s], cs = h->in[s];
+      if (q - os >= cs) continue;
       int rank = 0;
-      for (int t = 0; t < cs; ++t) rank += before(bkt[os + t], me) ? 1 : 0;
-      if (act && rank < sel) smap[so + rank] = os + q;
-      if (act && rank < 2) {
-        h->cand[2 * s + rank] = me;
-        h->candv[2 * s + rank] = os + q;
-      }
+      for (int t = os; t < os + cs; ++t) rank += before(bkey[t], btie[t], bkey[q], btie[q]) ? 1 : 0;
+      claim(q, s, rank);
     }
   }
   wave_lds_sync();
 
   // 4. the frame: the two nearest among the species' two nearest
-  if (lane < 2 * c.S) {
-    const ulonglong2 me = h->cand[lane];
-    const int v = h->candv[lane];
+  int fa = -1, fb = -1;
+  {
+    const double me = lane < 2 * kMaxSpecies ? h->ckey[lane] : nan;
+    const int v = lane < 2 * kMaxSpecies ? h->candv[lane] : -1;
     int g = 0;
-    for (int t = 0; t < 2 * c.S; ++t) g += before(h->cand[t], me) ? 1 : 0;
-    if (v >= 0 && g == 0) h->fa = v;
-    if (v >= 0 && g == 1) h->fb = v;
+#pragma unroll
+    for (int t = 0; t < 2 * kMaxSpecies; ++t) g += h->ckey[t] < me;
+    const unsigned long long m = __ballot(v >= 0), m0 = __ballot(v >= 0 && g == 0), m1 = __ballot(v >= 0 && g == 1);
+    const int nm = __popcll(m);
+    if (__popcll(m0) == min(nm, 1) && __popcll(m1) == (nm >= 2 ? 1 : 0)) {
+      if (m0) fa = __builtin_amdgcn_readlane(v, __ffsll(m0) - 1);
+      if (m1) fb = __builtin_amdgcn_readlane(v, __ffsll(m1) - 1);
+    } else {  // equal keys: the ties decide
+      if (lane == 0) {
+        h->fa = -1;
+        h->fb = -1;
+      }
+      if (v >= 0) {
+        const unsigned long long tie = h->ctie[lane];
+        g = 0;
+        for (int t = 0; t < 2 * kMaxSpecies; ++t)
+          g += h->candv[t] >= 0 && before(h->ckey[t], h->ctie[t], me, tie) ? 1 : 0;
+        if (g == 0) h->fa = v;
+        if (g == 1) h->fb = v;
+      }
+      wave_lds_sync();
+      fa = h->fa;
+      fb = h->fb;
+    }
   }
-  wave_lds_sync();
-  const int fa = h->fa, fb = h->fb;
   const Frame f = make_frame(fa >= 0, fa >= 0 ? bd[fa] : make_float4(0.f, 0.f, 0.f, 1.f), fb >= 0,
                              fb >= 0 ? bd[fb] : make_float4(0.f, 0.f, 0.f, 1.f));
 
@@ -306,9 +370,9 @@ k_dp_fwd(const float4 *__restrict__ pos, const float *__restrict__ coords,
       const float4 dv = bd[v];
       const float ir = 1.f / dv.w;
       out.x = ir;
-      out.y = (dv.x * f.ex[0] + dv.y * f.ex[1] + dv.z * f.ex[2]) * ir;
-      out.z = (dv.x * f.ey[0] + dv.y * f.ey[1] + dv.z * f.ey[2]) * ir;
-      out.w = (dv.x * f.ez[0] + dv.y * f.ez[1] + dv.z * f.ez[2]) * ir;
+      out.y = fmaf(dv.z, f.ex[2], fmaf(dv.x, f.ex[0], dv.y * f.ex[1])) * ir;
+      out.z = fmaf(dv.z, f.ey[2], fmaf(dv.x, f.ey[0], dv.y * f.ey[1])) * ir;
+      out.w = fmaf(dv.z, f.ez[2], fmaf(dv.x, f.ez[0], dv.y * f.ez[1])) * ir;
     }
     store_slot<BF16>(Grow, k, out);
     if (rrow)
@@ -435,14 +499,22 @@ k_dp_bwd(const int *__restrict__ row_of_atom, const float *__restrict__ dG, int 
 // Batches of small non-periodic systems (every neighbour inside the centre's
 // own system): one workgroup per system, its waves taking the system's
 // centres in turn; the system's forces are summed in LDS (64-bit fixed
-// point, integer atomics) and stored once, with no global atomics.
+// point, integer atomics) and stored once, with no global atomics.  Issue
+// bounds it (660 vector instructions per centre), on the compute unit with the
+// most centres: systems in order of decreasing size, and the second workgroup
+// of each compute unit (two of 16 waves fit) in the opposite order.
+constexpr int kCus = 256;
+
 template <int WPB>
 __global__ void __launch_bounds__(WPB * kWave)
 k_dp_bwd_sys(const SysDesc *__restrict__ sys, const int *__restrict__ row_of_atom,
              const float *__restrict__ dG, int ldg, DpConst c, const float4 *__restrict__ rec,
              float *__restrict__ F, float *__restrict__ W_atom) {
   __shared__ unsigned long long facc[3 * kSmallSystem];
-  const SysDesc &d = sys[blockIdx.x];
+  const int n_sys = gridDim.x;
+  int place = blockIdx.x;
+  if (place >= kCus && place < 2 * kCus) place = kCus + min(2 * kCus, n_sys) - 1 - place;
+  const SysDesc &d = sys[sys[place].by_size];
   const int n = d.n, a0 = d.atom_off;
   for (int t = threadIdx.x; t < 3 * n; t += WPB * kWave) facc[t] = 0ull;
   __syncthreads();
@@ -503,7 +575,13 @@ void launch_dp_fwd(const float4 *pos, const float *coords, const AtomState *stat
 // atom receives one set of float atomics per cell instead of one per
 // contribution.  A contribution that finds the table full goes straight to
 // global memory.
-constexpr int kMinCellGroups = 256;
+//
+// Float atomics bound the per-centre form.  Up to 512 cells, two per compute
+// unit, the waves of a cell are few and their latency bounds this one: sixteen
+// waves per cell (216 cells of 28 atoms: 23 us, and 59 with a wave per centre
+// and atomics; 64 cells of 31: 20 and 26; 27 cells of 37: 22 and 21), else eight.
+constexpr int kMinCellGroups = 64;
+constexpr int kCellsWide = 512;
 constexpr int kHashBits = 11;
 constexpr int kHashSlots = 1 << kHashBits;   // 2048 atoms; a cell's neighbourhood holds ~700
 
@@ -559,21 +637,24 @@ k_dp_bwd_cells(const int *__restrict__ cell_start, const int *__restrict__ cell_
 
 // The per-centre backward uses no LDS: four waves per workgroup unless asked
 // otherwise.  With small_systems (every system non-periodic with at most
-// kSmallSystem atoms) the per-system form runs instead, eight waves per
-// system; with a cell grid (cell_start non-null) of at least one cell per
-// compute unit the per-cell form, eight waves per cell (fewer cells leave
-// most of the chip idle: the 2,001-atom water box has 64).
+// kSmallSystem atoms) the per-system form runs instead, sixteen waves per
+// system; with a cell grid (cell_start non-null) of at least kMinCellGroups
+// cells the per-cell form.
 void launch_dp_bwd(const SysDesc *sys, int n_sys, bool small_systems, const int *cell_start,
                    const int *cell_atoms, int n_cells, const int *row_of_atom, const float *dG, int ldg, int N,
                    const DpConst &c, const float4 *rec, float *F, float *W_atom, int wpb_pref, hipStream_t st) {
   if (N <= 0) return;
   if (small_systems) {
-    k_dp_bwd_sys<8><<<n_sys, 8 * kWave, 0, st>>>(sys, row_of_atom, dG, ldg, c, rec, F, W_atom);
+    k_dp_bwd_sys<16><<<n_sys, 16 * kWave, 0, st>>>(sys, row_of_atom, dG, ldg, c, rec, F, W_atom);
     return;
   }
   if (cell_start && n_cells >= kMinCellGroups) {
-    k_dp_bwd_cells<8><<<n_cells, 8 * kWave, 0, st>>>(cell_start, cell_atoms, row_of_atom, dG, ldg, c, rec, F,
-                                                     W_atom);
+    if (n_cells <= kCellsWide)
+      k_dp_bwd_cells<16><<<n_cells, 16 * kWave, 0, st>>>(cell_start, cell_atoms, row_of_atom, dG, ldg, c, rec, F,
+                                                         W_atom);
+    else
+      k_dp_bwd_cells<8><<<n_cells, 8 * kWave, 0, st>>>(cell_start, cell_atoms, row_of_atom, dG, ldg, c, rec, F,
+                                                       W_atom);
     return;
   }
   const int wpb = (wpb_pref == 1 || wpb_pref == 2) ? wpb_pref : 4;

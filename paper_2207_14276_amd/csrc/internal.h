@@ -109,6 +109,7 @@ struct SysDesc {
   int rebuild;       // nonzero: build this system's neighbour list in this call
   int order_off;     // first wave of this system's centres in the AEV kernels'
                      // launch order (systems by decreasing size)
+  int by_size;       // the system in this place of that order
   long long list_off;   // first neighbour row of the system in the list pool
   long long state_off;  // first per-atom state slot (reference position, wrap)
 };
