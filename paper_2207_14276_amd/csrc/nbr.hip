@@ -396,8 +396,17 @@ k_nbr_build(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
 // same arithmetic, (r_j - r_i) + image * L.
 constexpr int kCandChunk = 1024;  // candidates staged at a time
 constexpr int kHomeChunk = 256;   // atoms of the home cell handled at a time
+// Each wave takes home atoms in turn and each atom a chain of ballots over the
+// candidates, so the latency of a cell bounds a grid of few cells: 16 waves
+// per cell up to two cells per compute unit, all of which are then resident
+// (27 cells of 37 atoms: 54 us with four waves, 20 with sixteen; 125 cells of
+// 16: 17.5 and 10; 216 of 28: 39 and 17; 512 of 23: 23 and 21).  Past that four
+// waves, five or more cells per compute unit (1,728 cells: 31 us, and 59 with
+// sixteen waves; 5,832 cells: 79 and 178).
+constexpr int kCellsWide = 512;
 
-__global__ void __launch_bounds__(256)
+template <int WPB>
+__global__ void __launch_bounds__(WPB * kWave)
 k_nbr_cell(const float4 *__restrict__ pos, const SysDesc *__restrict__ sys, Live n_sys_,
            const int *__restrict__ cell_start, const int *__restrict__ cell_atoms, float rc_list,
            int cap, int2 *__restrict__ nbr, int *__restrict__ nbr_cnt, int *__restrict__ status) {
@@ -587,8 +596,12 @@ void launch_nbr_build(const float4 *pos, const int *sys_of, const SysDesc *sys, 
   // boxes); sparse grids of small solutes are faster with a wave per atom
   // (decided on the launch sizes)
   if (n_cells > 0 && N.v >= 8 * (long long)n_cells) {
-    k_nbr_cell<<<n_cells, 256, 0, st>>>(pos, sys, n_sys, cell_start, cell_atoms, rc_list, cap, nbr,
-                                        nbr_cnt, status);
+    if (n_cells <= kCellsWide)
+      k_nbr_cell<16><<<n_cells, 1024, 0, st>>>(pos, sys, n_sys, cell_start, cell_atoms, rc_list, cap, nbr, nbr_cnt,
+                                               status);
+    else
+      k_nbr_cell<4><<<n_cells, 256, 0, st>>>(pos, sys, n_sys, cell_start, cell_atoms, rc_list, cap, nbr, nbr_cnt,
+                                             status);
     return;
   }
   k_nbr_build<<<(N.v + 3) / 4, 256, 0, st>>>(pos, sys_of, sys, cell_start, cell_atoms, N, rc_list,

@@ -91,6 +91,20 @@ def test_several_systems(kind, case, big):
     m.close()
 
 
+@pytest.mark.parametrize("kind", ["aev", "dp"])
+def test_lists_of_few_and_many_cells(kind):
+    """Sixteen waves per cell (one box) and four (a call of more than 512
+    cells) build the same lists."""
+    boxes = [synth.water_box(512, seed=50 + k) for k in range(9)]
+    m = _model(kind)
+    b, one = synth.make_batch(boxes), synth.make_batch(boxes[:1])
+    m.reserve(b.n_atoms, len(boxes), 304)
+    cnt, ent = m.neighbors(*to_dev(one), 304)
+    cnt2, ent2 = m.neighbors(*to_dev(b), 304)
+    assert torch.equal(cnt, cnt2[:one.n_atoms]) and torch.equal(ent, ent2[:one.n_atoms])
+    m.close()
+
+
 def test_persistent_lists(big):
     """Lists kept over calls: built, kept while no atom moves half the skin,
     and built again for the one system whose atom does; the same with the
