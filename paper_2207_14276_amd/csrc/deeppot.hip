@@ -578,7 +578,7 @@ void launch_dp_fwd(const float4 *pos, const float *coords, const AtomState *stat
 //
 // Float atomics bound the per-centre form.  Up to 512 cells, two per compute
 // unit, the waves of a cell are few and their latency bounds this one: sixteen
-// waves per cell (216 cells of 28 atoms: 23 us, and 59 with a wave per centre
+// waves per cell (216 cells of 28 atoms: 19 us, and 59 with a wave per centre
 // and atomics; 64 cells of 31: 20 and 26; 27 cells of 37: 22 and 21), else eight.
 constexpr int kMinCellGroups = 64;
 constexpr int kCellsWide = 512;
@@ -626,12 +626,10 @@ k_dp_bwd_cells(const int *__restrict__ cell_start, const int *__restrict__ cell_
     });
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < kHashSlots; t += WPB * kWave) {
-    const int j = hkey[t];
-    if (j < 0) continue;
-    atomicAdd(&F[3 * (size_t)j], from_fix((long long)hval[3 * t]));
-    atomicAdd(&F[3 * (size_t)j + 1], from_fix((long long)hval[3 * t + 1]));
-    atomicAdd(&F[3 * (size_t)j + 2], from_fix((long long)hval[3 * t + 2]));
+  // a component per lane: an atom's three go to one memory line together
+  for (int t = threadIdx.x; t < 3 * kHashSlots; t += WPB * kWave) {
+    const int j = hkey[t / 3];
+    if (j >= 0) atomicAdd(&F[3 * (size_t)j + t % 3], from_fix((long long)hval[t]));
   }
 }
 
