@@ -10,10 +10,8 @@
 // ballots.  Then
 //   radial:  lanes = 16 radial shifts x 4 neighbour slots, one species block
 //            at a time, reduced across the 4 slots with lane shuffles;
-//   angular (forward): the species-pair blocks in passes of 64 pair slots;
-//            a pass holds a 64-pair piece of a large block, or the rest of
-//            one block followed by whole smaller blocks, each padded to a
-//            multiple of 8 slots:
+//   angular (forward): the species-pair blocks, each padded to a multiple of
+//            8 slots, one after another in passes of 64 pair slots:
 //            (A) lane per slot: the pair geometry (cos and sin of the angle,
 //                the 4 radial Gaussians of the mean distance times the
 //                cutoff product) is computed once and staged in a per-wave
@@ -47,18 +45,6 @@ __device__ inline float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ inline float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
-
-// q = u / n and r = u mod n for 0 <= u < 2^23 through a float reciprocal
-// (rn within an ulp of 1/n): the estimate is off by at most one, corrected
-// by selects.
-__device__ inline int fdivmod(int u, int n, float rn, int &r) {
-  int q = (int)((float)u * rn);
-  int m = u - q * n;
-  const bool hi = m >= n, lo = m < 0;
-  q = hi ? q + 1 : (lo ? q - 1 : q);
-  r = hi ? m - n : (lo ? m + n : m);
-  return q;
-}
 
 // Wave-uniform per-species counts and offsets of the sorted lists.
 struct Lists {
@@ -133,7 +119,7 @@ __device__ inline WaveLds carve(char *base, int cap) {
 // y in the shorter of length n2; a same-species block uses the one list for
 // both; the angular term is symmetric in its two neighbours): oxy = offsets
 // of the x and y lists (16 bits each), ns = n1 | n2 << 16 | same << 31,
-// r2 = 1 / n2 (a hardware reciprocal: fdivmod corrects the quotient).
+// r2 = 1 / n2 (a hardware reciprocal, see unrank).
 // Other lanes get T = 0.
 __device__ inline void block_words(int lane, const Lists &ls, int S, int &bT, int &bOxy, int &bNs, float &bR2) {
   bT = 0;
@@ -164,14 +150,16 @@ __device__ inline void block_words(int lane, const Lists &ls, int S, int &bT, in
 // every unordered pair comes once (for even n the last row q = n / 2 - 1
 // holds only y < n / 2).  Either way y + q (+ 1) < 2 n1, and neighbouring
 // lanes take different entries of both lists (their LDS adds to an entry's
-// accumulators do not pile up on one address).
+// accumulators do not pile up on one address).  The quotient is that of
+// (u + 1/2) r2, cut off: (u + 1/2) / n2 keeps 1 / (2 n2) from any integer,
+// more than the rounding of r2 (two ulp) and of the product for every u and n2
+// that lists of 1,025 entries allow.
 __device__ inline void unrank(int u, int ns, float r2, int oxy, int &ax, int &ay) {
   const int n1 = ns & 0xffff, n2 = (ns >> 16) & 0x7fff;
-  int y;
-  const int q = fdivmod(u, n2, r2, y);
-  int x = y + q + (ns < 0 ? 1 : 0);
-  x = x >= n1 ? x - n1 : x;
-  ax = (oxy & 0xffff) + x;
+  const int q = (int)(((float)u + 0.5f) * r2);
+  const int y = u - (int)__umul24((unsigned)q, (unsigned)n2);
+  const unsigned x = (unsigned)(y + q) + ((unsigned)ns >> 31);
+  ax = (oxy & 0xffff) + (int)min(x, x - (unsigned)n1);
   ay = ((oxy >> 16) & 0xffff) + y;
 }
 
@@ -227,43 +215,23 @@ __device__ __attribute__((always_inline)) inline void put_entry(int q, int qa, b
   }
 }
 
-// Builds the species-sorted radial list (R < rc_r) and angular list
-// (R < rc_a, a subset) of centre i in LDS from its neighbour row, or (self
-// >= 0) from all atoms of its system, keeping those a list would hold (R^2
-// below rc_r^2 as the list build tests it).  Two passes over the entries:
-// per-species counts by ballot, then placement.  Rows of up to 128 entries
-// (the common case) are loaded once and kept in registers for both passes;
-// longer rows are loaded again.  Per-species tallies live in registers
-// (loops over the species slots are fully unrolled; species without an
-// entry in a chunk are skipped) and the wave-uniform result is published
-// in LDS.
+// fill_lists of rows of more than 128 entries: two passes over the entries,
+// per-species counts by ballot, then placement.  Per-species tallies live in
+// registers (loops over the species slots are fully unrolled; species without
+// an entry in a chunk are skipped).
 template <bool BWD>
-__device__ inline void fill_lists(int lane, int n, const int2 *__restrict__ ent, int self, int j0, int n_sys,
-                                  const float4 *__restrict__ pos, const float4 &pi,
-                                  const float L[3], const AevConst &c, WaveLds &w) {
+__device__ inline void fill_lists_long(int lane, int n, const int2 *__restrict__ ent, int self, int j0, int n_sys,
+                                       const float4 *__restrict__ pos, const float4 &pi,
+                                       const float L[3], const AevConst &c, WaveLds &w) {
   const int S = c.S;
-  const bool cached = n <= 2 * kWave;  // wave-uniform
   const float rc2 = c.rc_r * c.rc_r;
-  int sj0 = -1, sj1 = -1, jj0 = 0, jj1 = 0;
-  float4 d0 = make_float4(0.f, 0.f, 0.f, 1e30f), d1 = d0;
-  if (cached) {
-    load_entry(lane, n, ent, self, j0, n_sys, pos, pi, L, sj0, jj0, d0);
-    if (n > kWave) load_entry(kWave + lane, n, ent, self, j0, n_sys, pos, pi, L, sj1, jj1, d1);
-  }
   int cR[kMaxSpecies], cA[kMaxSpecies];
 #pragma unroll
   for (int s = 0; s < kMaxSpecies; ++s) { cR[s] = 0; cA[s] = 0; }
   for (int b = 0; b < n; b += kWave) {
     int sj, j;
     float4 d;
-    if (cached) {  // the entry of this lane in the chunk starting at b
-      const bool first = b == 0;
-      sj = first ? sj0 : sj1;
-      j = first ? jj0 : jj1;
-      d = first ? d0 : d1;
-    } else {
-      load_entry(b + lane, n, ent, self, j0, n_sys, pos, pi, L, sj, j, d);
-    }
+    load_entry(b + lane, n, ent, self, j0, n_sys, pos, pi, L, sj, j, d);
     const bool inR = sj >= 0 && d.w < c.rc_r && (self < 0 || d.x * d.x + d.y * d.y + d.z * d.z < rc2),
                inA = inR && d.w < c.rc_a;
 #pragma unroll
@@ -293,14 +261,7 @@ __device__ inline void fill_lists(int lane, int n, const int2 *__restrict__ ent,
   for (int b = 0; b < n; b += kWave) {
     int sj, j;
     float4 d;
-    if (cached) {  // the entry of this lane in the chunk starting at b
-      const bool first = b == 0;
-      sj = first ? sj0 : sj1;
-      j = first ? jj0 : jj1;
-      d = first ? d0 : d1;
-    } else {
-      load_entry(b + lane, n, ent, self, j0, n_sys, pos, pi, L, sj, j, d);
-    }
+    load_entry(b + lane, n, ent, self, j0, n_sys, pos, pi, L, sj, j, d);
     const bool inR = sj >= 0 && d.w < c.rc_r && (self < 0 || d.x * d.x + d.y * d.y + d.z * d.z < rc2),
                inA = inR && d.w < c.rc_a;
     // slots of this lane's entry in the two lists (selects per species;
@@ -320,6 +281,84 @@ __device__ inline void fill_lists(int lane, int n, const int2 *__restrict__ ent,
     }
     put_entry<BWD>(q, qa, inR, inA, j, d, kr, ka, w);
   }
+}
+
+// Counts per species slot, a byte each: slots 0 to 3 in lo, 4 to 7 in hi.
+struct Bytes8 {
+  unsigned lo, hi;
+  __device__ inline Bytes8 operator+(const Bytes8 &o) const { return {lo + o.lo, hi + o.hi}; }
+};
+__device__ inline int byte_of(const Bytes8 &v, int s) {
+  return (int)__builtin_amdgcn_ubfe(s < 4 ? v.lo : v.hi, 8u * ((unsigned)s & 3u), 8u);
+}
+// Per lane: how many of the lanes up to it are in, by species (hi only where
+// there can be a slot above 3).
+__device__ inline Bytes8 species_scan(bool in, int s, bool many) {
+  const unsigned one = in ? 1u << (8u * ((unsigned)s & 3u)) : 0u;
+  Bytes8 v = {s < 4 ? one : 0u, 0u};
+  v.lo = wave_scan(v.lo);
+  if (many) v.hi = wave_scan(s < 4 ? 0u : one);
+  return v;
+}
+__device__ inline Bytes8 last_lane(const Bytes8 &v) {
+  return {(unsigned)__builtin_amdgcn_readlane((int)v.lo, kWave - 1),
+          (unsigned)__builtin_amdgcn_readlane((int)v.hi, kWave - 1)};
+}
+// Sums over the slots below each.
+__device__ inline Bytes8 slots_below(const Bytes8 &v) {
+  return {v.lo * 0x01010100u, v.hi * 0x01010100u + (v.lo * 0x01010101u >> 24) * 0x01010101u};
+}
+
+// Builds the species-sorted radial list (R < rc_r) and angular list
+// (R < rc_a, a subset) of centre i in LDS from its neighbour row, or (self
+// >= 0) from all atoms of its system, keeping those a list would hold (R^2
+// below rc_r^2 as the list build tests it).  The wave-uniform counts and
+// offsets are published in LDS.
+// Rows of up to 128 entries (the common case): the entries stay in registers,
+// and an entry's slot is its place among the lanes of its species, by a scan
+// over the wave of byte counters (about 40 instructions per 64 entries and
+// list, where a ballot per species and pass took 110).
+template <bool BWD>
+__device__ inline void fill_lists(int lane, int n, const int2 *__restrict__ ent, int self, int j0, int n_sys,
+                                  const float4 *__restrict__ pos, const float4 &pi,
+                                  const float L[3], const AevConst &c, WaveLds &w) {
+  if (n > 2 * kWave) {
+    fill_lists_long<BWD>(lane, n, ent, self, j0, n_sys, pos, pi, L, c, w);
+    return;
+  }
+  const float rc2 = c.rc_r * c.rc_r;
+  const bool two = n > kWave, many = c.S > 4;
+  int s0 = -1, s1 = -1, j_0 = 0, j_1 = 0;
+  float4 d0 = make_float4(0.f, 0.f, 0.f, 1e30f), d1 = d0;
+  load_entry(lane, n, ent, self, j0, n_sys, pos, pi, L, s0, j_0, d0);
+  if (two) load_entry(kWave + lane, n, ent, self, j0, n_sys, pos, pi, L, s1, j_1, d1);
+  auto in_radial = [&](int s, const float4 &d) {
+    return s >= 0 && d.w < c.rc_r && (self < 0 || d.x * d.x + d.y * d.y + d.z * d.z < rc2);
+  };
+  const bool r0 = in_radial(s0, d0), a0 = r0 && d0.w < c.rc_a;
+  const Bytes8 scR0 = species_scan(r0, s0, many), scA0 = species_scan(a0, s0, many);
+  const Bytes8 tR0 = last_lane(scR0), tA0 = last_lane(scA0);
+  bool r1 = false, a1 = false;
+  Bytes8 scR1 = {0u, 0u}, scA1 = scR1, tR = tR0, tA = tA0;
+  if (two) {
+    r1 = in_radial(s1, d1);
+    a1 = r1 && d1.w < c.rc_a;
+    scR1 = species_scan(r1, s1, many);
+    scA1 = species_scan(a1, s1, many);
+    tR = tR + last_lane(scR1);
+    tA = tA + last_lane(scA1);
+  }
+  const Bytes8 oR = slots_below(tR), oA = slots_below(tA);
+  if (lane < 8) {
+    w.ls->cR[lane] = byte_of(tR, lane);
+    w.ls->oR[lane] = byte_of(oR, lane);
+    w.ls->cA[lane] = byte_of(tA, lane);
+    w.ls->oA[lane] = byte_of(oA, lane);
+  }
+  const float kr = kPi / c.rc_r, ka = kPi / c.rc_a;
+  put_entry<BWD>(byte_of(scR0 + oR, s0) - 1, byte_of(scA0 + oA, s0) - 1, r0, a0, j_0, d0, kr, ka, w);
+  if (two)
+    put_entry<BWD>(byte_of(scR1 + (oR + tR0), s1) - 1, byte_of(scA1 + (oA + tA0), s1) - 1, r1, a1, j_1, d1, kr, ka, w);
 }
 
 // A workgroup of W waves at one centre (W = 1: a wave on its own): orders the
@@ -353,6 +392,8 @@ __device__ inline void fill_lists_group(int wave, int lane, int n, const int2 *_
   int sj0 = -1, jj0 = 0;
   float4 d0 = make_float4(0.f, 0.f, 0.f, 1e30f);
   bool inR0 = false, inA0 = false;
+  const bool many = S > 4;
+  Bytes8 scR0 = {0u, 0u}, scA0 = scR0;
   const int b0 = wave * kWave;
   if (b0 < n) load(b0, sj0, jj0, d0, inR0, inA0);
   for (int b = b0; b < n; b += W * kWave) {
@@ -360,13 +401,14 @@ __device__ inline void fill_lists_group(int wave, int lane, int n, const int2 *_
     float4 d = d0;
     bool inR = inR0, inA = inA0;
     if (b != b0) load(b, sj, j, d, inR, inA);
-    int v = 0;  // lane s: radial entries of species s, lane 8 + s: angular ones
-#pragma unroll
-    for (int s = 0; s < kMaxSpecies; ++s) {
-      const int r = __popcll(__ballot(inR && sj == s)), a = __popcll(__ballot(inA && sj == s));
-      v = lane == s ? r : lane == 8 + s ? a : v;
+    const Bytes8 scR = species_scan(inR, sj, many), scA = species_scan(inA, sj, many);
+    if (b == b0) {
+      scR0 = scR;
+      scA0 = scA;
     }
-    if (lane < 16) cnt[(b / kWave) * 16 + lane] = v;
+    // lane s: radial entries of species s, lane 8 + s: angular ones
+    const Bytes8 tR = last_lane(scR), tA = last_lane(scA);
+    if (lane < 16) cnt[(b / kWave) * 16 + lane] = byte_of(lane < 8 ? tR : tA, lane & 7);
   }
   centre_sync<W>();
   // lane s / 8 + s: the species' total, then its first slot in the list
@@ -396,19 +438,13 @@ __device__ inline void fill_lists_group(int wave, int lane, int n, const int2 *_
     int sj = sj0, j = jj0;
     float4 d = d0;
     bool inR = inR0, inA = inA0;
-    if (b != b0) load(b, sj, j, d, inR, inA);
-    int q = 0, qa = 0;
-#pragma unroll
-    for (int s = 0; s < kMaxSpecies; ++s) {
-      const unsigned long long mR = __ballot(inR && sj == s);
-      if (!mR) continue;
-      const unsigned long long mA = __ballot(inA && sj == s);
-      const int fR = __builtin_amdgcn_readlane(first, s), fA = __builtin_amdgcn_readlane(first, 8 + s);
-      if (sj == s) {
-        q = fR + (int)lanes_below(mR);
-        qa = fA + (int)lanes_below(mA);
-      }
+    Bytes8 scR = scR0, scA = scA0;
+    if (b != b0) {
+      load(b, sj, j, d, inR, inA);
+      scR = species_scan(inR, sj, many);
+      scA = species_scan(inA, sj, many);
     }
+    const int q = __shfl(first, sj & 7) + byte_of(scR, sj) - 1, qa = __shfl(first, 8 + (sj & 7)) + byte_of(scA, sj) - 1;
     put_entry<BWD>(q, qa, inR, inA, j, d, kr, ka, w);
   }
 }
@@ -470,6 +506,14 @@ __device__ inline unsigned long long spread_pairs(unsigned long long x) {
 static_assert(kNShfRad == 16 && kAngBlock == 32, "row mask halves");
 static_assert(kMaxSpecies + kMaxSpecies * (kMaxSpecies + 1) <= 64, "row mask width");
 
+// The issue of vector instructions bounds it (97% of the cycles on 512 ragged
+// solutes, 67 neighbours and 830 pairs per centre).  Of 3,900 instructions per
+// centre 450 went into the sorted lists and 80 into each pass of pair geometry;
+// with byte-counter scans, a quotient that needs no correction and blocks that
+// run on over the passes (14 in place of 16.4) there are 3,450: 512 solutes 205
+// -> 190 us, 4,096 snapshots of 40 atoms 730 -> 608, a box of 100,002 atoms 197
+// -> 169.
+//
 // Several waves per centre (GROUP): for calls with fewer centres than the chip
 // has SIMDs, where a centre's chain of passes is the call's latency, and for
 // neighbour capacities whose lists leave too few waves on a compute unit.  The
@@ -587,59 +631,42 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
       for (int k = GROUP ? (int)threadIdx.x : lane; k < n_blk * kChunksPerBlock; k += W * kWave)
         if (!((nonempty >> (k / kChunksPerBlock)) & 1ull)) ang[k] = make_uint4(0u, 0u, 0u, 0u);
     }
-    // Passes of 64 pair slots.  A block with more than 64 pairs left fills
-    // a pass on its own; otherwise the pass takes the rest of the block and
-    // then whole following blocks while they fit, each padded to a multiple
-    // of 8 slots, so that every group of 8 slots belongs to one block.
+    // Passes of 64 pair slots, eight groups of 8, over the stream of the
+    // blocks' pairs; every block is padded to whole groups, and a block that
+    // does not end in a pass goes on in the next one.
     float acc0 = 0.f, acc1 = 0.f, acc2 = 0.f, acc3 = 0.f;
-    unsigned long long pending = nonempty;
+    int bG = (bT + 7) >> 3;  // lane b: groups of block b
     if constexpr (GROUP) {
       // the blocks whose middle lies in this wave's share of all pair slots
-      int end = (bT + 7) & ~7;
-#pragma unroll
-      for (int d = 1; d < 32; d <<= 1) {  // n_blk <= 28
-        const int y = __shfl_up(end, d, 32);
-        if ((lane & 31) >= d) end += y;
-      }
-      const int total = __builtin_amdgcn_readlane(end, n_blk - 1), mid = end - ((bT + 7) >> 1);
-      pending = __ballot(bT > 0 && min((int)((float)mid * (float)W * fast_rcp((float)max(total, 1))), W - 1) == wave);
+      const int end = 8 * (int)wave_scan((unsigned)bG);
+      const int total = __builtin_amdgcn_readlane(end, kWave - 1), mid = end - ((bT + 7) >> 1);
+      const bool mine = min((int)((float)mid * (float)W * fast_rcp((float)max(total, 1))), W - 1) == wave;
+      bG = mine ? bG : 0;
     }
-    int u = 0;  // pairs of the first pending block done by earlier passes
-    while (pending) {
-      const int q = __builtin_ctzll(pending);
-      const int Tq = __builtin_amdgcn_readlane(bT, q);
-      // this lane's slot: block fields, pair index within the block, count
-      int l_oxy = __builtin_amdgcn_readlane(bOxy, q);
-      int l_ns = __builtin_amdgcn_readlane(bNs, q);
-      float l_r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bR2), q));
-      int l_u = u + lane, l_T = Tq;
-      unsigned long long in_pass = 1ull << q;
-      const bool finish = Tq - u <= kPairPass;
-      int used = kPairPass;  // slots taken by the pass's blocks
-      if (finish) {
-        used = (Tq - u + 7) & ~7;
-        unsigned long long rest = pending & (pending - 1);
-        while (rest) {
-          const int q2 = __builtin_ctzll(rest);
-          const int T2 = __builtin_amdgcn_readlane(bT, q2);
-          const int g2 = (T2 + 7) & ~7;
-          if (used + g2 > kPairPass) break;
-          if (lane >= used) {
-            l_oxy = __builtin_amdgcn_readlane(bOxy, q2);
-            l_ns = __builtin_amdgcn_readlane(bNs, q2);
-            l_r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bR2), q2));
-            l_u = lane - used;
-            l_T = T2;
-          }
-          used += g2;
-          in_pass |= 1ull << q2;
-          rest &= rest - 1;
-        }
+    const int gEnd = (int)wave_scan((unsigned)bG), gStart = gEnd - bG;
+    const int n_groups = __builtin_amdgcn_readlane(gEnd, kWave - 1);
+    const unsigned long long todo = __ballot(bG > 0);
+    int qb = todo ? __builtin_ctzll(todo) : 0;  // the block of the pass's first group
+    for (int base = 0; base < n_groups; base += kPairPass / 8) {
+      // this lane's block: the last one that starts at or before its group
+      const int gi = base + a;
+      int p = qb;
+      for (unsigned long long m = todo & (~0ull << (qb + 1)); m; m &= m - 1) {
+        const int r = __builtin_ctzll(m);
+        const int sr = __builtin_amdgcn_readlane(gStart, r);
+        if (sr >= base + kPairPass / 8) break;
+        p = gi >= sr ? r : p;
       }
+      const int pa = p << 2;
+      const int l_oxy = __builtin_amdgcn_ds_bpermute(pa, bOxy);
+      const int l_ns = __builtin_amdgcn_ds_bpermute(pa, bNs);
+      const float l_r2 = __int_as_float(__builtin_amdgcn_ds_bpermute(pa, __float_as_int(bR2)));
+      const int l_T = __builtin_amdgcn_ds_bpermute(pa, bT);
+      const int l_u = 8 * (gi - __builtin_amdgcn_ds_bpermute(pa, gStart)) + t0;
       // (A) lane per pair slot; padding slots (and slots past the pass's
       // blocks) repeat a valid pair with a zero cutoff product
       {
-        const bool valid = lane < used && l_u < l_T;
+        const bool valid = gi < n_groups && l_u < l_T;
         const int tt = min(l_u, l_T - 1);
         int qj, qk;
         unrank(tt, l_ns, l_r2, l_oxy, qj, qk);
@@ -662,14 +689,11 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
       // block's accumulators are reduced across the 8 pairs and stored once
       // its last pair is done
       {
-        int g = 0;  // first group of the block in the pass
-        unsigned long long blocks = in_pass;
-        while (blocks) {
-          const int k = __builtin_ctzll(blocks);
-          blocks &= blocks - 1;
-          const int Tk = __builtin_amdgcn_readlane(bT, k);
-          const int ng = k == q ? (finish ? (Tq - u + 7) >> 3 : kPairPass / 8) : (Tk + 7) >> 3;
-          const int gend = g + ng;
+        int g = 0;
+        const int used = min(n_groups - base, kPairPass / 8);
+        while (g < used) {
+          const int k = qb, end = __builtin_amdgcn_readlane(gEnd, k) - base;
+          const int gend = min(end, used);
           for (; g + 2 <= gend; g += 2) {
             const int q0 = 8 * g + t0, q1 = q0 + 8;
             const float2 geo0 = w.tGeo[q0], geo1 = w.tGeo[q1];
@@ -692,7 +716,7 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
             acc0 += v * f2.x; acc1 += v * f2.y; acc2 += v * f2.z; acc3 += v * f2.w;
             ++g;
           }
-          if (k != q || finish) {
+          if (end <= used) {
             // sums over the 8 slot lanes of each angle shift, halving the
             // values in flight at each step: the two quads of the 8 lanes
             // swap halves (r 0, 1 stay low, r 2, 3 high), then the lane
@@ -708,16 +732,12 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
               store1<BF16>(Grow, c.rad_len + k * kAngBlock + kNShfZ * r + a, C);
             }
             acc0 = acc1 = acc2 = acc3 = 0.f;
+            const unsigned long long next = todo & (~0ull << (k + 1));
+            if (next) qb = __builtin_ctzll(next);
           }
         }
       }
       wave_lds_sync();
-      if (finish) {
-        pending &= ~in_pass;
-        u = 0;
-      } else {
-        u += kPairPass;
-      }
     }
   }
   if (status && lane == 0 && nb_cnt > nb_max) atomicMax(status + 1, nb_cnt);
@@ -890,18 +910,11 @@ __device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__res
     const float *gA = g + c.rad_len;
     // lane b: species-pair block b, with the first pair of the block in the
     // stream (an exclusive prefix sum of the counts over the lanes)
-    const int n_blk = c.S * (c.S + 1) / 2;
     int bT, bOxy, bNs;
     float bR2;
     block_words(lane, ls, c.S, bT, bOxy, bNs, bR2);
-    int bStart = bT;
-#pragma unroll
-    for (int d = 1; d < 32; d <<= 1) {  // n_blk <= 28: the first 32 lanes hold every block
-      const int y = __shfl_up(bStart, d, 32);
-      if ((lane & 31) >= d) bStart += y;
-    }
-    const int P = __builtin_amdgcn_readlane(bStart, n_blk - 1);
-    bStart -= bT;
+    const int bEnd = (int)wave_scan((unsigned)bT), bStart = bEnd - bT;
+    const int P = __builtin_amdgcn_readlane(bEnd, kWave - 1);
     const float zm1 = c.zeta - 1.0f;
     const float keta = -c.eta_a * 1.4426950408889634f;
     const float m2eta = -2.0f * c.eta_a;
@@ -1019,8 +1032,8 @@ __device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__res
       // the same on every call
       for (int turn = 0; turn < W; ++turn) {
         if ((W == 1 || turn == wave) && valid) {
-          double *gj = w.rG + 3 * qj;
-          double *gk = w.rG + 3 * qk;
+          double *gj = (double *)((char *)w.rG + __umul24((unsigned)qj, 24u));
+          double *gk = (double *)((char *)w.rG + __umul24((unsigned)qk, 24u));
           atomicAdd(gj + 0, (double)gjx);
           atomicAdd(gj + 1, (double)gjy);
           atomicAdd(gj + 2, (double)gjz);

@@ -74,6 +74,16 @@ __device__ inline float wave_sum(float v) {
 template <int CTRL, int ROWS = 0xF> __device__ inline unsigned dpp_u(unsigned v) {
   return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
+// sum over this lane and all lanes below it
+__device__ inline unsigned wave_scan(unsigned v) {
+  v += dpp_u<0x111>(v);  // row_shr:1
+  v += dpp_u<0x112>(v);  // row_shr:2
+  v += dpp_u<0x114>(v);  // row_shr:4
+  v += dpp_u<0x118>(v);  // row_shr:8
+  v += dpp_u<0x142, 0xA>(v);  // row_bcast15 into rows 1 and 3
+  v += dpp_u<0x143, 0xC>(v);  // row_bcast31 into rows 2 and 3
+  return v;
+}
 __device__ inline unsigned wave_or(unsigned v) {
   v |= dpp_u<0xB1>(v);
   v |= dpp_u<0x4E>(v);
