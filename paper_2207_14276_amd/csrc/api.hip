@@ -129,6 +129,7 @@ struct nnp_model {
   bool split = false;                    // float32 model whose GEMMs run on the bf16 matrix cores (split.hip)
   std::vector<void *> weight_allocs;
   int cap = 256;                         // neighbour capacity per atom
+  int gapG = 0;                          // zero columns after the radial part of a row of G
   int ldG = 0;                           // row stride of the AEV buffer G: the AEV length
                                          // rounded up to 32; columns past it stay zero
   size_t G_zeroed = 0;                   // bytes of G cleared since its last growth
@@ -206,14 +207,15 @@ static int upload(nnp_model *m, const void *host, size_t bytes, void **dev) {
 
 // The three bf16 parts of a device matrix [rows][K] (columns padded to Kp)
 // into *out, allocated here (for `copies` such matrices) where it is null.
-static int split_parts(nnp_model *m, const float *src, int rows, int K, int Kp, int copies, uint16_t **out) {
+static int split_parts(nnp_model *m, const float *src, int rows, int K, int Kp, int copies, uint16_t **out,
+                       int gap_at = 0, int gap = 0) {
   if (!*out) {
     void *p = nullptr;
     HIP_TRY(hipMalloc(&p, (size_t)copies * rows * Kp * 6));
     m->weight_allocs.push_back(p);
     *out = (uint16_t *)p;
   }
-  launch_split_weights(src, rows, K, K, Kp, *out, nullptr);
+  launch_split_weights(src, rows, K, K, Kp, gap_at, gap, *out, nullptr);
   HIP_TRY(hipGetLastError());
   return NNP_OK;
 }
@@ -382,6 +384,10 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
     for (size_t k = 0; k < nw; ++k) finite &= std::fabs(wp[k]) <= 3.3895314e38f;
     m->split = ok && finite;
   }
+  // the first layer's padded rows (bfloat16 and split models) have the zero
+  // columns after the radial part where its length is no multiple of 32 (it
+  // is of 16): the angular blocks are whole chunks then
+  if (m->kind == kDescAev && L >= 2 && (m->precision == NNP_BF16 || m->split)) m->gapG = m->aev.rad_len % 32;
   std::vector<float> tmp;
   std::vector<uint16_t> tb;
   for (int mb = 0; mb < m->M; ++mb)
@@ -403,7 +409,13 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
             // first layer: rows padded with zeros to the stride of G
             std::vector<uint16_t> pad((size_t)lw.n_out * m->ldG, 0);
             for (int o = 0; o < lw.n_out; ++o)
-              round_bf16_host(wp + (size_t)o * lw.n_in, pad.data() + (size_t)o * m->ldG, lw.n_in);
+            {
+              const float *src = wp + (size_t)o * lw.n_in;
+              uint16_t *dst = pad.data() + (size_t)o * m->ldG;
+              const int n1 = m->gapG ? m->aev.rad_len : lw.n_in;
+              round_bf16_host(src, dst, n1);
+              round_bf16_host(src + n1, dst + n1 + m->gapG, lw.n_in - n1);
+            }
             if ((rc = upload(m, pad.data(), pad.size() * 2, (void **)&lw.Wb))) return rc;
           } else {
             round_bf16_host(wp, tb.data(), nw);
@@ -418,7 +430,8 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
           const LayerW *first = mb > 0 ? &m->layer(0, s, l) : nullptr;
           if (first) lw.Ws = first->Ws + (size_t)mb * lw.n_out * Kp * 3;
           if (first && l > 0) lw.Wts = first->Wts + (size_t)mb * nw * 3;
-          if ((rc = split_parts(m, lw.W, lw.n_out, lw.n_in, Kp, m->M, &lw.Ws))) return rc;
+          if ((rc = split_parts(m, lw.W, lw.n_out, lw.n_in, Kp, m->M, &lw.Ws, m->aev.rad_len, l == 0 ? m->gapG : 0)))
+            return rc;
           if (l > 0 && (rc = split_parts(m, lw.Wt, lw.n_in, lw.n_out, lw.n_out, m->M, &lw.Wts))) return rc;
         }
         wp += nw;
@@ -1366,23 +1379,25 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     float *W_atom = o.virial ? m->W_atom.as<float>() : nullptr;  // per-centre virials, where asked for
     // descriptor forward into rows of G (the AEV export: float32 rows of the
     // dE/dG buffer, gathered back to atom order)
-    auto descriptor = [&](void *Gp, bool g_bf16, int ldg, float4 *rec, unsigned long long *tm, int wpb) {
+    auto descriptor = [&](void *Gp, bool g_bf16, int ldg, int gap, float4 *rec, unsigned long long *tm, int wpb) {
+      AevConst aev = m->aev;
+      aev.rad_len += gap;  // (where the angular part starts in the row)
       if (dp)
         launch_dp_fwd(pos, coords, pool_state, m->sys_of.as<int>(), dsys, pool_nbr, pool_cnt, cap,
                       m->row_of_atom.as<int>(), Gp, g_bf16, ldg, N, m->dp, rec, wpb, st);
       else
         launch_aev_fwd(pos, m->sys_of.as<int>(), dsys, direct ? nullptr : pool_nbr, pool_cnt, lds_cap,
-                       m->row_of_atom.as<int>(), Gp, g_bf16, ldg, lN, m->aev, tm, wave_atom,
+                       m->row_of_atom.as<int>(), Gp, g_bf16, ldg, lN, aev, tm, wave_atom,
                        direct ? status : nullptr, wpb, m->max_lds, st);
     };
     if (mode == kAev) {
-      descriptor(m->dG.p, false, D, nullptr, nullptr, 0);
+      descriptor(m->dG.p, false, D, 0, nullptr, nullptr, 0);
       launch_gather_rows(m->dG.as<float>(), D, m->row_of_atom.as<int>(), N, D, o.aev, st);
       HIP_TRY(hipGetLastError());
       return NNP_OK;
     }
     site_begin(kSiteAevFwd);
-    descriptor(m->G.p, bf16, m->ldG, dp && want_grad ? m->dp_rec.as<float4>() : nullptr, gmask,
+    descriptor(m->G.p, bf16, m->ldG, m->gapG, dp && want_grad ? m->dp_rec.as<float4>() : nullptr, gmask,
                m->tune_val[kSiteAevFwd]);
     site_end(kSiteAevFwd);
     mark();
@@ -1412,7 +1427,11 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
       gl.ldc = M * m->ldH[l];
       gl.c_member_stride = m->ldH[l];
       gl.bucket_cnt = m->bucket_cnt.as<int>();
-      if (l == 0) gl.row_mask = gmask;
+      if (l == 0) {
+        gl.row_mask = gmask;
+        gl.rad_halves = S;
+        gl.rad_gap = m->gapG / 16;
+      }
       for (int mb = 0; mb < M; ++mb)
         for (int s = 0; s < S; ++s) {
           LayerW &lw = m->layer(mb, s, l);

@@ -192,6 +192,11 @@ struct GemmLaunch {
   // for a wave whose columns are all such.
   const unsigned long long *row_mask;
   const int *bucket_cnt;       // [n_groups] real rows per bucket (with row_mask)
+  // First layer, with row_mask: the rows of A and B hold rad_gap halves of
+  // zeros after their rad_halves radial ones, so that an angular block (two
+  // halves) is one K chunk of 32 columns from a 64-byte line's start on: it is
+  // read whole or not at all.
+  int rad_halves, rad_gap;
   int n_groups;                // species
   int n_members;               // grid dimension over ensemble members
   int n_seg;                   // K segments summed into one output
@@ -353,7 +358,8 @@ void launch_chain(const ChainLaunch &cl, bool f32, int n_hidden, bool grad, int 
 // float32 models on the bfloat16 matrix cores (split.hip).  Weights: src
 // [rows][K] float32 (row stride ld) to parts [rows][Kp / 32][3][32], Kp a
 // multiple of 32 >= K, zeros past K.
-void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, uint16_t *dst, hipStream_t st);
+void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, int gap_at, int gap, uint16_t *dst,
+                          hipStream_t st);
 // As launch_gemm with float32 activations and parts as B (row_mask nullable,
 // bucket_cnt required); every K a multiple of 32; where the members share A,
 // n_out too, and member m's parts follow member m - 1's in memory.

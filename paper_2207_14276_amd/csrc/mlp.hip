@@ -279,11 +279,11 @@ template <> struct Vec8<false> {
 // (or TN x 32) operand tile is 16-byte slots, row r's 4 K-chunks at slots
 // 4 r + (chunk ^ swz(r)); a wave's load instruction fills 64 consecutive
 // slots, and the XOR swizzle keeps the MFMA operand reads free of bank
-// conflicts for both 8- and 16-lane LDS phases.  Requires every K (per
+// conflicts (measured: 5.2 clocks a read; 8.9 with (r >> 1) ^ (r >> 3)).  Requires every K (per
 // segment), lda, ldb and the segment and member offsets to be multiples of
 // 32 elements (gl.k32); column tiles past n_out read a clamped, valid row and
 // their results are discarded.
-__device__ inline int lds_swz(int r) { return ((r >> 1) ^ (r >> 3)) & 3; }
+__device__ inline int lds_swz(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
 // s_waitcnt immediate: vmcnt = n (bits 3:0 and 15:14), expcnt and lgkmcnt
 // left at their maxima.
@@ -293,33 +293,42 @@ constexpr int vm_imm(int n) { return 0xF70 | (n & 15) | ((n >> 4) << 14); }
 // instructions per chunk) are outstanding; ahead is wave-uniform.
 template <int LOADS, int MAXA>
 __device__ inline void wait_chunks(int ahead) {
-  if (MAXA >= 3 && ahead >= 3) __builtin_amdgcn_s_waitcnt(vm_imm(3 * LOADS));
-  else if (MAXA >= 2 && ahead >= 2) __builtin_amdgcn_s_waitcnt(vm_imm(2 * LOADS));
-  else if (MAXA >= 1 && ahead >= 1) __builtin_amdgcn_s_waitcnt(vm_imm(LOADS));
-  else __builtin_amdgcn_s_waitcnt(vm_imm(0));
+  if constexpr (MAXA > 0) {
+    if (ahead < MAXA) {
+      wait_chunks<LOADS, MAXA - 1>(ahead);
+      return;
+    }
+  }
+  static_assert(MAXA * LOADS < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt(vm_imm(MAXA * LOADS));
 }
 
 // Bits 0, 2, 4, ... of x gathered into bits 0, 1, 2, ...
-__device__ inline unsigned long long even_bits(unsigned long long x) {
+__device__ inline unsigned even_bits(unsigned long long x) {
   x &= 0x5555555555555555ull;
   x = (x | (x >> 1)) & 0x3333333333333333ull;
   x = (x | (x >> 2)) & 0x0f0f0f0f0f0f0f0full;
   x = (x | (x >> 4)) & 0x00ff00ff00ff00ffull;
   x = (x | (x >> 8)) & 0x0000ffff0000ffffull;
-  return (x | (x >> 16)) & 0x00000000ffffffffull;
+  return (unsigned)(x | (x >> 16));
 }
 
 // 256-wide tiles hold 128 accumulator registers per lane; the kernel is
 // held to 256 registers in all so that two workgroups share a compute unit.
-// STAGES: depth of the operand ring; loads run STAGES - 1 chunks ahead.
+// The bounds also keep the accumulators in the vector registers: with more to
+// spare the compiler moves them to the accumulation registers and back around
+// the MFMAs of every chunk.
+// STAGES: depth of the operand ring; loads run STAGES - 1 chunks ahead.  Three:
+// a deeper ring leaves fewer workgroups on a compute unit and is slower (five
+// stages, two workgroups: 322 and 320 us in place of 280 and 298).
 template <int EPI, int TN, bool SPAN, int STAGES>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TN == 256 ? 2 : 1)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TN == 256 ? 2 : TN == 128 ? 3 : 4)))
 k_gemm_dl(GemmLaunch gl) {
   const float inv_alpha = 1.f / gl.alpha, k_exp = 1.4426950408889634f * inv_alpha;
   typedef uint16_t T;
   constexpr int TM = kTileM;
   constexpr int TK = 32;
-  static_assert(STAGES == 3, "ring depth: the first two chunks are issued unconditionally");
+  static_assert(STAGES >= 3, "ring depth: the first two chunks are issued unconditionally");
   constexpr int WM = TN == 64 ? 32 : 64;
   constexpr int WN = TN == 256 ? 128 : 64;
   constexpr int WAVES_N = TN / WN;
@@ -364,38 +373,93 @@ k_gemm_dl(GemmLaunch gl) {
   const T *B = (const T *)grp.B;
   const size_t ldb = grp.ldb ? (size_t)grp.ldb : (size_t)K * nseg;
 
-  // this thread's source rows and chunks (fixed over the K loop)
-  const T *asrc[A_LD];
-  const T *bsrc[B_LD];
+  // The AEV halves (16 columns) that some row of the tile may have non-zero
+  // (wave-uniform; all without the record).
+  // First layer: after the first chunks, a K chunk (two halves) is loaded only
+  // if one of its halves is live, and a half's MFMAs run only if it is; the
+  // skipped products are zero for every row.  The angular blocks of two halves
+  // are whole chunks (GemmLaunch::rad_gap).  Each wave loads the tile's row
+  // records (1 KB, two per lane) like the operands, ahead of chunk 0, into its
+  // own slots of the ring's last stage, which chunk 2 fills only after they
+  // are read.
+  // dE/dG: a column half no row has is read by no one; the live halves are
+  // the output columns, side by side, so that a tile of TN columns holds TN /
+  // 16 of them and the tiles past them leave at once.
+  // A box of water has 8 of 63 halves: on 100,002 atoms x 8 members the first
+  // layer took 294 us with blocks across two chunks and dE/dG 376 with
+  // 256-column tiles skipped whole; they take 259 and 297 so, and the first layer
+  // of 4,096 snapshots of 40 atoms 104 in place of 119.
+  constexpr bool kMaskK = EPI == kEpiFwd, kMaskN = EPI == kEpiOut;
+  const bool masked = gl.row_mask != nullptr && (kMaskN || (kMaskK && nseg == 1 && nk <= 32));
+  static_assert(TM == 2 * kWave && A_SLOTS >= 256, "two row records per lane, in the wave's A slots");
+  unsigned long long live_h = ~0ull;
+  // live halves of the rows of two records (records past the bucket's real
+  // rows are not the forward's)
+  auto live_of = [&](uint4 r) {
+    const int real = real_end - r0 - 2 * lane;
+    const unsigned h_lo = (real > 0 ? r.x : 0u) | (real > 1 ? r.z : 0u);
+    const unsigned h_hi = (real > 0 ? r.y : 0u) | (real > 1 ? r.w : 0u);
+    return ((unsigned long long)wave_or(h_hi) << 32) | wave_or(h_lo);
+  };
+  int n_live = 0, halves_in_order = 0;  // dE/dG, masked: live halves
+  bool some_dead = false;
+  if constexpr (kMaskN) {
+    if (masked) {
+      live_h = live_of(*(const uint4 *)(gl.row_mask + r0 + 2 * lane)) & (~0ull >> (64 - min(n_cols / 16, 64)));
+      n_live = __popcll(live_h);
+      if (c0 / 16 >= n_live) return;  // (every wave, no load to LDS in flight)
+      some_dead = n_live < n_cols / 16;
+      if (some_dead) halves_in_order = live_halves(live_h, lane);
+    }
+  }
+
+  // this thread's byte offsets of load q; with SPAN the members' weights lie
+  // apart, so B by pointers
+  unsigned aoff[A_LD], boff[B_LD];
+  const T *bsrc[SPAN ? B_LD : 1];
 #pragma unroll
   for (int q = 0; q < A_LD; ++q) {
     const int sl = q * 256 + tid, row = sl >> 2, kc = (sl & 3) ^ lds_swz(row);
-    asrc[q] = A + (size_t)row * gl.lda + kc * 8;
+    aoff[q] = (unsigned)(row * gl.lda + kc * 8) * 2u;
   }
 #pragma unroll
   for (int q = 0; q < B_LD; ++q) {
     const int sl = q * 256 + tid, row = sl >> 2, kc = (sl & 3) ^ lds_swz(row);
-    const int col = min(c0 + row, n_cols - 1);
-    if (SPAN) {
+    int col = min(c0 + row, n_cols - 1);
+    if (kMaskN && some_dead) col = 16 * half_at(halves_in_order, min((c0 + row) / 16, n_live - 1)) + (row & 15);
+    if constexpr (SPAN) {
       const int m = col / grp.n_out;
       bsrc[q] = (const T *)gl.g[m * gl.n_groups + s].B + (size_t)(col - m * grp.n_out) * ldb + kc * 8;
     } else {
-      bsrc[q] = B + (size_t)col * ldb + kc * 8;
+      boff[q] = (unsigned)(col * (int)ldb + kc * 8) * 2u;
     }
   }
-  auto issue = [&](int c, int stage) {
-    const int seg = c / nk, k0 = (c % nk) * TK;
-    const size_t ao = (size_t)seg * gl.a_seg_stride + k0, bo = (size_t)seg * K + k0;
+  // the 32 columns from k0 of segment seg
+  auto issue_at = [&](int seg, int k0, int stage) {
+    const char *a0 = (const char *)(A + (size_t)seg * gl.a_seg_stride + k0);
+    const size_t bk = (size_t)seg * K + k0;
 #pragma unroll
     for (int q = 0; q < A_LD; ++q)
-      __builtin_amdgcn_global_load_lds((const void *)(asrc[q] + ao),
+      __builtin_amdgcn_global_load_lds((const void *)(a0 + aoff[q]),
                                        (__attribute__((address_space(3))) void *)&smem[stage][q * 256 + wave * kWave],
                                        16, 0, 0);
 #pragma unroll
-    for (int q = 0; q < B_LD; ++q)
-      __builtin_amdgcn_global_load_lds((const void *)(bsrc[q] + bo),
+    for (int q = 0; q < B_LD; ++q) {
+      const void *src = SPAN ? (const void *)(bsrc[SPAN ? q : 0] + bk) : (const void *)((const char *)(B + bk) + boff[q]);
+      __builtin_amdgcn_global_load_lds(src,
                                        (__attribute__((address_space(3))) void *)&smem[stage][A_SLOTS + q * 256 + wave * kWave],
                                        16, 0, 0);
+    }
+  };
+  int i_seg = 0, i_k = 0, i_stage = 0;  // of the next chunk to issue
+  auto issue = [&]() {
+    issue_at(i_seg, i_k, i_stage);
+    i_k += TK;
+    if (i_k == K) {
+      i_k = 0;
+      ++i_seg;
+    }
+    i_stage = i_stage + 1 == STAGES ? 0 : i_stage + 1;
   };
 
   floatx16 acc[BM][BN];
@@ -404,46 +468,40 @@ k_gemm_dl(GemmLaunch gl) {
 #pragma unroll
     for (int j = 0; j < BN; ++j) acc[i][j] = floatx16{};
 
-  // The AEV halves (16 columns) that some row of the tile may have
-  // non-zero (wave-uniform; all without the record).  First layer: after
-  // the first chunks, a K chunk (halves 2c, 2c + 1) is loaded only if one
-  // of its halves is live, and a half's MFMAs run only if it is; the
-  // skipped products are zero for every row.  dE/dG: a column half no row
-  // has is read by no one and is not stored; a wave whose columns are all
-  // such runs no MFMAs.  Each wave loads the tile's row records (1 KB, two
-  // per lane) like the operands, ahead of chunk 0, into its own slots of the
-  // ring's last stage, which chunk 2 fills only after the records are read.
-  constexpr bool kMaskK = EPI == kEpiFwd, kMaskN = EPI == kEpiOut;
-  const bool masked = gl.row_mask != nullptr && (kMaskN || (kMaskK && nseg == 1 && nk <= 32));
-  static_assert(TM == 2 * kWave && A_SLOTS >= 256, "two row records per lane, in the wave's A slots");
-  if (masked)
+  if (kMaskK && masked)
     __builtin_amdgcn_global_load_lds((const void *)(gl.row_mask + r0 + 2 * lane),
                                      (__attribute__((address_space(3))) void *)&smem[STAGES - 1][wave * kWave],
                                      16, 0, 0);
-  // the first chunks go out in order (every call has at least STAGES - 1)
-  const int n_pro = STAGES - 1;
+  // the first chunks go out in order (every call has at least two), more of
+  // the ring where the chunks are known
+  constexpr int n_pro = 2;
 #pragma unroll
-  for (int q = 0; q < STAGES - 1; ++q) issue(q, q);
-  unsigned long long live_h = ~0ull;
-  // live K chunks after the first ones, in order (first layer, masked: one
-  // segment of at most 32 chunks), set with live_h
-  unsigned long long kc_issue = 0, kc_comp = 0;
+  for (int q = 0; q < n_pro; ++q) issue();
+  // live chunks past the first ones that are left to issue and to compute
+  // (first layer, masked: one segment of at most 32 chunks), set with live_h
+  unsigned left = 0, comp = 0;
   int total = kMaskK && masked ? n_pro : nk * nseg;  // masked first layer: until live_h is known
-  // chunk of the k-th issue (called for k = 0, 1, 2, ... in turn)
-  auto chunk_at = [&](int k) {
-    if (!(kMaskK && masked) || k < n_pro) return k;
-    const int cc = __builtin_ctzll(kc_issue);
-    kc_issue &= kc_issue - 1;
-    return cc;
+  int issued = n_pro;
+  // the next chunk, into its stage
+  auto issue_next = [&]() {
+    ++issued;
+    if (!(kMaskK && masked)) {
+      issue();
+      return;
+    }
+    issue_at(0, __builtin_ctz(left) * TK, i_stage);
+    left &= left - 1;
+    i_stage = i_stage + 1 == STAGES ? 0 : i_stage + 1;
   };
-  bool wave_live = true;  // whether any column half of this wave is live (dE/dG)
-  bool some_dead = false;  // whether a column half of the tile is not (dE/dG)
+  // whether this wave has a live column (dE/dG)
+  const bool wave_live = !(kMaskN && masked) || (c0 + wc * WN) / 16 < n_live;
 
+  int stage = 0;  // of chunk c
   for (int c = 0; c < total; ++c) {
     // this wave's loads of chunk c are done once at most those of the
     // chunks issued after it remain
-    wait_chunks<LOADS, STAGES - 2>(min(total - 1 - c, STAGES - 2));
-    if (masked && c == 0) {
+    wait_chunks<LOADS, STAGES - 2>(min(issued - 1 - c, STAGES - 2));
+    if (kMaskK && masked && c == 0) {
       // this wave's own record load preceded its chunk 0 loads, waited for
       // above (no barrier needed); the read waits for itself (a plain LDS
       // read here would make the compiler wait for every load in flight)
@@ -451,47 +509,29 @@ k_gemm_dl(GemmLaunch gl) {
       const unsigned ra =
           (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint4 *)&smem[STAGES - 1][wave * kWave + lane];
       asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r) : "v"(ra) : "memory");
-      // records past the bucket's real rows are not the forward's
-      const int real = real_end - r0 - 2 * lane;
-      const unsigned h_lo = (real > 0 ? r.x : 0u) | (real > 1 ? r.z : 0u);
-      const unsigned h_hi = (real > 0 ? r.y : 0u) | (real > 1 ? r.w : 0u);
-      live_h = ((unsigned long long)wave_or(h_hi) << 32) | wave_or(h_lo);
-      if (kMaskN) {
-        // a column tile without a live half: nothing to compute or store
-        // (every wave leaves here; the operand loads in flight land in this
-        // workgroup's LDS first)
-        const unsigned long long tile_h = (live_h >> (c0 / 16)) & ((1ull << (TN / 16 - 1) << 1) - 1);
-        if (tile_h == 0) {
-          __builtin_amdgcn_s_waitcnt(vm_imm(0));
-          return;
-        }
-        // every half of the column tile live: stores without the check
-        some_dead = tile_h != ((1ull << (TN / 16 - 1) << 1) - 1);
-        wave_live = ((live_h >> ((c0 + wc * WN) / 16)) & ((1ull << (WN / 16 - 1) << 1) - 1)) != 0;
-      } else {
-        kc_issue = even_bits(live_h | (live_h >> 1)) & (nk >= 64 ? ~0ull : (1ull << nk) - 1) &
-                   ~((1ull << n_pro) - 1);
-        kc_comp = kc_issue;
-        total = n_pro + __builtin_popcountll(kc_issue);
-      }
+      live_h = gapped(live_of(r), gl.rad_halves, gl.rad_gap);
+      left = even_bits(live_h | (live_h >> 1)) & (nk >= 32 ? ~0u : (1u << nk) - 1u) & ~((1u << n_pro) - 1u);
+      comp = left;
+      total = n_pro + __builtin_popcount(left);
     }
     // a plain barrier: LDS is coherent within the workgroup, every wave has
     // waited for its own part of chunk c above, and its reads of the stage
     // overwritten next were consumed (by MFMAs) before it got here; a full
     // __syncthreads() would also wait for the loads of later chunks
     __builtin_amdgcn_s_barrier();
-    // stage (c + STAGES - 1) % STAGES was last read for chunk c - 1, which
-    // every wave has finished (barrier above)
-    if (c + STAGES - 1 < total) issue(chunk_at(c + STAGES - 1), (c + STAGES - 1) % STAGES);
-    const uint4 *As = smem[c % STAGES];
+    // chunk c + STAGES - 1 takes the stage of chunk c - 1, which every wave has
+    // finished (barrier above)
+    while (issued < total && issued < c + STAGES) issue_next();
+    const uint4 *As = smem[stage];
+    stage = stage + 1 == STAGES ? 0 : stage + 1;
     const uint4 *Bs = As + A_SLOTS;
     // live halves of this chunk (first layer, masked)
     unsigned halves = 3u;
     if (kMaskK && masked) {
       int cc = c;
       if (c >= n_pro) {
-        cc = __builtin_ctzll(kc_comp);
-        kc_comp &= kc_comp - 1;
+        cc = __builtin_ctz(comp);
+        comp &= comp - 1;
       }
       halves = (unsigned)(live_h >> (2 * cc)) & 3u;
     }
@@ -532,8 +572,14 @@ k_gemm_dl(GemmLaunch gl) {
     for (int bi = 0; bi < BM; ++bi)
 #pragma unroll
       for (int bj = 0; bj < BN; ++bj) {
-        const int col = c0 + wc * WN + bj * 32 + l32;
-        if (col >= n_cols || (some_dead && !((live_h >> (col / 16)) & 1ull))) continue;
+        int col = c0 + wc * WN + bj * 32 + l32;
+        if (some_dead) {
+          const bool dead = col / 16 >= n_live;
+          col = 16 * half_at(halves_in_order, col / 16) + (l32 & 15);
+          if (dead) continue;
+        } else if (col >= n_cols) {
+          continue;
+        }
         float *out = (float *)gl.C + (size_t)(r0 + wr * WM + bi * 32 + 4 * hi) * gl.ldc + col;
 #pragma unroll
         for (int i = 0; i < 16; ++i) out[(size_t)(8 * (i / 4) + (i % 4)) * gl.ldc] = acc[bi][bj][i] * gl.scale;
@@ -593,9 +639,6 @@ k_gemm_dl(GemmLaunch gl) {
   }
 }
 
-// operand ring depth per tile width
-constexpr int kStages128 = 3, kStages256 = 3;
-
 template <int EPI, bool BF16>
 static void launch_t(GemmLaunch gl, int row_tiles, int tn, hipStream_t st) {
   // the blocks of one row tile (every column tile and member) form a chunk
@@ -605,12 +648,12 @@ static void launch_t(GemmLaunch gl, int row_tiles, int tn, hipStream_t st) {
   if (BF16 && gl.k32) {
     if constexpr (EPI == kEpiFwd) {
       if (gl.span) {
-        k_gemm_dl<EPI, 256, true, kStages256><<<blocks, 256, 0, st>>>(gl);
+        k_gemm_dl<EPI, 256, true, 3><<<blocks, 256, 0, st>>>(gl);
         return;
       }
     }
-    if (tn == 256) k_gemm_dl<EPI, 256, false, kStages256><<<blocks, 256, 0, st>>>(gl);
-    else if (tn == 128) k_gemm_dl<EPI, 128, false, kStages128><<<blocks, 256, 0, st>>>(gl);
+    if (tn == 256) k_gemm_dl<EPI, 256, false, 3><<<blocks, 256, 0, st>>>(gl);
+    else if (tn == 128) k_gemm_dl<EPI, 128, false, 3><<<blocks, 256, 0, st>>>(gl);
     else k_gemm_dl<EPI, 64, false, 3><<<blocks, 256, 0, st>>>(gl);
     return;
   }
@@ -655,12 +698,14 @@ void launch_gemm(int epi, bool bf16, GemmLaunch gl, int row_tiles, int max_n_out
   // members all read the same input, the members' columns side by side
   const bool wide_ok = gl.k32 && max_n_out >= 160;
   const bool span_ok = wide_ok && epi == kEpiFwd && gl.a_member_stride == 0 && gemm_span_uniform(gl);
-  // the tuned width, else: 256 for the AEV-gradient GEMM when that still
-  // gives several workgroups per compute unit; 128-wide column tiles when
-  // they waste little; else 64
+  // the tuned width, else 128-wide column tiles when they waste little, else
+  // 64; for the AEV-gradient GEMM 64 too while 128 would not give every
+  // compute unit a workgroup (2,001 atoms: 6.5 us with 64, 8.3 with 128, 10.6
+  // with 256; 512 ragged solutes 40, 37 and 41; 6,000 atoms x 8 members 46, 40
+  // and 45; 100,002 x 8 271, 298 and 388)
   const int t128 = (max_n_out + 127) / 128 * 128, t64 = (max_n_out + 63) / 64 * 64;
   int tn = tn_pref == 64 || tn_pref == 128 || tn_pref == 256 ? tn_pref
-         : wide_ok && epi == kEpiOut && row_tiles * ((max_n_out + 255) / 256) >= 2048 ? 256
+         : epi == kEpiOut && row_tiles * (t128 / 128) <= 256 ? 64
          : (t128 - max_n_out) * 4 <= max_n_out && t128 <= t64 + 32 ? 128 : 64;
   if (tn == 256 && !wide_ok) tn = 128;
   gl.span = tn == 256 && span_ok ? 1 : 0;

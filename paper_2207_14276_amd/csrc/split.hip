@@ -29,14 +29,16 @@
 namespace nnp {
 
 // ------------------------------------------------------------------ weights
-// Parts of src [rows][K] (row stride ld) into dst [rows][Kp / 32][3][32];
-// columns past K are zeros.
+// Parts of src [rows][K] (row stride ld) into dst [rows][Kp / 32][3][32], with
+// gap zero columns from column gap_at on; columns past those are zeros.
 __global__ void __launch_bounds__(256)
-k_split_weights(const float *__restrict__ src, int rows, int K, int ld, int Kp, uint16_t *__restrict__ dst) {
+k_split_weights(const float *__restrict__ src, int rows, int K, int ld, int Kp, int gap_at, int gap,
+                uint16_t *__restrict__ dst) {
   const size_t total = (size_t)rows * Kp;
   for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (size_t)gridDim.x * blockDim.x) {
     const int r = (int)(t / Kp), k = (int)(t - (size_t)r * Kp);
-    const float x = k < K ? src[(size_t)r * ld + k] : 0.f;
+    const int ks = k < gap_at ? k : k < gap_at + gap ? K : k - gap;
+    const float x = ks < K ? src[(size_t)r * ld + ks] : 0.f;
     const __bf16 p1 = (__bf16)x;
     const float a = x - (float)p1;
     const __bf16 p2 = (__bf16)a;
@@ -48,11 +50,12 @@ k_split_weights(const float *__restrict__ src, int rows, int K, int ld, int Kp, 
   }
 }
 
-void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, uint16_t *dst, hipStream_t st) {
+void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, int gap_at, int gap, uint16_t *dst,
+                          hipStream_t st) {
   const size_t total = (size_t)rows * Kp;
   if (total == 0) return;
   const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 4096);
-  k_split_weights<<<blocks, 256, 0, st>>>(src, rows, K, ld, Kp, dst);
+  k_split_weights<<<blocks, 256, 0, st>>>(src, rows, K, ld, Kp, gap_at, gap, dst);
 }
 
 // ------------------------------------------------------------- grouped GEMM
@@ -67,14 +70,14 @@ void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, uin
 // (weights as the first operand), so that a lane ends with four consecutive
 // columns of one row.
 //
-// 128 x 64 tiles (4 x 1 waves of 32 x 64: every activation is split by one
+// 128 x 128 tiles (4 x 1 waves of 32 x 128: every activation is split by one
 // wave only), two workgroups per compute unit.  16 x 64 tiles (1 x 4 waves of
 // 16 x 16) serve calls whose 128-row tiles would leave compute units idle: a
 // wave's chain of dependent MFMAs is an eighth as long, and the row tiles
 // without a real row are skipped.  Every output element sums its products in
 // the same order in both.
-__device__ inline int aswz(int r) { return (r >> 1) & 7; }
-__device__ inline int bswz(int r) { return ((r >> 1) ^ (r >> 3)) & 3; }
+__device__ inline int aswz(int r) { return (r ^ (r >> 1)) & 7; }
+__device__ inline int bswz(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
 constexpr int vm_count(int n) { return 0xF70 | (n & 15) | ((n >> 4) << 14); }
 // Waits until at most `ahead` chunks' loads of this wave are outstanding.
@@ -126,7 +129,8 @@ k_gemm_split(GemmLaunch gl) {
 
   // The 16-column halves of the AEV that some row of the tile has (see
   // GemmLaunch::row_mask): a chunk without one is not loaded in the first
-  // layer, a column block without one is not stored in the dE/dG product.
+  // layer; in the dE/dG product the live halves are the columns, side by side
+  // (8 of 63 in a box of water: 12,003 atoms x 8 members 195 -> 133 us).
   constexpr bool kMaskK = EPI == kEpiFwd, kMaskN = EPI == kEpiOut;
   unsigned long long live_h = ~0ull;
   const bool masked = gl.row_mask != nullptr && (kMaskN || (kMaskK && nseg == 1 && nk <= 32));
@@ -138,18 +142,24 @@ k_gemm_split(GemmLaunch gl) {
       h_hi |= (unsigned)(h >> 32);
     }
     live_h = ((unsigned long long)wave_or(h_hi) << 32) | wave_or(h_lo);
+    if (kMaskK) live_h = gapped(live_h, gl.rad_halves, gl.rad_gap);
   }
   bool wave_live = c0 + wc * 16 * CB < n_cols;
+  int n_live = 0, halves_in_order = 0;  // dE/dG, masked: live halves
+  bool some_dead = false;
   if (kMaskN && masked) {
-    const unsigned long long tile_h = (live_h >> (c0 / 16)) & ((1ull << (TN / 16)) - 1);
-    if (tile_h == 0) return;  // uniform over the workgroup, nothing issued yet
-    wave_live = wave_live && ((live_h >> ((c0 + wc * 16 * CB) / 16)) & ((1ull << CB) - 1)) != 0;
+    live_h &= ~0ull >> (64 - min(n_cols / 16, 64));
+    n_live = __popcll(live_h);
+    if (c0 / 16 >= n_live) return;  // uniform over the workgroup, nothing issued yet
+    wave_live = (c0 + wc * 16 * CB) / 16 < n_live;
+    some_dead = n_live < n_cols / 16;
+    if (some_dead) halves_in_order = live_halves(live_h, lane);
   }
 
   // uniform tile bases and this thread's byte offsets from them
   const char *A = (const char *)((const float *)gl.A + (size_t)r0 * gl.lda + (size_t)mb * gl.a_member_stride);
   const unsigned ldb = (unsigned)(nk * nseg) * (kPartChunk * 2);  // bytes of a row of B
-  const char *B = (const char *)grp.B + (size_t)c0 * ldb;
+  const char *B = (const char *)grp.B;
   unsigned aoff[A_LD], boff[B_LD];
 #pragma unroll
   for (int q = 0; q < A_LD; ++q) {
@@ -160,7 +170,9 @@ k_gemm_split(GemmLaunch gl) {
   for (int q = 0; q < B_LD; ++q) {
     const int sl = q * T + tid, part = sl / (TN * 4), row = (sl - part * (TN * 4)) >> 2, ch = (sl & 3) ^ bswz(row);
     // past the columns: a valid row, its results are not stored
-    boff[q] = (unsigned)min(row, n_cols - 1 - c0) * ldb + (part * 32 + ch * 8) * 2;
+    int col = min(c0 + row, n_cols - 1);
+    if (some_dead) col = 16 * half_at(halves_in_order, min((c0 + row) / 16, n_live - 1)) + (row & 15);
+    boff[q] = (unsigned)col * ldb + (part * 32 + ch * 8) * 2;
   }
   const bool loads_a = wave < A_WAVES;  // (wave-uniform)
   auto issue = [&](int c, int stage) {
@@ -274,9 +286,13 @@ k_gemm_split(GemmLaunch gl) {
   if (!wave_live) return;
 #pragma unroll
   for (int j = 0; j < CB; ++j) {
-    const int v16 = c0 + (wc * CB + j) * 16;  // wave-uniform
+    int v16 = c0 + (wc * CB + j) * 16;  // wave-uniform
+    if (some_dead) {
+      if (v16 / 16 >= n_live) continue;
+      v16 = 16 * __builtin_amdgcn_readfirstlane(half_at(halves_in_order, v16 / 16));
+    }
     // (a descriptor length may end inside a sixteen; it is a multiple of 4)
-    if (v16 + 4 * kq >= n_cols || (kMaskN && !((live_h >> (v16 / 16)) & 1ull))) continue;
+    if (v16 + 4 * kq >= n_cols) continue;
     const int om = gl.span ? v16 / grp.n_out : mb;
     const int col = v16 - (gl.span ? om * grp.n_out : 0) + 4 * kq;
     float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);

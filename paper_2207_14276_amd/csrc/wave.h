@@ -94,6 +94,21 @@ __device__ inline unsigned wave_or(unsigned v) {
   return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// The AEV's live halves as they lie in a first layer's input row: gap halves
+// follow the rad radial ones (GemmLaunch::rad_gap).
+__device__ inline unsigned long long gapped(unsigned long long live, int rad, int gap) {
+  const unsigned long long low = (1ull << rad) - 1;
+  return (live & low) | (live & ~low) << gap;
+}
+
+// Lane r: the r-th set bit of live (bit 63 is not set); and that bit for any
+// r, by every lane of the wave.  (In registers: a table in LDS would make the
+// compiler wait for all loads to LDS in flight before each read of operands.)
+__device__ inline int live_halves(unsigned long long live, int lane) {
+  return __builtin_amdgcn_ds_permute(((live >> lane) & 1ull ? (int)lanes_below(live) : 63) << 2, lane);
+}
+__device__ inline int half_at(int halves, int r) { return __builtin_amdgcn_ds_bpermute(r << 2, halves); }
+
 // Orders this wave's LDS writes before its later LDS reads by other lanes
 // (LDS requests of one wave are served in order; this only stops the
 // compiler from moving accesses across it).
