@@ -526,14 +526,14 @@ k_aev_fwd(const float4 *__restrict__ pos, const int *__restrict__ sys_of,
           const SysDesc *__restrict__ sys, const int2 *__restrict__ nbr,
           const int *__restrict__ nbr_cnt, int cap, const int *__restrict__ row_of_atom,
           void *__restrict__ G, int ldg, unsigned long long *__restrict__ row_mask,
-          const int *__restrict__ wave_atom, int *__restrict__ status, Live N_, AevConst c) {
+          const int *__restrict__ wave_atom, int *__restrict__ status, Live N_, int xcd_run, AevConst c) {
   extern __shared__ float4 lds4[];
   const int N = N_.get();
   // the wave index is uniform across the wave: keep it (and the centre's
   // index, descriptors and row pointers) in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
   constexpr int W = GROUP ? WPB : 1;  // waves per centre
-  const int wv = GROUP ? (int)blockIdx.x : blockIdx.x * WPB + wave;
+  const int wv = GROUP ? (int)blockIdx.x : xcd_chunked(blockIdx.x, xcd_run) * WPB + wave;
   const int i = wave_atom && wv < N ? __builtin_amdgcn_readfirstlane(wave_atom[wv]) : wv;
   // an atom without a network row (outside a caller's mask) is skipped
   const bool live = i < N && row_of_atom[i] >= 0;
@@ -1247,21 +1247,26 @@ static void aev_fwd_t(const float4 *pos, const int *sys_of, const SysDesc *sys, 
   if (group_centres(N.v, nbr != nullptr, wave_lds_bytes<false>(cap), max_lds)) {
     const size_t lds = wave_lds_bytes<false>(cap) + kGroupWaves * kPairPass * 24;
     k_aev_fwd<kGroupWaves, BF16, true><<<(unsigned)N.v, kGroupWaves * kWave, lds, st>>>(
-        pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg, row_mask, wave_atom, status, N, c);
+        pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg, row_mask, wave_atom, status, N, 1, c);
     return;
   }
+  // Runs of 256 centres on one XCD (their system's records and the neighbouring
+  // rows' masks stay in its L2) where there are enough rounds of waves to even
+  // out: 163,840 centres of 4,096 snapshots 821 -> 792 us per call, 100,002 of
+  // a box the same; 32,671 of ragged solutes, largest first, 218 -> 220.
   int wpb = waves_for_cap<false>(cap, wpb_pref);
+  const int run = N.v >= 65536 ? 256 / wpb : 1;
   size_t lds = wave_lds_bytes<false>(cap) * wpb;
-  unsigned grid = (unsigned)((N.v + wpb - 1) / wpb);
+  unsigned grid = xcd_grid((unsigned)((N.v + wpb - 1) / wpb), run);
   if (wpb == 4)
     k_aev_fwd<4, BF16, false><<<grid, 4 * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
-                                                            row_mask, wave_atom, status, N, c);
+                                                            row_mask, wave_atom, status, N, run, c);
   else if (wpb == 2)
     k_aev_fwd<2, BF16, false><<<grid, 2 * kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
-                                                            row_mask, wave_atom, status, N, c);
+                                                            row_mask, wave_atom, status, N, run, c);
   else
     k_aev_fwd<1, BF16, false><<<grid, kWave, lds, st>>>(pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg,
-                                                        row_mask, wave_atom, status, N, c);
+                                                        row_mask, wave_atom, status, N, run, c);
 }
 
 void launch_aev_fwd(const float4 *pos, const int *sys_of, const SysDesc *sys, const int2 *nbr,
