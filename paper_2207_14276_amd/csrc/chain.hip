@@ -242,12 +242,8 @@ k_chain(ChainLaunch cl, int n_hidden, int grad) {
   const int n_rt = cl.n_blocks / cl.n_members;
   const int mb = lb / n_rt;
   const int r0 = (lb - mb * n_rt) * R;
-  int s = -1, real_end = 0;
-  for (int q = 0; q < cl.n_groups; ++q)
-    if (r0 >= cl.bucket_off[q] && r0 < cl.bucket_off[q + 1]) {
-      s = q;
-      real_end = cl.bucket_off[q] + cl.bucket_cnt[q];
-    }
+  int real_end;
+  const int s = tile_bucket(cl.bucket_off, cl.bucket_cnt, cl.n_groups, r0, lane, real_end);
   if (s < 0 || r0 >= real_end) return;  // padding rows only: their gradients are not read
   const ChainNet &net = cl.nets[mb * cl.n_groups + s];
   auto tile = [&](int l) {  // offsets are of 16 rows

@@ -350,12 +350,9 @@ k_gemm_dl(GemmLaunch gl) {
   const int r0 = rt * TM;
   // the row tile's species bucket, and (with row records) where its real
   // rows end
-  int s = -1, real_end = 0;
-  for (int q = 0; q < gl.n_groups; ++q)
-    if (r0 >= gl.bucket_off[q] && r0 < gl.bucket_off[q + 1]) {
-      s = q;
-      if (gl.row_mask) real_end = gl.bucket_off[q] + gl.bucket_cnt[q];
-    }
+  int real_end;
+  const int s = tile_bucket(gl.bucket_off, gl.row_mask ? gl.bucket_cnt : nullptr, gl.n_groups, r0,
+                            threadIdx.x % kWave, real_end);
   if (s < 0) return;
   const GemmGroup grp = gl.g[mb * gl.n_groups + s];
   const int n_cols = SPAN ? grp.n_out * gl.n_members : grp.n_out;

@@ -110,12 +110,17 @@ k_gemm_split(GemmLaunch gl) {
   const int mb = gl.span ? 0 : (lb / n_ct) % gl.n_members;
   const int rt = gl.span ? lb / n_ct : lb / (n_ct * gl.n_members);
   const int r0 = rt * TM;
-  int s = -1, real_end = 0;
-  for (int q = 0; q < gl.n_groups; ++q)
-    if (r0 >= gl.bucket_off[q] && r0 < gl.bucket_off[q + 1]) {
-      s = q;
-      real_end = gl.bucket_off[q] + gl.bucket_cnt[q];
-    }
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  // (the rows' records, masked below, on their way meanwhile)
+  constexpr bool kMaskK = EPI == kEpiFwd, kMaskN = EPI == kEpiOut;
+  constexpr int H_LD = (TM + kWave - 1) / kWave;
+  unsigned long long row_h[H_LD];
+  if ((kMaskK || kMaskN) && gl.row_mask) {
+#pragma unroll
+    for (int q = 0; q < H_LD; ++q) row_h[q] = gl.row_mask[r0 + min(lane + q * kWave, TM - 1)];
+  }
+  int real_end;
+  const int s = tile_bucket(gl.bucket_off, gl.bucket_cnt, gl.n_groups, r0, lane, real_end);
   if (s < 0 || r0 >= real_end) return;  // no row of an atom in this tile
   const GemmGroup grp = gl.g[mb * gl.n_groups + s];
   const int n_cols = gl.span ? grp.n_out * gl.n_members : grp.n_out;
@@ -123,7 +128,6 @@ k_gemm_split(GemmLaunch gl) {
   if (c0 >= n_cols) return;
   const int K = grp.K, nseg = gl.n_seg, nk = K / TK;
 
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
   const int l16 = lane & 15, kq = lane >> 4;
   const int wr = wave / WC, wc = wave % WC;
 
@@ -131,15 +135,15 @@ k_gemm_split(GemmLaunch gl) {
   // GemmLaunch::row_mask): a chunk without one is not loaded in the first
   // layer; in the dE/dG product the live halves are the columns, side by side
   // (8 of 63 in a box of water: 12,003 atoms x 8 members 195 -> 133 us).
-  constexpr bool kMaskK = EPI == kEpiFwd, kMaskN = EPI == kEpiOut;
   unsigned long long live_h = ~0ull;
   const bool masked = gl.row_mask != nullptr && (kMaskN || (kMaskK && nseg == 1 && nk <= 32));
   if (masked) {
     unsigned h_lo = 0, h_hi = 0;
-    for (int r = lane; r < min(TM, real_end - r0); r += kWave) {
-      const unsigned long long h = gl.row_mask[r0 + r];
-      h_lo |= (unsigned)h;
-      h_hi |= (unsigned)(h >> 32);
+#pragma unroll
+    for (int q = 0; q < H_LD; ++q) {
+      const bool real = lane + q * kWave < min(TM, real_end - r0);
+      h_lo |= real ? (unsigned)row_h[q] : 0u;
+      h_hi |= real ? (unsigned)(row_h[q] >> 32) : 0u;
     }
     live_h = ((unsigned long long)wave_or(h_hi) << 32) | wave_or(h_lo);
     if (kMaskK) live_h = gapped(live_h, gl.rad_halves, gl.rad_gap);

@@ -27,6 +27,25 @@ __device__ inline float4 load4f(Global<float> p) {
   return make_float4(v[0], v[1], v[2], v[3]);
 }
 
+// The species bucket of the row tile at r0 (buckets are whole tiles), -1 past
+// the last, and in real_end where its rows of atoms end (cnt null: 0).  Lane q
+// looks at bucket q, so that a tile waits for memory once: read in turn, the
+// buckets were a chain of up to seven waits ahead of a tile's first load
+// (a 24-atom call's dE/dG and first layer 8.3 and 13.3 -> 7.9 and 12.7 us with
+// the rows' records loaded meanwhile; the chain of a 6,000-atom region with 8
+// members 45.2 -> 43.7, its first layer 34.4 -> 33.5).
+__device__ inline int tile_bucket(const int *off, const int *cnt, int n_groups, int r0, int lane, int &real_end) {
+  static_assert(kMaxSpecies <= kWave, "a lane per bucket");
+  const int q = min(lane, n_groups - 1);
+  const int from = off[q], to = off[q + 1], n = cnt ? cnt[q] : -from;
+  const unsigned long long m = __ballot(lane < n_groups && r0 >= from && r0 < to);
+  real_end = 0;
+  if (m == 0) return -1;
+  const int s = __builtin_ctzll(m);
+  real_end = __builtin_amdgcn_readlane(from + n, s);
+  return s;
+}
+
 // Hardware reciprocal and square root (about 1 ulp), in place of the
 // correctly rounded division and square-root sequences.
 __device__ inline float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
