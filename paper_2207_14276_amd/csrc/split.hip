@@ -74,8 +74,14 @@ void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, int
 // wave only), two workgroups per compute unit.  16 x 64 tiles (1 x 4 waves of
 // 16 x 16) serve calls whose 128-row tiles would leave compute units idle: a
 // wave's chain of dependent MFMAs is an eighth as long, and the row tiles
-// without a real row are skipped.  Every output element sums its products in
-// the same order in both.
+// without a real row are skipped.  Where there are at most 256 of them, one per
+// compute unit, they take STEP = 2 chunks per barrier from a ring of eight: a
+// chunk is then bound by its chain of LDS reads, splitting and five dependent
+// MFMAs (0.39 us), and two chunks' reads and splitting run beside each other.
+// First layer of a call of 24 atoms 12.7 -> 11.7 us, of 101 atoms 20.3 -> 17.3;
+// with the ring of eight alone 14.2, with more workgroups the 112 KB of LDS
+// would leave one of them where two fit.  Every output element sums its
+// products in the same order in all.
 __device__ inline int aswz(int r) { return (r ^ (r >> 1)) & 7; }
 __device__ inline int bswz(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
@@ -83,13 +89,14 @@ constexpr int vm_count(int n) { return 0xF70 | (n & 15) | ((n >> 4) << 14); }
 // Waits until at most `ahead` chunks' loads of this wave are outstanding.
 template <int LOADS, int MAXA>
 __device__ inline void wait_ahead(int ahead) {
-  if (MAXA >= 3 && ahead >= 3) __builtin_amdgcn_s_waitcnt(vm_count(3 * LOADS));
+  if (MAXA >= 4 && ahead >= 4) __builtin_amdgcn_s_waitcnt(vm_count(4 * LOADS));
+  else if (MAXA >= 3 && ahead >= 3) __builtin_amdgcn_s_waitcnt(vm_count(3 * LOADS));
   else if (MAXA >= 2 && ahead >= 2) __builtin_amdgcn_s_waitcnt(vm_count(2 * LOADS));
   else if (MAXA >= 1 && ahead >= 1) __builtin_amdgcn_s_waitcnt(vm_count(LOADS));
   else __builtin_amdgcn_s_waitcnt(vm_count(0));
 }
 
-template <int EPI, int HR, int CB, int WR, int WC, int STAGES>
+template <int EPI, int HR, int CB, int WR, int WC, int STAGES, int STEP>
 __global__ void __launch_bounds__(WR * WC * kWave, 2)
 k_gemm_split(GemmLaunch gl) {
   constexpr int TM = 16 * HR * WR, TN = 16 * CB * WC, T = WR * WC * kWave, TK = 32;
@@ -216,20 +223,11 @@ k_gemm_split(GemmLaunch gl) {
     todo &= todo - 1;
     return c;
   };
-  for (int q = 0; q < STAGES - 1; ++q)
+  for (int q = 0; q < STAGES - STEP; ++q)
     if (q < total) issue(next(q), q);
 
-  for (int c = 0; c < total; ++c) {
-    if (A_WAVES == WR * WC || loads_a) wait_ahead<A_LD + B_LD, STAGES - 2>(min(total - 1 - c, STAGES - 2));
-    else wait_ahead<B_LD, STAGES - 2>(min(total - 1 - c, STAGES - 2));
-    // every wave has its part of chunk c and is done with chunk c - 1, whose
-    // stage the next issue fills
-    __builtin_amdgcn_s_barrier();
-    if (c + STAGES - 1 < total) issue(next(c + STAGES - 1), (c + STAGES - 1) % STAGES);
-    const uint4 *As = split_lds + (c % STAGES) * (A_SLOTS + B_SLOTS);
-    const uint4 *Bs = As + A_SLOTS;
-    if (!wave_live) continue;
-    Parts a[HR];
+  // This wave's activations of chunk c (its stage's A slots), and the largest magnitude.
+  auto take_a = [&](const uint4 *As, Parts (&a)[HR]) {
     float big = 0.f;
 #pragma unroll
     for (int h = 0; h < HR; ++h) {
@@ -243,44 +241,101 @@ k_gemm_split(GemmLaunch gl) {
       big = fmaxf(big, r0 + r < real_end ? max8(x) : 0.f);
       a[h] = split8(x);
     }
-    // block j's fragment of part p: slot(j)[4 TN p] (the XOR of a row depends
-    // on its block's parity alone)
-    const uint4 *be = Bs + 4 * ((wc * CB) * 16 + l16);
-    const int xe = kq ^ bswz((wc * CB) * 16 + l16), xo = kq ^ bswz((wc * CB + 1) * 16 + l16);
-    auto slot = [&](int j) { return be + 64 * j + (j & 1 ? xo : xe); };
-    if (__ballot(big > kPartMax) == 0) {
+    return __ballot(big > kPartMax) != 0;
+  };
+  // block j's fragment of part p: slot(j)[4 TN p] (the XOR of a row depends
+  // on its block's parity alone)
+  const int br = (wc * CB) * 16 + l16;
+  const int xe = kq ^ bswz(br), xo = kq ^ bswz(br + 16);
+  auto slot = [&](const uint4 *As, int j) { return As + A_SLOTS + 4 * br + 64 * j + (j & 1 ? xo : xe); };
+  auto take_b = [&](const uint4 *As, int j, bf16x8 (&w)[3]) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) w[p] = __builtin_bit_cast(bf16x8, slot(As, j)[4 * TN * p]);
+  };
+  auto products = [&](const Parts (&a)[HR], const bf16x8 (&w)[3], int j) {
+#pragma unroll
+    for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[0], a[h].p3, low[h][j], 0, 0, 0);
+#pragma unroll
+    for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[2], a[h].p1, low[h][j], 0, 0, 0);
+#pragma unroll
+    for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[1], a[h].p2, low[h][j], 0, 0, 0);
+#pragma unroll
+    for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[0], a[h].p2, low[h][j], 0, 0, 0);
+#pragma unroll
+    for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[1], a[h].p1, low[h][j], 0, 0, 0);
+#pragma unroll
+    for (int h = 0; h < HR; ++h) acc[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[0], a[h].p1, acc[h][j], 0, 0, 0);
+  };
+  // a chunk on the float32 instruction
+  auto products32 = [&](const uint4 *As) {
+#pragma unroll 1
+    for (int k = 0; k < 8; ++k) {
 #pragma unroll
       for (int j = 0; j < CB; ++j) {
-        const bf16x8 b1 = __builtin_bit_cast(bf16x8, slot(j)[0]);
-        const bf16x8 b2 = __builtin_bit_cast(bf16x8, slot(j)[4 * TN]);
-        const bf16x8 b3 = __builtin_bit_cast(bf16x8, slot(j)[8 * TN]);
+        const float b = joined((const uint16_t *)slot(As, j) + k, 32 * TN);
 #pragma unroll
-        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a[h].p3, low[h][j], 0, 0, 0);
-#pragma unroll
-        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b3, a[h].p1, low[h][j], 0, 0, 0);
-#pragma unroll
-        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b2, a[h].p2, low[h][j], 0, 0, 0);
-#pragma unroll
-        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a[h].p2, low[h][j], 0, 0, 0);
-#pragma unroll
-        for (int h = 0; h < HR; ++h) low[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b2, a[h].p1, low[h][j], 0, 0, 0);
-#pragma unroll
-        for (int h = 0; h < HR; ++h) acc[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a[h].p1, acc[h][j], 0, 0, 0);
-      }
-    } else {
-#pragma unroll 1
-      for (int k = 0; k < 8; ++k) {
-#pragma unroll
-        for (int j = 0; j < CB; ++j) {
-          const float b = joined((const uint16_t *)slot(j) + k, 32 * TN);
-#pragma unroll
-          for (int h = 0; h < HR; ++h) {
-            const int r = (wr * HR + h) * 16 + l16;
-            const float x = ((const float *)&As[8 * r + ((2 * kq + (k >> 2)) ^ aswz(r))])[k & 3];
-            acc[h][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b, x, acc[h][j], 0, 0, 0);
-          }
+        for (int h = 0; h < HR; ++h) {
+          const int r = (wr * HR + h) * 16 + l16;
+          const float x = ((const float *)&As[8 * r + ((2 * kq + (k >> 2)) ^ aswz(r))])[k & 3];
+          acc[h][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b, x, acc[h][j], 0, 0, 0);
         }
       }
+    }
+  };
+
+  for (int c = 0; c < total; c += STEP) {
+    constexpr int MAXA = STAGES - 2 * STEP;
+    if (A_WAVES == WR * WC || loads_a) wait_ahead<A_LD + B_LD, MAXA>(min(total - STEP - c, MAXA));
+    else wait_ahead<B_LD, MAXA>(min(total - STEP - c, MAXA));
+    // every wave has its part of these chunks and is done with the STEP before
+    // them, whose stages the next issues fill
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int q = 0; q < STEP; ++q)
+      if (c + STAGES - STEP + q < total) issue(next(c + STAGES - STEP + q), (c + STAGES - STEP + q) % STAGES);
+    const uint4 *As = split_lds + (c % STAGES) * (A_SLOTS + B_SLOTS);
+    if (!wave_live) continue;
+    if (STEP == 2 && c + 1 < total) {
+      const uint4 *An = split_lds + ((c + 1) % STAGES) * (A_SLOTS + B_SLOTS);
+      Parts a[HR], an[HR];
+      bf16x8 w[CB][3], wn[CB][3];
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        take_b(As, j, w[j]);
+        take_b(An, j, wn[j]);
+      }
+      const bool wide = take_a(As, a), wide_n = take_a(An, an);
+      if (!wide && !wide_n) {
+#pragma unroll
+        for (int j = 0; j < CB; ++j) products(a, w[j], j);
+#pragma unroll
+        for (int j = 0; j < CB; ++j) products(an, wn[j], j);
+      } else {
+        if (wide) {
+          products32(As);
+        } else {
+#pragma unroll
+          for (int j = 0; j < CB; ++j) products(a, w[j], j);
+        }
+        if (wide_n) {
+          products32(An);
+        } else {
+#pragma unroll
+          for (int j = 0; j < CB; ++j) products(an, wn[j], j);
+        }
+      }
+      continue;
+    }
+    Parts a[HR];
+    if (!take_a(As, a)) {
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        bf16x8 w[3];
+        take_b(As, j, w);
+        products(a, w, j);
+      }
+    } else {
+      products32(As);
     }
   }
 
@@ -321,14 +376,14 @@ k_gemm_split(GemmLaunch gl) {
   }
 }
 
-template <int EPI, int HR, int CB, int WR, int WC, int STAGES>
+template <int EPI, int HR, int CB, int WR, int WC, int STAGES, int STEP>
 static void gemm_split_t(GemmLaunch gl, int rows, int cols, hipStream_t st) {
   constexpr int TM = 16 * HR * WR, TN = 16 * CB * WC;
   gl.col_tiles = (cols + TN - 1) / TN;
   gl.xcd_chunk = (gl.span ? 1 : gl.n_members) * gl.col_tiles;
   gl.n_blocks = rows / TM * gl.xcd_chunk;
   const size_t lds = (size_t)STAGES * (TM * 8 + TN * 12) * 16;
-  k_gemm_split<EPI, HR, CB, WR, WC, STAGES>
+  k_gemm_split<EPI, HR, CB, WR, WC, STAGES, STEP>
       <<<xcd_grid((unsigned)gl.n_blocks, gl.xcd_chunk), WR * WC * kWave, lds, st>>>(gl);
 }
 
@@ -342,9 +397,12 @@ void launch_gemm_split(int epi, GemmLaunch gl, int rows, int max_n_out, int tn_p
   if (gl.span) cols *= gl.n_members;
   const long long big = (long long)(rows / 128) * ((cols + 127) / 128) * (gl.span ? 1 : gl.n_members);
   const bool small = tn_pref == 64 || (tn_pref != 128 && tn_pref != 256 && big < 256);
-#define NNP_SPLIT(E)                                                  \
-  if (small) gemm_split_t<E, 1, 1, 1, 4, 4>(gl, rows, cols, st);      \
-  else gemm_split_t<E, 2, 8, 4, 1, 2>(gl, rows, cols, st)
+  // a workgroup per compute unit at most (see above)
+  const bool lone = small && (long long)(rows / 16) * ((cols + 63) / 64) * (gl.span ? 1 : gl.n_members) <= 256;
+#define NNP_SPLIT(E)                                                    \
+  if (lone) gemm_split_t<E, 1, 1, 1, 4, 8, 2>(gl, rows, cols, st);      \
+  else if (small) gemm_split_t<E, 1, 1, 1, 4, 4, 1>(gl, rows, cols, st); \
+  else gemm_split_t<E, 2, 8, 4, 1, 2, 1>(gl, rows, cols, st)
   if (epi == kEpiFwd) { NNP_SPLIT(kEpiFwd); }
   else if (epi == kEpiBwd) { NNP_SPLIT(kEpiBwd); }
   else { NNP_SPLIT(kEpiOut); }
