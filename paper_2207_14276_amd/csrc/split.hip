@@ -78,7 +78,7 @@ void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, int
 // compute unit, they take STEP = 2 chunks per barrier from a ring of eight: a
 // chunk is then bound by its chain of LDS reads, splitting and five dependent
 // MFMAs (0.39 us), and two chunks' reads and splitting run beside each other.
-// First layer of a call of 24 atoms 12.7 -> 11.7 us, of 101 atoms 20.3 -> 17.3;
+// First layer of a call of 24 atoms 13.0 -> 11.6 us, of 101 atoms 20.1 -> 17.5;
 // with the ring of eight alone 14.2, with more workgroups the 112 KB of LDS
 // would leave one of them where two fit.  Every output element sums its
 // products in the same order in all.

@@ -31,7 +31,7 @@ __device__ inline float4 load4f(Global<float> p) {
 // the last, and in real_end where its rows of atoms end (cnt null: 0).  Lane q
 // looks at bucket q, so that a tile waits for memory once: read in turn, the
 // buckets were a chain of up to seven waits ahead of a tile's first load
-// (a 24-atom call's dE/dG and first layer 8.3 and 13.3 -> 7.9 and 12.7 us with
+// (a 24-atom call's dE/dG and first layer 8.4 and 13.6 -> 7.9 and 13.0 us with
 // the rows' records loaded meanwhile; the chain of a 6,000-atom region with 8
 // members 45.2 -> 43.7, its first layer 34.4 -> 33.5).
 __device__ inline int tile_bucket(const int *off, const int *cnt, int n_groups, int r0, int lane, int &real_end) {
