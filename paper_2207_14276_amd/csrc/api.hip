@@ -323,6 +323,45 @@ static int create_dp_impl(const nnp_dp_model_desc *dd, nnp_model *m) {
   return create_networks(&net, m);
 }
 
+// Whether a float32 model's dense layers may run on the three bfloat16 parts of
+// their operands (split.hip) without losing what float32 operands keep.
+//   - Hidden widths are whole 32-column chunks.
+//   - Every hidden weight is a multiple of 2^-126, the smallest normal
+//     bfloat16, so that its parts add up to it (24 bits are three times 8);
+//     any weight of at least 2^-102 is one.
+//   - Every network's gain, the product over its layers of max(1, n max |w|) for
+//     the larger width n, is at most 2^64.  An activation or gradient below
+//     2^-102 loses less than 2^-125 with its parts below 2^-126, so that no
+//     energy, and no dE/dG, is off by more than about 2^-60 for it; and no
+//     gradient comes near the largest float.
+//   - Biases are finite, and below a rounding of the largest float.
+// Other models run on the float32 matrix instructions.
+static bool parts_suffice(const nnp_model *m, const float *w) {
+  if (m->L < 2) return false;
+  for (int s = 0; s < m->S; ++s)
+    for (int l = 1; l < m->L; ++l)
+      if (m->widths[s][l] % 32 != 0) return false;
+  for (int mb = 0; mb < m->M; ++mb)
+    for (int s = 0; s < m->S; ++s) {
+      double gain = 1.0;
+      for (int l = 0; l < m->L; ++l) {
+        const int n_in = m->widths[s][l], n_out = m->widths[s][l + 1];
+        float largest = 0.f;
+        for (size_t k = 0; k < (size_t)n_in * n_out; ++k) {
+          const float a = std::fabs(*w++);
+          if (!(a <= 3.3895314e38f)) return false;
+          if (l + 1 < m->L && a < 0x1p-102f && std::fmod((double)a, 0x1p-126) != 0.0) return false;
+          largest = std::max(largest, a);
+        }
+        gain *= std::max(1.0, (double)largest * std::max(n_in, n_out));
+        for (int k = 0; k < n_out; ++k)
+          if (!(std::fabs(*w++) <= 3.3895314e38f)) return false;
+      }
+      if (gain > 0x1p64) return false;
+    }
+  return true;
+}
+
 static int create_networks(const NetArgs *d, nnp_model *m) {
   if (d->n_ensemble < 1) return fail(NNP_EINVAL, "n_ensemble must be >= 1");
   if (d->n_ensemble > kMaxMembers) return fail(NNP_EUNSUPPORTED, "at most %d ensemble members", kMaxMembers);
@@ -368,22 +407,7 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
   }
   m->layers.resize((size_t)m->M * S * L);
   const float *wp = d->weights;
-  // float32 on the bfloat16 matrix cores: hidden widths that are whole
-  // 32-column chunks, weights with a finite first part (below a rounding of
-  // the largest float)
-  if (m->precision == NNP_FP32 && L >= 2) {
-    size_t nw = 0;
-    bool ok = true;
-    for (int s = 0; s < S; ++s)
-      for (int l = 0; l < L; ++l) {
-        nw += (size_t)m->widths[s][l + 1] * (m->widths[s][l] + 1);
-        ok = ok && (l + 1 == L || m->widths[s][l + 1] % 32 == 0);
-      }
-    nw *= m->M;
-    bool finite = true;
-    for (size_t k = 0; k < nw; ++k) finite &= std::fabs(wp[k]) <= 3.3895314e38f;
-    m->split = ok && finite;
-  }
+  if (m->precision == NNP_FP32) m->split = parts_suffice(m, wp);
   // the first layer's padded rows (bfloat16 and split models) have the zero
   // columns after the radial part where its length is no multiple of 32 (it
   // is of 16): the angular blocks are whole chunks then

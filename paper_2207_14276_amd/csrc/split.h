@@ -74,8 +74,8 @@ __device__ inline float max8(const float (&x)[8]) {
 }
 constexpr float kPartMax = 3.3895314e38f;  // largest finite bfloat16: above it the first part may overflow
 
-// A value from its parts, `stride` elements apart (exact: the parts are its own
-// bits).
+// A value from its parts, `stride` elements apart (exact for what the parts
+// hold: all bits of a weight, and of an activation of at least 2^-102).
 template <class P>
 __device__ inline float joined(P p, int stride) {
   const float a = __uint_as_float((uint32_t)p[0] << 16), b = __uint_as_float((uint32_t)p[stride] << 16);

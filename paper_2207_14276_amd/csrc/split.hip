@@ -1,10 +1,13 @@
 // Dense layers of the float32 model on the bfloat16 matrix cores.
 //
-// A float32 operand x is taken as three bfloat16 parts, x = p1 + p2 + p3 (each
-// part the rounding of what the earlier ones leave; 3 x 8 significant bits, so
-// the remainder is below 2^-26 |x|), and a product x w as the six part
-// products down to 2^-18: p1 w1, p1 w2, p2 w1, p2 w2, p1 w3, p3 w1.  Each of
-// them is exact in the matrix core's float32 accumulation; p1 w1 sums in one
+// A float32 operand x is taken as three bfloat16 parts, x = p1 + p2 + p3, each
+// part the rounding of what the earlier ones leave.  Their 3 x 8 significant
+// bits are all of x for |x| >= 2^-102, where no part falls below the smallest
+// normal bfloat16, 2^-126; below, less than 2^-125 of x is lost.  (Models
+// where that could count stay on float32 operands, see below.)  A product x w
+// is the six part products down to 2^-18: p1 w1, p1 w2, p2 w1, p2 w2, p1 w3,
+// p3 w1; the three left out are below 2^-26 |x w|.  Each of the six is exact
+// in the matrix core's float32 accumulation; p1 w1 sums in one
 // accumulator and the five small ones in a second, added at the end.  The six
 // v_mfma_f32_16x16x32_bf16 take 6/16 of the time of the float32 MFMAs they
 // replace, and the main sum is rounded once per 32 products instead of once
@@ -18,8 +21,10 @@
 // a rounding of the largest float) takes its products on the float32 matrix
 // instruction instead, with the weights put together again from their parts
 // (exact), so that overflows come out as they do there.  Models whose weights
-// are not finite, or whose widths leave a partial 32-column chunk, stay on
-// the float32 kernels of mlp.hip.
+// are not finite, are not whole multiples of 2^-126, or are so large that what
+// the smallest activations lose could grow to count (parts_suffice in api.hip),
+// or whose widths leave a partial 32-column chunk, stay on the float32 kernels
+// of mlp.hip.
 #include "internal.h"
 #include "split.h"
 #include "wave.h"
