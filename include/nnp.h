@@ -307,6 +307,11 @@ int nnp_debug_neighbors(nnp_model *model, int n_systems, const int64_t *batch_of
                         const float *coords, const int32_t *species, const float *box,
                         int32_t *counts, int32_t *entries, int capacity, void *stream);
 
+/* The form of the model's dense layers: 1 if float32 layers run on bfloat16
+ * parts of their operands (see split.hip for which models can), plus 2 if the
+ * layers after the first run fused; a negative code for a null model. */
+int nnp_debug_dense(const nnp_model *model);
+
 /* ------------------------------------------------------------------------
  * Serving: continuous batching of energy/force requests (a request is one
  * system and a number of successive evaluations, as an MD client or a

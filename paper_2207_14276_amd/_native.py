@@ -89,7 +89,7 @@ class nnp_server_counters(C.Structure):
 
 EXPORTS = ["nnp_create", "nnp_destroy", "nnp_reserve", "nnp_energy_forces", "nnp_debug_aev",
            "nnp_energy_forces_noalloc",
-           "nnp_debug_neighbors", "nnp_status", "nnp_aev_dim", "nnp_last_error",
+           "nnp_debug_neighbors", "nnp_debug_dense", "nnp_status", "nnp_aev_dim", "nnp_last_error",
            "nnp_set_timing", "nnp_stage_timings", "nnp_nlist_create", "nnp_nlist_destroy",
            "nnp_energy_forces_nlist", "nnp_nlist_builds", "nnp_autotune", "nnp_tuning",
            "nnp_energy_forces_pairs", "nnp_bar", "nnp_create_dp",
@@ -123,6 +123,7 @@ def load():
     lib.nnp_energy_forces_noalloc.argtypes = [vp, C.c_int, i64p, vp, vp, fp, vp, vp, vp, vp, vp]
     lib.nnp_debug_aev.argtypes = [vp, C.c_int, i64p, vp, vp, fp, vp, vp]
     lib.nnp_debug_neighbors.argtypes = [vp, C.c_int, i64p, vp, vp, fp, vp, vp, C.c_int, vp]
+    lib.nnp_debug_dense.argtypes = [vp]
     lib.nnp_status.argtypes = [vp, vp, C.POINTER(C.c_int)]
     lib.nnp_aev_dim.argtypes = [vp]
     lib.nnp_last_error.restype = C.c_char_p

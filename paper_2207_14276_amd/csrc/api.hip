@@ -334,7 +334,8 @@ static int create_dp_impl(const nnp_dp_model_desc *dd, nnp_model *m) {
 //     2^-102 loses less than 2^-125 with its parts below 2^-126, so that no
 //     energy, and no dE/dG, is off by more than about 2^-60 for it; and no
 //     gradient comes near the largest float.
-//   - Biases are finite, and below a rounding of the largest float.
+//   - Biases are finite; they are added in float32, and where they make an
+//     activation that has no finite first part, its products are float32 ones.
 // Other models run on the float32 matrix instructions.
 static bool parts_suffice(const nnp_model *m, const float *w) {
   if (m->L < 2) return false;
@@ -349,13 +350,13 @@ static bool parts_suffice(const nnp_model *m, const float *w) {
         float largest = 0.f;
         for (size_t k = 0; k < (size_t)n_in * n_out; ++k) {
           const float a = std::fabs(*w++);
-          if (!(a <= 3.3895314e38f)) return false;
+          if (!std::isfinite(a)) return false;
           if (l + 1 < m->L && a < 0x1p-102f && std::fmod((double)a, 0x1p-126) != 0.0) return false;
           largest = std::max(largest, a);
         }
         gain *= std::max(1.0, (double)largest * std::max(n_in, n_out));
         for (int k = 0; k < n_out; ++k)
-          if (!(std::fabs(*w++) <= 3.3895314e38f)) return false;
+          if (!std::isfinite(*w++)) return false;
       }
       if (gain > 0x1p64) return false;
     }
@@ -1702,6 +1703,11 @@ extern "C" int nnp_debug_neighbors(nnp_model *m, int n_systems, const int64_t *o
   o.nb_entries = entries;
   o.nb_cap = capacity;
   return run(m, n_systems, offs, coords, species, box, o, (hipStream_t)stream, kNbr);
+}
+
+extern "C" int nnp_debug_dense(const nnp_model *m) {
+  if (!m) return fail(NNP_EINVAL, "null model");
+  return (m->split ? 1 : 0) | (m->chain ? 2 : 0);
 }
 
 extern "C" int nnp_autotune(nnp_model *m, int n_systems, const int64_t *offs, const float *coords,

@@ -258,6 +258,13 @@ class NNPModel:
                 _stream_handle(self.device)))
         return cnt, ent
 
+    def dense_form(self) -> str:
+        """How the dense layers run: "plain" (operands as they are) or "parts"
+        (float32 operands as bfloat16 parts), with "+chain" where the layers
+        after the first are fused."""
+        form = nat.check(nat.load().nnp_debug_dense(self._h))
+        return ("parts" if form & 1 else "plain") + ("+chain" if form & 2 else "")
+
     STAGES = ("ingest", "cells", "neighbours", "buckets", "aev_fwd", "mlp", "aev_bwd", "reduce")
 
     def set_timing(self, on: bool = True, stage: str = None):
