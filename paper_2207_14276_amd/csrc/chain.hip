@@ -77,16 +77,17 @@ struct ChainTile {
   int plane;    // elements between planes
 };
 
-// Four consecutive elements of a row: 8 bytes in each plane.  P = 3: a value
-// without a finite first part keeps its leading bits there (an infinity
-// nothing else), so that its parts still add up to it, and is reported.
+// Four consecutive elements of a row: 8 bytes in each plane.  P = 3,
+// activations (huge given): a value without a finite first part keeps its
+// leading bits there (an infinity nothing else), so that its parts still add up
+// to it, and is reported.  (Gradients do not come near it, see split.hip.)
 template <int P>
-__device__ inline void put4(const ChainTile &t, int row, int col, float (&x)[4], bool &huge) {
+__device__ inline void put4(const ChainTile &t, int row, int col, float (&x)[4], bool *huge = nullptr) {
   uint16_t *d = t.p + row * t.ld + col;
-  if (P == 3) {
+  if (P == 3 && huge) {
     const bool b = fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))) > kPartMax;
     if (__builtin_expect(__ballot(b) != 0, 0)) {
-      huge = huge || b;
+      *huge = *huge || b;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float v = x[k];
@@ -281,14 +282,14 @@ k_chain(ChainLaunch cl, int n_hidden, int grad) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  // P = 3: whether a tile (h_l, then d_l) holds a value without a finite first part
-  __shared__ int huge_tile[2][kChainMax + 1];
+  // P = 3: whether h_l holds a value without a finite first part
+  __shared__ int huge_tile[kChainMax + 1];
   if (P == 3) {
-    if (tid < 2 * (kChainMax + 1)) (&huge_tile[0][0])[tid] = 0;
+    if (tid <= kChainMax) huge_tile[tid] = 0;
     lds_barrier();
   }
-  auto report = [&](int d, int l, bool huge) {
-    if (P == 3 && __builtin_expect(__ballot(huge) != 0, 0)) huge_tile[d][l] = 1;
+  auto report = [&](int l, bool huge) {
+    if (P == 3 && __builtin_expect(__ballot(huge) != 0, 0)) huge_tile[l] = 1;
   };
 
   Layer cur = layer(1);
@@ -314,11 +315,11 @@ k_chain(ChainLaunch cl, int n_hidden, int grad) {
           const float4 v = r0 + row < real_end ? *(const float4 *)(src + (size_t)row * cl.ldh + ch)
                                                : make_float4(0.f, 0.f, 0.f, 0.f);
           float x[4] = {v.x, v.y, v.z, v.w};
-          put4<P>(t0, row, ch, x, huge);
+          put4<P>(t0, row, ch, x, &huge);
         }
       }
     }
-    report(0, 0, huge);
+    report(0, huge);
   }
   lds_barrier();
 
@@ -346,7 +347,7 @@ k_chain(ChainLaunch cl, int n_hidden, int grad) {
         if (P == 3) acc.low[q][h] = floatx4{0.f, 0.f, 0.f, 0.f};
       }
     }
-    const bool plain = P == 1 || __builtin_amdgcn_readfirstlane(huge_tile[fwd ? 0 : 1][l_in]) == 0;
+    const bool plain = P == 1 || !fwd || __builtin_amdgcn_readfirstlane(huge_tile[l_in]) == 0;
     if (plain) {
       const Global<uint16_t> wp = frags(cur, 0);
 #define NNP_CHAIN_K(NKB)                                                                       \
@@ -406,11 +407,11 @@ k_chain(ChainLaunch cl, int n_hidden, int grad) {
           if (P == 3 && ph == 2 * n_hidden)  // d_0 straight to memory
             *(float4 *)(d0 + (size_t)row * cl.ldd + col) = make_float4(x[0], x[1], x[2], x[3]);
           else
-            put4<P>(out, row, col, x, huge);
+            put4<P>(out, row, col, x, fwd ? &huge : nullptr);
         }
       }
     }
-    report(fwd ? 0 : 1, l_out, huge);
+    if (fwd) report(l_out, huge);
     if (P == 3 && ph == 2 * n_hidden) return;
     lds_barrier();
 
@@ -421,7 +422,6 @@ k_chain(ChainLaunch cl, int n_hidden, int grad) {
     if (ph == n_hidden) {
       const int nch = net.width[n_hidden] / 8;
       const ChainTile hl = out;
-      bool hg = false;
       // R * 8 is a multiple of 64: every group of eight lanes takes the loop's
       // iterations together
       for (int t8 = tid; t8 < R * 8; t8 += T) {
@@ -440,7 +440,7 @@ k_chain(ChainLaunch cl, int n_hidden, int grad) {
               e += h[k] * w[k];
               h[k] = w[k] * dcelu_h(h[k], inv_alpha) * cl.inv_m;
             }
-            if (grad) put4<P>(hl, row, col, h, hg);
+            if (grad) put4<P>(hl, row, col, h);
           }
         }
         e = sum8(e);
@@ -454,7 +454,6 @@ k_chain(ChainLaunch cl, int n_hidden, int grad) {
           }
         }
       }
-      report(1, n_hidden, hg);
       lds_barrier();
     }
   }

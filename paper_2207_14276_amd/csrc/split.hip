@@ -17,10 +17,11 @@
 // memory and LDS; a wave splits them as it reads its fragments, in the shadow
 // of its MFMAs.
 //
-// A fragment with a value that has no finite first part (infinite, or within
-// a rounding of the largest float) takes its products on the float32 matrix
-// instruction instead, with the weights put together again from their parts
-// (exact), so that overflows come out as they do there.  Models whose weights
+// A fragment of activations with a value that has no finite first part
+// (infinite, or within a rounding of the largest float) takes its products on
+// the float32 matrix instruction instead, with the weights put together again
+// from their parts (exact), so that overflows come out as they do there.
+// Gradients need no such care: none exceeds its network's gain.  Models whose weights
 // are not finite, are not whole multiples of 2^-126, or are so large that what
 // the smallest activations lose could grow to count (parts_suffice in api.hip),
 // or whose widths leave a partial 32-column chunk, stay on the float32 kernels
@@ -231,7 +232,9 @@ k_gemm_split(GemmLaunch gl) {
   for (int q = 0; q < STAGES - STEP; ++q)
     if (q < total) issue(next(q), q);
 
-  // This wave's activations of chunk c (its stage's A slots), and the largest magnitude.
+  // This wave's rows of A of chunk c (its stage's A slots); whether one of them
+  // is an activation without a finite first part.
+  constexpr bool kWide = EPI == kEpiFwd;
   auto take_a = [&](const uint4 *As, Parts (&a)[HR]) {
     float big = 0.f;
 #pragma unroll
@@ -243,10 +246,10 @@ k_gemm_split(GemmLaunch gl) {
       const floatx4 v = *(const floatx4 *)&As[8 * r + ((2 * kq + 1) ^ aswz(r))];
       const float x[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
       // (padding rows hold whatever an earlier call left there)
-      big = fmaxf(big, r0 + r < real_end ? max8(x) : 0.f);
+      if (kWide) big = fmaxf(big, r0 + r < real_end ? max8(x) : 0.f);
       a[h] = split8(x);
     }
-    return __ballot(big > kPartMax) != 0;
+    return kWide && __ballot(big > kPartMax) != 0;
   };
   // block j's fragment of part p: slot(j)[4 TN p] (the XOR of a row depends
   // on its block's parity alone)
