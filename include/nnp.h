@@ -475,11 +475,16 @@ int nnp_sched_info(nnp_sched *sched, int64_t *info);
  *                    the members' columns side by side in one tile space);
  *   site 10 + l      dense layer l input-gradient GEMM: width 64, 128 or 256;
  *   site 18          the dE/dG GEMM: width 64, 128 or 256;
+ *                    (float32 layers on bfloat16 parts, sites 2 to 18: 64 for
+ *                    tiles of 16 rows and 64 columns, 128 or 256 for tiles of
+ *                    128 rows and columns);
  *   site 19          the fused hidden-layer chain: 4, 8 or 18 for 16, 32 or
  *                    (bfloat16) 64 rows per workgroup.
  * The choices stay with the model for all later calls (no call changes any
  * result: tile shapes change no per-element arithmetic order); sites that did
- * not run keep their default (0).  Waits for the stream; allocates. */
+ * not run keep their default (0), and so do sites 0 and 1 where the batch's
+ * few centres or long lists take several waves per centre whatever the value.
+ * Waits for the stream; allocates. */
 int nnp_autotune(nnp_model *model, int n_systems, const int64_t *batch_offsets, const float *coords,
                  const int32_t *species, const float *box, void *stream);
 /* Copies up to n tuned site values (0 = default shape) into values; returns

@@ -1239,6 +1239,10 @@ static bool group_centres(int n_centres, bool list, size_t lds_per_wave, size_t 
   return n_centres <= (list ? 1024 : 4096) || lds_per_wave * 11 > max_lds;
 }
 
+bool aev_grouped(bool bwd, int n_centres, bool list, int cap, size_t max_lds) {
+  return group_centres(n_centres, list, bwd ? wave_lds_bytes<true>(cap) : wave_lds_bytes<false>(cap), max_lds);
+}
+
 template <bool BF16>
 static void aev_fwd_t(const float4 *pos, const int *sys_of, const SysDesc *sys, const int2 *nbr,
                       const int *nbr_cnt, int cap, const int *row_of_atom, void *G, int ldg,
@@ -1321,6 +1325,8 @@ static void aev_bwd_launch(int form, size_t lds, unsigned grid, const AevBwdGrou
 // them): per system for a batch of small non-periodic systems (gp.groups),
 // per cell on a grid of at least kBwdMinCells cells (fewer would leave
 // compute units idle).  Without a grouped form: one wave per centre.
+// Calls with several waves per centre (group_centres) run those whatever
+// wpb_pref is.
 void launch_aev_bwd(const float4 *pos, const int *sys_of, const SysDesc *sys, const int2 *nbr,
                     const int *nbr_cnt, int cap, const int *row_of_atom, const float *dG, int ldg,
                     Live N, const AevConst &c, unsigned long long *Ffix, float *W_atom, const AevBwdGroups &gp,

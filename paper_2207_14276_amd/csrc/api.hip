@@ -1310,11 +1310,15 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     };
     // per-site events while tuning (every site launches at most once per call)
     const bool tuning = m->tuning && mode == kFull;
-    auto site_begin = [&](int site) {
+    // (choice: the site's value has a say in this call)
+    auto site_begin = [&](int site, bool choice = true) {
       if (tuning) {
         (void)hipEventRecord(m->tune_ev[site][0], st);
-        m->tune_hit[site] = true;
+        m->tune_hit[site] = choice;
       }
+    };
+    auto aev_choice = [&](bool bwd) {
+      return m->kind != kDescAev || !aev_grouped(bwd, lN.v, !direct, lds_cap, m->max_lds);
     };
     auto site_end = [&](int site) {
       if (tuning) (void)hipEventRecord(m->tune_ev[site][1], st);
@@ -1421,7 +1425,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
       HIP_TRY(hipGetLastError());
       return NNP_OK;
     }
-    site_begin(kSiteAevFwd);
+    site_begin(kSiteAevFwd, aev_choice(false));
     descriptor(m->G.p, bf16, m->ldG, m->gapG, dp && want_grad ? m->dp_rec.as<float4>() : nullptr, gmask,
                m->tune_val[kSiteAevFwd]);
     site_end(kSiteAevFwd);
@@ -1578,7 +1582,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     }
     mark();
     if (want_grad) {
-      site_begin(kSiteAevBwd);
+      site_begin(kSiteAevBwd, aev_choice(true));
       if (dp) {
         // cells exist for this call unless the pair list or the small-system scan replaced them
         const bool cells = !pairs && !all_small;
@@ -1737,7 +1741,8 @@ extern "C" int nnp_autotune(nnp_model *m, int n_systems, const int64_t *offs, co
   // centre with device atomics; 5, 4, 8: a grouped form with that many
   // waves) and the fused chain's shape to kChainW[r]
   constexpr int kRounds = 4, kReps = 5;
-  const int kTn[kRounds] = {64, 128, 256, 128}, kWpb[kRounds] = {1, 2, 4, 2};
+  // (float32 layers on parts have two shapes, 64 and 128)
+  const int kTn[kRounds] = {64, 128, m->split ? 128 : 256, m->split ? 64 : 128}, kWpb[kRounds] = {1, 2, 4, 2};
   const int kBwd[kRounds] = {1, 5, 4, 8};
   // chain: 32, 16 or (bfloat16) 64 rows per workgroup
   const int kChainW[kRounds] = {8, 4, m->precision == NNP_BF16 ? 18 : 8, 8};

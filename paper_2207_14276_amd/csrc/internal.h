@@ -324,6 +324,8 @@ void launch_aev_fwd(const float4 *pos, const int *sys_of, const SysDesc *sys, co
                     const int *nbr_cnt, int cap, const int *row_of_atom, void *G, bool g_bf16,
                     int ldg, Live N, const AevConst &c, unsigned long long *row_mask, const int *wave_atom,
                     int *status, int wpb_pref, size_t max_lds, hipStream_t st);
+// Whether the AEV kernels run several waves per centre, whatever wpb_pref is.
+bool aev_grouped(bool bwd, int n_centres, bool list, int cap, size_t max_lds);
 // How the AEV backward groups its centres (at most one of the two forms):
 // groups[n_groups] = {first centre, count} of consecutive centres of one
 // small non-periodic system (max_sys_atoms: the largest such system), or the
