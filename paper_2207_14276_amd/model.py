@@ -364,7 +364,8 @@ class NNPFunction(torch.autograd.Function):
         (forces,) = ctx.saved_tensors
         g = -grad_e.to(torch.float32)
         if len(ctx.counts) > 1:
-            # the output size is known here: no wait for the device
-            g = torch.repeat_interleave(g, torch.as_tensor(ctx.counts, device=g.device),
-                                        output_size=int(forces.shape[0]))
+            # no wait for the device: the counts go there from pinned memory,
+            # and the output size is known here
+            counts = torch.from_numpy(ctx.counts).pin_memory().to(g.device, non_blocking=True)
+            g = torch.repeat_interleave(g, counts, output_size=int(forces.shape[0]))
         return (g[:, None] * forces).to(ctx.coords_dtype), None, None, None, None
