@@ -555,6 +555,10 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
   int rc = m->status.ensure(2 * sizeof(int));
   if (rc) return rc;
   HIP_TRY(hipMemset(m->status.p, 0, 2 * sizeof(int)));
+  // the weights are laid out by kernels on the null stream, which a caller's
+  // stream need not wait for
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipStreamSynchronize(nullptr));
   return NNP_OK;
 }
 
