@@ -363,6 +363,26 @@ static bool parts_suffice(const nnp_model *m, const float *w) {
   return true;
 }
 
+// Whether the layers after the first run fused: 2..4 hidden layers in all,
+// widths that are multiples of 32 and at most 256, the activation tiles of 32
+// rows within a workgroup's LDS.  Fills in the tiles' layout.
+static bool plan_chain(nnp_model *m) {
+  const bool f32 = m->precision == NNP_FP32;
+  if ((f32 && !m->split) || m->L < 3 || m->L - 2 > kChainMax) return false;
+  size_t elems = 0;
+  for (int l = 0; l + 1 < m->L; ++l) {
+    for (int s = 0; s < m->S; ++s) {
+      const int w = m->widths[s][l + 1];
+      if (w % 32 != 0 || w > 256) return false;
+    }
+    m->chain_proto.lds_off[l] = (int)elems;
+    m->chain_proto.lds_ld[l] = m->ldH[l] + 8;
+    elems += (size_t)16 * (m->ldH[l] + 8) * (f32 ? 3 : 1);
+  }
+  m->chain_lds = elems * 2;
+  return f32 ? 2 * m->chain_lds + 64 <= m->max_lds : 2 * m->chain_lds <= 64 * 1024;
+}
+
 static int create_networks(const NetArgs *d, nnp_model *m) {
   if (d->n_ensemble < 1) return fail(NNP_EINVAL, "n_ensemble must be >= 1");
   if (d->n_ensemble > kMaxMembers) return fail(NNP_EUNSUPPORTED, "at most %d ensemble members", kMaxMembers);
@@ -409,6 +429,7 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
   m->layers.resize((size_t)m->M * S * L);
   const float *wp = d->weights;
   if (m->precision == NNP_FP32) m->split = parts_suffice(m, wp);
+  m->chain = plan_chain(m);
   // the first layer's padded rows (bfloat16 and split models) have the zero
   // columns after the radial part where its length is no multiple of 32 (it
   // is of 16): the angular blocks are whole chunks then
@@ -449,7 +470,8 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
           round_bf16_host(tmp.data(), tb.data(), nw);
           if ((rc = upload(m, tb.data(), nw * 2, (void **)&lw.Wtb))) return rc;
         }
-        if (m->split && l + 1 < L) {
+        if (m->split && l + 1 < L && (l == 0 || !m->chain)) {
+          // (the chain has its own layout of the layers after the first)
           // one allocation per species and layer, the members' parts in turn
           const int Kp = l == 0 ? m->ldG : lw.n_in;
           const LayerW *first = mb > 0 ? &m->layer(0, s, l) : nullptr;
@@ -494,57 +516,32 @@ static int create_networks(const NetArgs *d, nnp_model *m) {
       if (m->split && (rc = split_parts(m, m->Wdg[s], D, MK, MK, 1, &m->Wdg_s[s]))) return rc;
     }
   }
-  // fused chain: 2..4 hidden layers after the first, widths that are
-  // multiples of 32 and at most 256, the activation tiles of 32 rows within a
-  // workgroup's LDS
-  const bool f32 = m->precision == NNP_FP32;
-  if ((m->split || !f32) && L >= 3 && L - 2 <= kChainMax) {
-    bool ok = true;
-    const int planes = f32 ? 3 : 1;
-    size_t elems = 0;
-    ChainLaunch &cp = m->chain_proto;
-    for (int l = 0; l + 1 < L; ++l) {
+  if (m->chain) {
+    std::vector<ChainNet> nets((size_t)m->M * S);
+    for (int mb = 0; mb < m->M; ++mb)
       for (int s = 0; s < S; ++s) {
-        const int w = m->widths[s][l + 1];
-        ok = ok && w % 32 == 0 && w <= 256;
-      }
-      if (l <= kChainMax) {
-        cp.lds_off[l] = (int)elems;
-        cp.lds_ld[l] = m->ldH[l] + 8;
-        elems += (size_t)16 * (m->ldH[l] + 8) * planes;
-      }
-    }
-    const size_t lds = elems * 2;
-    ok = ok && (f32 ? 2 * lds + 64 <= m->max_lds : 2 * lds <= 64 * 1024);
-    if (ok) {
-      std::vector<ChainNet> nets((size_t)m->M * S);
-      for (int mb = 0; mb < m->M; ++mb)
-        for (int s = 0; s < S; ++s) {
-          ChainNet &n = nets[(size_t)mb * S + s];
-          memset(&n, 0, sizeof n);
-          for (int l = 1; l <= L - 2; ++l) {
-            LayerW &lw = m->layer(mb, s, l);
-            uint16_t *frags = nullptr;  // the layer, then its transpose
-            const size_t nf = (size_t)lw.n_in * lw.n_out * planes;
-            HIP_TRY(hipMalloc((void **)&frags, 2 * nf * 2));
-            m->weight_allocs.push_back(frags);
-            launch_weight_frags(lw.W, lw.Wb, lw.n_out, lw.n_in, frags, nullptr);
-            launch_weight_frags(lw.Wt, lw.Wtb, lw.n_in, lw.n_out, frags + nf, nullptr);
-            n.W[l - 1] = frags;
-            n.Wt[l - 1] = frags + nf;
-            n.b[l - 1] = lw.b;
-          }
-          LayerW &lo = m->layer(mb, s, L - 1);
-          n.w_out = lo.W;
-          HIP_TRY(hipMemcpy(&n.b_out, lo.b, sizeof(float), hipMemcpyDeviceToHost));
-          for (int l = 0; l <= L - 2; ++l) n.width[l] = m->widths[s][l + 1];
+        ChainNet &n = nets[(size_t)mb * S + s];
+        memset(&n, 0, sizeof n);
+        for (int l = 1; l <= L - 2; ++l) {
+          LayerW &lw = m->layer(mb, s, l);
+          uint16_t *frags = nullptr;  // the layer, then its transpose
+          const size_t nf = (size_t)lw.n_in * lw.n_out * (m->split ? 3 : 1);
+          HIP_TRY(hipMalloc((void **)&frags, 2 * nf * 2));
+          m->weight_allocs.push_back(frags);
+          launch_weight_frags(lw.W, lw.Wb, lw.n_out, lw.n_in, frags, nullptr);
+          launch_weight_frags(lw.Wt, lw.Wtb, lw.n_in, lw.n_out, frags + nf, nullptr);
+          n.W[l - 1] = frags;
+          n.Wt[l - 1] = frags + nf;
+          n.b[l - 1] = lw.b;
         }
-      int rc = m->chain_nets.ensure(nets.size() * sizeof(ChainNet));
-      if (rc) return rc;
-      HIP_TRY(hipMemcpy(m->chain_nets.p, nets.data(), nets.size() * sizeof(ChainNet), hipMemcpyHostToDevice));
-      m->chain = true;
-      m->chain_lds = lds;
-    }
+        LayerW &lo = m->layer(mb, s, L - 1);
+        n.w_out = lo.W;
+        HIP_TRY(hipMemcpy(&n.b_out, lo.b, sizeof(float), hipMemcpyDeviceToHost));
+        for (int l = 0; l <= L - 2; ++l) n.width[l] = m->widths[s][l + 1];
+      }
+    int rc = m->chain_nets.ensure(nets.size() * sizeof(ChainNet));
+    if (rc) return rc;
+    HIP_TRY(hipMemcpy(m->chain_nets.p, nets.data(), nets.size() * sizeof(ChainNet), hipMemcpyHostToDevice));
   }
   for (StageSlot &ss : m->stage) {
     HIP_TRY(hipEventCreateWithFlags(&ss.done, hipEventDisableTiming | hipEventDisableSystemFence));
