@@ -374,9 +374,15 @@ template <int W> __device__ inline void centre_sync() {
 }
 
 // fill_lists by the W waves of a workgroup: wave v takes the row's 64-entry
-// chunks v, v + W, ...; the chunks' species counts meet in LDS (cnt, 16 ints a
-// chunk), and every entry lands where the one-wave form puts it.
+// chunks v, v + W, ...; the chunks' species counts meet in LDS (cnt, kChunkCounts
+// bytes a chunk), and every entry lands where the one-wave form puts it.  The
+// counts lie in the forward's pair scratch, and in the backward where the 24
+// bytes per entry of dE/dd follow: n entries, at most one more than the
+// capacity, come in at most (capacity + 64) / 64 chunks, and no capacity is
+// below 4.
 constexpr int kMaxChunks = 1024 / kWave + 1;  // rows hold at most 1,024 entries, systems without a list one more
+constexpr int kChunkCounts = 16 * sizeof(int);
+static_assert(kChunkCounts == kWave && 24 * 4 >= 4 + kChunkCounts, "chunk counts of the backward");
 template <bool BWD, int W>
 __device__ inline void fill_lists_group(int wave, int lane, int n, const int2 *__restrict__ ent, int self, int j0,
                                         int n_sys, const float4 *__restrict__ pos, const float4 &pi,
@@ -1054,8 +1060,10 @@ __device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__res
     float vir[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) vir[q] = 0.f;
+    static_assert(W == 1 || Sink::kByComponent, "a group's waves share a centre's adds by component");
     if constexpr (Sink::kByComponent) {
-      // component t of the entries by lane t (a group: by its waves but the first)
+      // component t of the entries by lane t (a group: by its waves but the
+      // first, which forms the centre's sums, in the one-wave order)
       constexpr int kSend = W > 1 ? W - 1 : 1;
       if (W == 1 || wave > 0)
         for (int t = first_e - (W > 1 ? kWave : 0); t < 3 * nR; t += kSend * kWave) {
@@ -1064,20 +1072,11 @@ __device__ inline void bwd_centre(int i, int wave, int lane, const float4 *__res
         }
       if (W > 1 && wave > 0) return;
     }
-    // a group: its first wave forms the centre's sums (in the one-wave order),
-    // the others send the neighbours' shares
-    if (W > 1 && wave > 0) {
-      for (int e = first_e - kWave; e < nR; e += (W - 1) * kWave) {
-        const float gx = (float)w.rG[3 * e], gy = (float)w.rG[3 * e + 1], gz = (float)w.rG[3 * e + 2];
-        sink.add(w.rJ[e], -to_fix(gx), -to_fix(gy), -to_fix(gz));
-      }
-      return;
-    }
     for (int e = lane; e < nR; e += kWave) {
       const float4 ur = w.rD[e];  // unit vector and R
       const float4 dv = make_float4(ur.x * ur.w, ur.y * ur.w, ur.z * ur.w, ur.w);
       const float gx = (float)w.rG[3 * e], gy = (float)w.rG[3 * e + 1], gz = (float)w.rG[3 * e + 2];
-      if (W == 1 && !Sink::kByComponent) sink.add(w.rJ[e], -to_fix(gx), -to_fix(gy), -to_fix(gz));
+      if (!Sink::kByComponent) sink.add(w.rJ[e], -to_fix(gx), -to_fix(gy), -to_fix(gz));
       fi0 += gx; fi1 += gy; fi2 += gz;
       if (!W_atom) continue;
       vir[0] -= dv.x * gx; vir[1] -= dv.x * gy; vir[2] -= dv.x * gz;
@@ -1235,6 +1234,7 @@ static int waves_for_cap(int cap, int pref) {  // centres per workgroup, a wave 
 //     capacity of 640 (18 / 36 KB a wave) 344 / 579 -> 206 / 370 us; water at
 //     256 (8 / 15 KB) 39 / 73 -> 62 / 90 us.
 constexpr int kGroupWaves = 4;
+static_assert(kMaxChunks * kChunkCounts <= kGroupWaves * kPairPass * 24, "chunk counts of the forward");
 static bool group_centres(int n_centres, bool list, size_t lds_per_wave, size_t max_lds) {
   return n_centres <= (list ? 1024 : 4096) || lds_per_wave * 11 > max_lds;
 }

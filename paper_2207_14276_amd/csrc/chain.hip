@@ -485,11 +485,6 @@ __global__ void k_chain_mean(const float *__restrict__ e_mem, int M, const int *
   e_atom[atom] = e * inv_m;
 }
 
-void launch_chain_mean(const ChainLaunch &cl, int rows, hipStream_t st) {
-  k_chain_mean<<<(rows + 255) / 256, 256, 0, st>>>(cl.e_mem, cl.n_members, cl.perm, cl.bucket_off, cl.n_groups,
-                                                    rows, cl.inv_m, cl.e_atom);
-}
-
 template <int P, int HR>
 static void chain_t(ChainLaunch cl, int n_hidden, bool grad, int rows, size_t lds16, hipStream_t st) {
   cl.n_blocks = rows / (16 * HR) * cl.n_members;
