@@ -1223,24 +1223,37 @@ static int waves_for_cap(int cap, int pref) {  // centres per workgroup, a wave 
 }
 
 // Several waves per centre where the centres alone leave the chip idle:
-//   - few centres: at most 1,024 (one wave per SIMD), or 4,096 in systems
-//     without a list, whose dense environments make a centre's passes many.
-//     Measured, forward / backward: 101 atoms 55 / 52 -> 21 / 26 us; 64 dense
-//     solutes (4,000 atoms) 74 / 77 -> 46 / 61 us, 100 of them 82 / 94 -> 68 /
-//     96; a water box of 1,200 atoms 15 / 18 -> 13 / 19, of 2,001 14 / 22 ->
-//     17 / 28 us (a centre has two passes, and waits for the group);
-//   - lists so long that the LDS holds fewer than eleven one-wave centres per
-//     compute unit: a mix of solutes and boxes of 60 to 2,400 atoms at a
-//     capacity of 640 (18 / 36 KB a wave) 344 / 579 -> 206 / 370 us; water at
-//     256 (8 / 15 KB) 39 / 73 -> 62 / 90 us.
+//   - at most 1,024 centres (one wave per SIMD).  Forward / backward, one wave
+//     and groups: 101 atoms 50 / 51 -> 21 / 27 us, 1,000 in solutes of 20 atoms
+//     17 / 12 -> 11 / 11, 900 of a box of water 13 / 15 -> 10 / 12;
+//   - up to 4,096 centres of systems without a list whose largest has enough
+//     atoms, so that a centre's passes may be many: in the forward more than a
+//     300th of the call's; in the backward, whose waves take turns at the adds,
+//     more than a 50th and than 48.  Of 4,000 atoms in solutes of 10, 20, 40,
+//     64, 100 and 200 (1.2 A n^(1/3) a side) the forward went from 17, 21, 30,
+//     47, 68 and 92 to 20, 22, 29, 36, 45 and 59 us, the backward from 12, 18,
+//     32, 56, 87 and 120 to 28, 31, 42, 54, 67 and 91; of 1,600 in solutes of
+//     4, 10, 40 and 64 the forward from 10, 14, 25 and 36 to 10, 12, 17 and 21,
+//     the backward from 8, 9, 22 and 37 to 14, 15, 23 and 30.  Open solutes
+//     (2.3 A n^(1/3)), whose centres have few passes, lose in the backward: of
+//     100 atoms, 4,000 in all, 17 -> 30;
+//   - lists (or systems without one) so long that the LDS holds fewer than
+//     eleven one-wave centres per compute unit, or seven in the backward of
+//     more than 4,096 centres with lists, where most of a row may lie past the
+//     angular cutoff: 30,000 atoms of water at capacities of 304, 400, 448 and
+//     600 take 126, 151, 168 and 236 us there one by one and 181, 181, 181 and
+//     216 in groups, 120 dense solutes of 10 to 120 atoms at 448 115 and 93; 60
+//     dense solutes of 500 atoms without a list 1,305 and 740, open ones 388 and
+//     224.  In the forward, those 120 solutes at 600 83 and 63, the water 110
+//     and 129.
 constexpr int kGroupWaves = 4;
 static_assert(kMaxChunks * kChunkCounts <= kGroupWaves * kPairPass * 24, "chunk counts of the forward");
-static bool group_centres(int n_centres, bool list, size_t lds_per_wave, size_t max_lds) {
-  return n_centres <= (list ? 1024 : 4096) || lds_per_wave * 11 > max_lds;
-}
-
 bool aev_grouped(bool bwd, int n_centres, bool list, int cap, size_t max_lds) {
-  return group_centres(n_centres, list, bwd ? wave_lds_bytes<true>(cap) : wave_lds_bytes<false>(cap), max_lds);
+  if (n_centres <= 1024) return true;
+  // (without a list, the capacity is the largest system's other atoms)
+  if (!list && n_centres <= 4096 && (bwd ? cap > 48 && cap * 50 > n_centres : cap * 300 > n_centres)) return true;
+  const size_t per = bwd ? wave_lds_bytes<true>(cap) : wave_lds_bytes<false>(cap);
+  return per * (bwd && list && n_centres > 4096 ? 7 : 11) > max_lds;
 }
 
 template <bool BF16>
@@ -1248,7 +1261,7 @@ static void aev_fwd_t(const float4 *pos, const int *sys_of, const SysDesc *sys, 
                       const int *nbr_cnt, int cap, const int *row_of_atom, void *G, int ldg,
                       unsigned long long *row_mask, const int *wave_atom, int *status, Live N, const AevConst &c,
                       int wpb_pref, size_t max_lds, hipStream_t st) {
-  if (group_centres(N.v, nbr != nullptr, wave_lds_bytes<false>(cap), max_lds)) {
+  if (aev_grouped(false, N.v, nbr != nullptr, cap, max_lds)) {
     const size_t lds = wave_lds_bytes<false>(cap) + kGroupWaves * kPairPass * 24;
     k_aev_fwd<kGroupWaves, BF16, true><<<(unsigned)N.v, kGroupWaves * kWave, lds, st>>>(
         pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, G, ldg, row_mask, wave_atom, status, N, 1, c);
@@ -1325,7 +1338,7 @@ static void aev_bwd_launch(int form, size_t lds, unsigned grid, const AevBwdGrou
 // them): per system for a batch of small non-periodic systems (gp.groups),
 // per cell on a grid of at least kBwdMinCells cells (fewer would leave
 // compute units idle).  Without a grouped form: one wave per centre.
-// Calls with several waves per centre (group_centres) run those whatever
+// Calls with several waves per centre (aev_grouped) run those whatever
 // wpb_pref is.
 void launch_aev_bwd(const float4 *pos, const int *sys_of, const SysDesc *sys, const int2 *nbr,
                     const int *nbr_cnt, int cap, const int *row_of_atom, const float *dG, int ldg,
@@ -1333,7 +1346,7 @@ void launch_aev_bwd(const float4 *pos, const int *sys_of, const SysDesc *sys, co
                     int wpb_pref, size_t max_lds, hipStream_t st) {
   if (N.v <= 0) return;
   const size_t per = wave_lds_bytes<true>(cap);
-  if (group_centres(N.v, nbr != nullptr, per, max_lds)) {
+  if (aev_grouped(true, N.v, nbr != nullptr, cap, max_lds)) {
     aev_bwd_launch<kGroupWaves>(3, per, (unsigned)N.v, gp, pos, sys_of, sys, nbr, nbr_cnt, cap, row_of_atom, dG, ldg,
                                 N, c, Ffix, W_atom, st);
     return;
