@@ -1587,7 +1587,9 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
       if (dp) {
         // cells exist for this call unless the pair list or the small-system scan replaced them
         const bool cells = !pairs && !all_small;
-        launch_dp_bwd(dsys, n_sys, all_small, cells ? m->cell_start.as<int>() : nullptr,
+        bool open = false;
+        for (int s = 0; s < n_sys; ++s) open = open || !sd[s].periodic;
+        launch_dp_bwd(dsys, n_sys, all_small, open, cells ? m->cell_start.as<int>() : nullptr,
                       m->cell_atoms.as<int>(), (int)C, m->row_of_atom.as<int>(), m->dG.as<float>(), D, N, m->dp,
                       m->dp_rec.as<float4>(), o.forces, W_atom, m->tune_val[kSiteAevBwd], st);
       } else {

@@ -580,6 +580,13 @@ void launch_dp_fwd(const float4 *pos, const float *coords, const AtomState *stat
 // unit, the waves of a cell are few and their latency bounds this one: sixteen
 // waves per cell (216 cells of 28 atoms: 19 us, and 59 with a wave per centre
 // and atomics; 64 cells of 31: 20 and 26; 27 cells of 37: 22 and 21), else eight.
+//
+// A system without a box reserves a cell per four atoms and may fill far fewer,
+// so where some system has none (open) the workgroups of the cells that are not
+// there take shares of those that are, of at least a centre per wave, as long as
+// the systems are few: up to two workgroups per compute unit in all (of 500
+// solutes and a box, shares of each took 20 us more than they gave).  990 atoms in one cell 297 -> 18 us (a wave per
+// centre and atomics: 55), 2,100 in eight 153 -> 20, 4,000 in 64 45 -> 22.
 constexpr int kMinCellGroups = 64;
 constexpr int kCellsWide = 512;
 constexpr int kHashBits = 11;
@@ -587,13 +594,34 @@ constexpr int kHashSlots = 1 << kHashBits;   // 2048 atoms; a cell's neighbourho
 
 template <int WPB>
 __global__ void __launch_bounds__(WPB * kWave)
-k_dp_bwd_cells(const int *__restrict__ cell_start, const int *__restrict__ cell_atoms,
-               const int *__restrict__ row_of_atom, const float *__restrict__ dG, int ldg, DpConst c,
-               const float4 *__restrict__ rec, float *__restrict__ F, float *__restrict__ W_atom) {
+k_dp_bwd_cells(const SysDesc *__restrict__ sys, int n_sys, int open, const int *__restrict__ cell_start,
+               const int *__restrict__ cell_atoms, const int *__restrict__ row_of_atom,
+               const float *__restrict__ dG, int ldg, DpConst c, const float4 *__restrict__ rec,
+               float *__restrict__ F, float *__restrict__ W_atom) {
   __shared__ int hkey[kHashSlots];
   __shared__ unsigned long long hval[3 * kHashSlots];
-  const int b = cell_start[blockIdx.x], e = cell_start[blockIdx.x + 1];
-  if (b == e) return;  // the whole workgroup leaves together
+  int cell = blockIdx.x, share = 0, shares = 1;
+  if (open) {
+    // the system of this reserved cell: the last one that starts at or before it
+    int lo = 0, hi = n_sys - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (sys[mid].cell_off <= cell) lo = mid; else hi = mid - 1;
+    }
+    const SysDesc &d = sys[lo];
+    const int there = d.nc[0] * d.nc[1] * d.nc[2];
+    shares = max(1, min(d.cell_cap, kCellsWide / n_sys) / there);
+    share = (cell - d.cell_off) / there;
+    if (share >= shares) return;  // (here and below: the whole workgroup)
+    cell -= share * there;
+  }
+  int b = cell_start[cell], e = cell_start[cell + 1];
+  if (shares > 1) {
+    const int each = max(WPB, (e - b + shares - 1) / shares);
+    b += share * each;
+    e = min(e, b + each);
+  }
+  if (b >= e) return;
   for (int t = threadIdx.x; t < kHashSlots; t += WPB * kWave) {
     hkey[t] = -1;
     hval[3 * t] = hval[3 * t + 1] = hval[3 * t + 2] = 0ull;
@@ -637,8 +665,8 @@ k_dp_bwd_cells(const int *__restrict__ cell_start, const int *__restrict__ cell_
 // otherwise.  With small_systems (every system non-periodic with at most
 // kSmallSystem atoms) the per-system form runs instead, sixteen waves per
 // system; with a cell grid (cell_start non-null) of at least kMinCellGroups
-// cells the per-cell form.
-void launch_dp_bwd(const SysDesc *sys, int n_sys, bool small_systems, const int *cell_start,
+// cells the per-cell form (open: some system has no box).
+void launch_dp_bwd(const SysDesc *sys, int n_sys, bool small_systems, bool open, const int *cell_start,
                    const int *cell_atoms, int n_cells, const int *row_of_atom, const float *dG, int ldg, int N,
                    const DpConst &c, const float4 *rec, float *F, float *W_atom, int wpb_pref, hipStream_t st) {
   if (N <= 0) return;
@@ -647,12 +675,13 @@ void launch_dp_bwd(const SysDesc *sys, int n_sys, bool small_systems, const int 
     return;
   }
   if (cell_start && n_cells >= kMinCellGroups) {
+    open = open && 2 * n_sys <= kCellsWide;
     if (n_cells <= kCellsWide)
-      k_dp_bwd_cells<16><<<n_cells, 16 * kWave, 0, st>>>(cell_start, cell_atoms, row_of_atom, dG, ldg, c, rec, F,
-                                                         W_atom);
+      k_dp_bwd_cells<16><<<n_cells, 16 * kWave, 0, st>>>(sys, n_sys, open, cell_start, cell_atoms, row_of_atom, dG, ldg, c,
+                                                         rec, F, W_atom);
     else
-      k_dp_bwd_cells<8><<<n_cells, 8 * kWave, 0, st>>>(cell_start, cell_atoms, row_of_atom, dG, ldg, c, rec, F,
-                                                       W_atom);
+      k_dp_bwd_cells<8><<<n_cells, 8 * kWave, 0, st>>>(sys, n_sys, open, cell_start, cell_atoms, row_of_atom, dG, ldg, c,
+                                                       rec, F, W_atom);
     return;
   }
   const int wpb = (wpb_pref == 1 || wpb_pref == 2) ? wpb_pref : 4;
