@@ -1447,6 +1447,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
     // with the fused chain only the first layer runs as a separate GEMM
     const bool use_chain = m->chain;
     const bool split = m->split;
+    const int n_rows = pin.mask ? -1 : N_l;  // atoms with a network row, where known
     for (int l = 0; l + 1 < (use_chain ? 2 : L); ++l) {
       GemmLaunch gl{};
       common(gl);
@@ -1473,7 +1474,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
           if (l == 0 && (bf16 || split)) g.K = g.ldb = m->ldG;  // zero-padded columns on both sides
         }
       site_begin(kSiteGemmFwd + l);
-      if (split) launch_gemm_split(kEpiFwd, gl, rows, m->ldH[l], m->tune_val[kSiteGemmFwd + l], st);
+      if (split) launch_gemm_split(kEpiFwd, gl, rows, n_rows, m->ldH[l], m->tune_val[kSiteGemmFwd + l], st);
       else launch_gemm(kEpiFwd, bf16, gl, row_tiles, m->ldH[l], m->tune_val[kSiteGemmFwd + l], st);
       site_end(kSiteGemmFwd + l);
     }
@@ -1552,7 +1553,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
           }
         gl.bucket_cnt = m->bucket_cnt.as<int>();
         site_begin(kSiteGemmBwd + l);
-        if (split) launch_gemm_split(kEpiBwd, gl, rows, m->ldH[l - 1], m->tune_val[kSiteGemmBwd + l], st);
+        if (split) launch_gemm_split(kEpiBwd, gl, rows, n_rows, m->ldH[l - 1], m->tune_val[kSiteGemmBwd + l], st);
         else launch_gemm(kEpiBwd, bf16, gl, row_tiles, m->ldH[l - 1], m->tune_val[kSiteGemmBwd + l], st);
         site_end(kSiteGemmBwd + l);
       }
@@ -1576,7 +1577,7 @@ static int run(nnp_model *m, int n_sys, const int64_t *offs, const float *coords
           g.K = m->widths[s][1];
         }
         site_begin(kSiteGemmOut);
-        if (split) launch_gemm_split(kEpiOut, gl, rows, D, m->tune_val[kSiteGemmOut], st);
+        if (split) launch_gemm_split(kEpiOut, gl, rows, n_rows, D, m->tune_val[kSiteGemmOut], st);
         else launch_gemm(kEpiOut, bf16, gl, row_tiles, D, m->tune_val[kSiteGemmOut], st);
         site_end(kSiteGemmOut);
       }

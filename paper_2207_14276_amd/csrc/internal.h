@@ -363,9 +363,10 @@ void launch_chain(const ChainLaunch &cl, bool f32, int n_hidden, bool grad, int 
 void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, int gap_at, int gap, uint16_t *dst,
                           hipStream_t st);
 // As launch_gemm with float32 activations and parts as B (row_mask nullable,
-// bucket_cnt required); every K a multiple of 32; where the members share A,
-// n_out too, and member m's parts follow member m - 1's in memory.
-void launch_gemm_split(int epi, GemmLaunch gl, int rows, int max_n_out, int tn_pref, hipStream_t st);
+// bucket_cnt required); n_atoms: real rows in all, or -1; every K a multiple of
+// 32; where the members share A, n_out too, and member m's parts follow member
+// m - 1's in memory.
+void launch_gemm_split(int epi, GemmLaunch gl, int rows, int n_atoms, int max_n_out, int tn_pref, hipStream_t st);
 // src: host memory the device reads directly (coherent pinned); bytes are
 // rounded up to 16 on both sides
 void launch_copy_from_host(const void *src, void *dst, size_t bytes, hipStream_t st);

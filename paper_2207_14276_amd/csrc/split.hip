@@ -78,16 +78,16 @@ void launch_split_weights(const float *src, int rows, int K, int ld, int Kp, int
 //
 // 128 x 128 tiles (4 x 1 waves of 32 x 128: every activation is split by one
 // wave only), two workgroups per compute unit.  16 x 64 tiles (1 x 4 waves of
-// 16 x 16) serve calls whose 128-row tiles would leave compute units idle: a
-// wave's chain of dependent MFMAs is an eighth as long, and the row tiles
-// without a real row are skipped.  Where there are at most 256 of them, one per
-// compute unit, they take STEP = 2 chunks per barrier from a ring of eight: a
-// chunk is then bound by its chain of LDS reads, splitting and five dependent
-// MFMAs (0.39 us), and two chunks' reads and splitting run beside each other.
-// First layer of a call of 24 atoms 13.0 -> 11.6 us, of 101 atoms 20.1 -> 17.5;
-// with the ring of eight alone 14.2, with more workgroups the 112 KB of LDS
-// would leave one of them where two fit.  Every output element sums its
-// products in the same order in all.
+// 16 x 16) serve small calls (the line: launch_gemm_split): a wave's chain of
+// dependent MFMAs is an eighth as long, and the row tiles without a real row are
+// skipped.  Where there are at most 256 of them, one per compute unit, they take
+// STEP = 2 chunks per barrier from a ring of eight: a chunk is then bound by its
+// chain of LDS reads, splitting and five dependent MFMAs (0.39 us), and two
+// chunks' reads and splitting run beside each other.  First layer of a call of
+// 24 atoms 13.0 -> 11.6 us, of 101 atoms 20.1 -> 17.5; with the ring of eight
+// alone 14.2, with more workgroups the 112 KB of LDS would leave one of them
+// where two fit.  Every output element sums its products in the same order in
+// all.
 __device__ inline int aswz(int r) { return (r ^ (r >> 1)) & 7; }
 __device__ inline int bswz(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
@@ -233,8 +233,11 @@ k_gemm_split(GemmLaunch gl) {
     if (q < total) issue(next(q), q);
 
   // This wave's rows of A of chunk c (its stage's A slots); whether one of them
-  // is an activation without a finite first part.
-  constexpr bool kWide = EPI == kEpiFwd;
+  // is an activation without a finite first part.  (128-row tiles look at
+  // gradients too, which are never found: without the branch the compiler's
+  // schedule makes a workgroup alone on its compute unit 3 to 5% slower, dE/dG
+  // of 6,006 atoms x 8 networks of 256 channels 136 -> 143 us.)
+  constexpr bool kWide = EPI == kEpiFwd || CB > 1;
   auto take_a = [&](const uint4 *As, Parts (&a)[HR]) {
     float big = 0.f;
 #pragma unroll
@@ -395,18 +398,41 @@ static void gemm_split_t(GemmLaunch gl, int rows, int cols, hipStream_t st) {
       <<<xcd_grid((unsigned)gl.n_blocks, gl.xcd_chunk), WR * WC * kWave, lds, st>>>(gl);
 }
 
-// tn_pref 64: 16-row tiles, 128 or 256: 128-row tiles, else by the grid.
-void launch_gemm_split(int epi, GemmLaunch gl, int rows, int max_n_out, int tn_pref, hipStream_t st) {
+// tn_pref 64: 16-row tiles, 128 or 256: 128-row tiles, else by the work.  A
+// product on 128-row tiles takes as long as one tile while the chip holds them
+// all.  16-row tiles take a round per two of them and compute unit, for the row
+// tiles with a real row (about one per bucket more than a sixteenth of the
+// atoms), and bring the weights in more slowly, which for wide layers costs as
+// much as 45 more row tiles.  First layer (1,008 columns), one network of 160 to
+// 256 channels, 16-row and 128-row tiles: 30 solutes (2,000 atoms) 28 to 42 and
+// 61 us, 60 of them 47 to 61 and 61, 100 65 to 82 and 62, 200 109 to 139 and 65
+// (the float32 instructions 60 to 98); 3 networks of 256 10 solutes 52 and 66, 25
+// 69 and 65; 8 of 128 6 solutes 59 and 69, 20 89 and 69; 8 of 256 one of 65 atoms
+// 73 and 60, but one of 24, with 4 of the 7 buckets, 6 us less than wide tiles.
+// With 32 or 64 channels (half a wide tile's columns) 200 solutes 47 and 59, 300
+// 66 and 61.
+// Where the real work is not known here, 16-row tiles until the 128-row ones
+// give every compute unit one: in calls with a mask (n_atoms < 0; 1,138 of 11,557
+// atoms of a DeepPot call 152 us so, 170 by the rule above), and in dE/dG with row
+// records, where the line suits boxes (2,001 atoms of water x 3 networks of 256
+// channels 28 and 40 us) and solutes would take the wide tiles sooner (40 of them
+// x 3 83 and 42).
+void launch_gemm_split(int epi, GemmLaunch gl, int rows, int n_atoms, int max_n_out, int tn_pref, hipStream_t st) {
   if (rows <= 0) return;
   // members side by side where they share A and every 32-column block lies
   // in one member
   gl.span = epi == kEpiFwd && gl.a_member_stride == 0 && gl.n_members > 1;
   int cols = max_n_out;
   if (gl.span) cols *= gl.n_members;
-  const long long big = (long long)(rows / 128) * ((cols + 127) / 128) * (gl.span ? 1 : gl.n_members);
-  const bool small = tn_pref == 64 || (tn_pref != 128 && tn_pref != 256 && big < 256);
+  const long long wide = (long long)((cols + 127) / 128) * (gl.span ? 1 : gl.n_members);
+  const long long narrow = (long long)((cols + 63) / 64) * (gl.span ? 1 : gl.n_members);
+  const bool few = n_atoms < 0 || (epi == kEpiOut && gl.row_mask)
+                       ? rows / 128 * wide < 256
+                       : (n_atoms / 16 + gl.n_groups + 45) * narrow <= (narrow > 1 ? 1400 : 920) ||
+                             (n_atoms <= 32 && narrow <= 32);
+  const bool small = tn_pref == 64 || (tn_pref != 128 && tn_pref != 256 && few);
   // a workgroup per compute unit at most (see above)
-  const bool lone = small && (long long)(rows / 16) * ((cols + 63) / 64) * (gl.span ? 1 : gl.n_members) <= 256;
+  const bool lone = small && rows / 16 * narrow <= 256;
 #define NNP_SPLIT(E)                                                    \
   if (lone) gemm_split_t<E, 1, 1, 1, 4, 8, 2>(gl, rows, cols, st);      \
   else if (small) gemm_split_t<E, 1, 1, 1, 4, 4, 1>(gl, rows, cols, st); \
