@@ -1229,14 +1229,15 @@ static int waves_for_cap(int cap, int pref) {  // centres per workgroup, a wave 
 //   - up to 4,096 centres of systems without a list whose largest has enough
 //     atoms, so that a centre's passes may be many: in the forward more than a
 //     300th of the call's; in the backward, whose waves take turns at the adds,
-//     more than a 50th and than 48.  Of 4,000 atoms in solutes of 10, 20, 40,
-//     64, 100 and 200 (1.2 A n^(1/3) a side) the forward went from 17, 21, 30,
-//     47, 68 and 92 to 20, 22, 29, 36, 45 and 59 us, the backward from 12, 18,
-//     32, 56, 87 and 120 to 28, 31, 42, 54, 67 and 91; of 1,600 in solutes of
-//     4, 10, 40 and 64 the forward from 10, 14, 25 and 36 to 10, 12, 17 and 21,
-//     the backward from 8, 9, 22 and 37 to 14, 15, 23 and 30.  Open solutes
-//     (2.3 A n^(1/3)), whose centres have few passes, lose in the backward: of
-//     100 atoms, 4,000 in all, 17 -> 30;
+//     more than a 50th and than 48, or 20 up to 1,280 centres, five groups per
+//     compute unit (37 solutes of 32 atoms 19 -> 15 us, 43 of them 19 and 18).
+//     Of 4,000 atoms in solutes of 10, 20, 40, 64, 100 and 200 (1.2 A n^(1/3) a
+//     side) the forward went from 17, 21, 30, 47, 68 and 92 to 20, 22, 29, 36,
+//     45 and 59 us, the backward from 12, 18, 32, 56, 87 and 120 to 28, 31, 42,
+//     54, 67 and 91; of 1,600 in solutes of 4, 10, 40 and 64 the forward from
+//     10, 14, 25 and 36 to 10, 12, 17 and 21, the backward from 8, 9, 22 and 37
+//     to 14, 15, 23 and 30.  Open solutes (2.3 A n^(1/3)), whose centres have
+//     few passes, lose in the backward: of 100 atoms, 4,000 in all, 17 -> 30;
 //   - lists (or systems without one) so long that the LDS holds fewer than
 //     eleven one-wave centres per compute unit, or seven in the backward of
 //     more than 4,096 centres with lists, where most of a row may lie past the
@@ -1249,8 +1250,8 @@ static int waves_for_cap(int cap, int pref) {  // centres per workgroup, a wave 
 constexpr int kGroupWaves = 4;
 static_assert(kMaxChunks * kChunkCounts <= kGroupWaves * kPairPass * 24, "chunk counts of the forward");
 bool aev_grouped(bool bwd, int n_centres, bool list, int cap, size_t max_lds) {
-  if (n_centres <= 1024) return true;
   // (without a list, the capacity is the largest system's other atoms)
+  if (n_centres <= (bwd && !list && cap >= 20 ? 1280 : 1024)) return true;
   if (!list && n_centres <= 4096 && (bwd ? cap > 48 && cap * 50 > n_centres : cap * 300 > n_centres)) return true;
   const size_t per = bwd ? wave_lds_bytes<true>(cap) : wave_lds_bytes<false>(cap);
   return per * (bwd && list && n_centres > 4096 ? 7 : 11) > max_lds;
