@@ -699,7 +699,9 @@ void launch_gemm(int epi, bool bf16, GemmLaunch gl, int row_tiles, int max_n_out
   // 64; for the AEV-gradient GEMM 64 too while 128 would not give every
   // compute unit a workgroup (2,001 atoms: 6.5 us with 64, 8.3 with 128, 10.6
   // with 256; 512 ragged solutes 40, 37 and 41; 6,000 atoms x 8 members 46, 40
-  // and 45; 100,002 x 8 271, 298 and 388)
+  // and 45).  On 100,002 atoms x 8, most of them water, 64 is the faster again
+  // (271, 298 and 388): how few columns are live is not known here, and the
+  // tuner finds it
   const int t128 = (max_n_out + 127) / 128 * 128, t64 = (max_n_out + 63) / 64 * 64;
   int tn = tn_pref == 64 || tn_pref == 128 || tn_pref == 256 ? tn_pref
          : epi == kEpiOut && row_tiles * (t128 / 128) <= 256 ? 64
